@@ -1,0 +1,218 @@
+"""Measured workloads of the quantized linear-layer path: what a program that serves or quantizes a model asks of
+this package, through its public calls.
+
+Two kinds of work.  "linear" is one quantized linear layer as a forward pass runs it: the producer of its input
+(nothing, a normalisation with or without the residual add, an activation function) fused with the token-wise FP8
+quantizer, then the product with the packed weight, with or without the low-rank correction.  The others
+("pack", "lorc", "gptq") are the steps that turn a layer's bfloat16 weight into that packed form.
+
+Sizes are those of the benchmark's layer shapes (inputs.CONFIGS) and ragged ones between them; activations,
+weights and low-rank factors follow the distributions of inputs.py.
+"""
+import math
+
+import torch
+
+from paper_2307_09782_amd import zqfp
+
+# Largest products that a drawn case may ask for: those of the listed cases.
+MAX_LINEAR_MACS = 4096 * 4096 * 12288
+MAX_WEIGHT = 8192 * 28672
+MAX_GPTQ_MACS = 4096 * 4096 * 12288
+
+
+def _linear(name, M, K, N, producer="none", rank=0, G=128, mode=1, out="bf16", accum="exact", weights="fp4", one_call=False):
+    return {"name": name, "kind": "linear", "M": M, "K": K, "N": N, "producer": producer, "rank": rank, "G": G, "mode": mode,
+            "out": out, "accum": accum, "weights": weights, "one_call": one_call}
+
+
+def listed():
+    return [
+        # one token through a square projection, the whole layer in one call: the least a generated token asks for
+        _linear("decode1_attn_out", 1, 4096, 4096, one_call=True),
+        # sixteen sequences decoding: the largest up projection, with the low-rank correction
+        _linear("decode16_ffn_up_lorc", 16, 8192, 28672, producer="rmsnorm", rank=8),
+        # four sequences decoding: gated activation in front of a very long K into few output channels
+        _linear("decode4_ffn_down", 4, 28672, 8192, producer="swiglu"),
+        # a small serving batch (or a verification step of a few drafts) behind the residual add and the norm
+        _linear("batch64_qkv", 64, 4096, 12288, producer="add_rmsnorm"),
+        # a ragged prompt chunk through a down projection
+        _linear("chunk333_ffn_down", 333, 11008, 4096, producer="swiglu"),
+        # a large prompt chunk, fused projections, float32 results
+        _linear("prefill4096_qkv", 4096, 4096, 12288, producer="add_rmsnorm", out="f32"),
+        # prefill with the low-rank correction (as the quantizer's left factor and the product's epilogue)
+        _linear("prefill2048_ffn_lorc", 2048, 5120, 13824, rank=8),
+        # an OPT-shaped layer: layer normalisation, groups of 256, column scales, the one-pass accumulation
+        _linear("prefill2048_fc1_fast", 2048, 2048, 8192, producer="layernorm", G=256, mode=2, accum="fast"),
+        # FP8 weights, a ragged prompt
+        _linear("prefill1000_ffn_up_w8", 1000, 4096, 11008, producer="rmsnorm", weights="fp8"),
+        # quantizing a layer: round to nearest on the FP4 grid
+        {"name": "pack_qkv", "kind": "pack", "K": 4096, "N": 12288, "G": 128, "mode": 1, "weights": "fp4"},
+        # the low-rank factors of the quantization error of a packed layer
+        {"name": "lorc_qkv", "kind": "lorc", "K": 4096, "N": 12288, "G": 128, "mode": 1, "rank": 8, "power_iters": 2},
+        # the same layer quantized with error feedback from calibration data
+        {"name": "gptq_qkv", "kind": "gptq", "K": 4096, "N": 12288, "G": 128, "mode": 1},
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _group(rng, K, sizes):
+    fits = [g for g in sizes if K % g == 0 and K // g <= 256]
+    return rng.choice(fits)
+
+
+def draw(rng):
+    kind = rng.choices(["linear", "pack", "lorc", "gptq"], [10, 1, 1, 1])[0]
+    mode = rng.choice([1, 1, 2])
+    if kind == "linear":
+        weights = "fp8" if rng.random() < 0.15 else "fp4"
+        while True:
+            M = _log_int(rng, 1, 4096)
+            K = 128 * _log_int(rng, 8, 224)
+            N = _log_int(rng, 1024, 28672)
+            if rng.random() < 0.7:  # real layers mostly have round widths; the rest stay odd
+                N = max(1024, N // 128 * 128)
+            if K * N <= MAX_WEIGHT and M * K * N <= MAX_LINEAR_MACS and M * (K + N) <= 4096 * 28672:
+                break
+        producer = rng.choice(["none", "rmsnorm", "add_rmsnorm", "layernorm", "add_layernorm", "relu", "swiglu"])
+        rank = rng.choice([0, 0, 0, 8, 8, 16, 40])
+        G = _group(rng, K, [128, 256, 128 if weights == "fp8" else 64])
+        case = _linear("", M, K, N, producer, rank, G, mode, rng.choice(["bf16", "bf16", "f32"]),
+                       "fast" if rng.random() < 0.15 else "exact", weights, weights == "fp4" and producer == "none" and rng.random() < 0.5)
+        del case["name"]
+        return case
+    K, N = 128 * _log_int(rng, 8, 64), _log_int(rng, 1024, 12288)
+    if rng.random() < 0.7:
+        N = max(1024, N // 128 * 128)
+    if kind == "pack":
+        weights = rng.choice(["fp4", "fp4", "fp8"])
+        return {"kind": kind, "K": K, "N": N, "G": _group(rng, K, [128, 256] if weights == "fp8" else [64, 128, 256]), "mode": mode, "weights": weights}
+    while K * N > 4096 * 12288 or (kind == "gptq" and (K > 6144 or K * K * N > MAX_GPTQ_MACS)):
+        K, N = max(1024, K // 256 * 128), max(1024, N * 3 // 4)
+    if kind == "lorc":
+        return {"kind": kind, "K": K, "N": N, "G": 128, "mode": mode, "rank": rng.choice([8, 8, 16, 32]), "power_iters": rng.choice([1, 2, 2])}
+    return {"kind": kind, "K": K, "N": N, "G": _group(rng, K, [64, 128, 128, 256]), "mode": mode}
+
+
+def _normal(gen, *shape):
+    return torch.randn(*shape, generator=gen, device="cuda", dtype=torch.float32)
+
+
+def _tokens(gen, M, K):
+    """Activations: standard normal with one channel in a hundred scaled up, as behind a normalisation layer."""
+    x = _normal(gen, M, K)
+    x[:, torch.randperm(K, generator=gen, device="cuda")[: K // 100]] *= 20.0
+    return x.bfloat16()
+
+
+def _calibration_factor(gen, K):
+    """Upper Cholesky factor of the inverse Hessian 2 X^T X / n + damping of correlated calibration tokens."""
+    n = 2 * K
+    x = _normal(gen, n, K) * torch.exp(0.5 * _normal(gen, K)) + _normal(gen, n, 32) @ _normal(gen, 32, K)
+    h = (2.0 / n) * (x.t().contiguous() @ x).double()
+    h.diagonal().add_(0.01 * h.diagonal().mean())
+    inv = torch.cholesky_inverse(torch.linalg.cholesky(h))
+    return torch.linalg.cholesky(inv, upper=True).float().contiguous()
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    K, N, G, mode = case["K"], case["N"], case["G"], case["mode"]
+    W = (_normal(gen, K, N) * 0.02).bfloat16()
+    s = dict(case)
+    if case["kind"] != "linear":
+        s["W"] = W
+        if case["kind"] == "lorc":
+            s["packed"] = zqfp.pack_weight_fp4(W, G, mode)
+            s["omega"] = _normal(gen, N, case["rank"] + 8)
+        if case["kind"] == "gptq":
+            s["hinv"] = _calibration_factor(gen, K)
+        return s
+    M, r, producer = case["M"], case["rank"], case["producer"]
+    s["packed"] = zqfp.pack_weight_fp8(W, G, mode) if case["weights"] == "fp8" else zqfp.pack_weight_fp4(W, G, mode)
+    s["U"] = (_normal(gen, K, r) * 0.01).half() if r else None
+    s["V"] = (_normal(gen, r, N) * 0.01).half() if r else None
+    s["X"] = _tokens(gen, M, K)
+    if producer.startswith("add") or producer == "swiglu":
+        s["other"] = _normal(gen, M, K).bfloat16()
+    if "norm" in producer:
+        s["gain"] = (1.0 + 0.1 * _normal(gen, K)).bfloat16()
+        s["bias"] = (0.1 * _normal(gen, K)).bfloat16() if "layernorm" in producer else None
+    return s
+
+
+def _run_linear(s):
+    out = torch.bfloat16 if s["out"] == "bf16" else torch.float32
+    accum = zqfp.ACCUM_FAST if s["accum"] == "fast" else zqfp.ACCUM_EXACT
+    if s["one_call"]:
+        return zqfp.w4a8_linear(s["X"], s["packed"], s["N"], s["G"], s["U"], s["V"], out_dtype=out, accum=accum)
+    producer, U, kept = s["producer"], s["U"], ()
+    if producer == "none":
+        q = zqfp.quantize_act_fp8(s["X"], U)
+    elif producer == "rmsnorm":
+        q = zqfp.rmsnorm_quantize_act_fp8(s["X"], s["gain"], 1e-5, U)
+    elif producer == "layernorm":
+        q = zqfp.layernorm_quantize_act_fp8(s["X"], s["gain"], s["bias"], 1e-5, U)
+    elif producer == "relu":
+        q = zqfp.relu_quantize_act_fp8(s["X"], U)
+    elif producer == "swiglu":
+        q = zqfp.swiglu_quantize_act_fp8(s["X"], s["other"], U)
+    else:  # the updated residual stream is a result of its own
+        h, *q = zqfp.add_norm_quantize_act_fp8(s["X"], s["other"], s["gain"], 1e-5, s["bias"], U)
+        kept = (h,)
+    T, V = (q[2], s["V"]) if U is not None else (None, None)
+    if s["weights"] == "fp8":
+        Y = zqfp.w8a8_gemm(q[0], q[1], s["packed"], s["N"], s["G"], T, V, out_dtype=out, accum=accum)
+    elif U is not None:
+        Y = zqfp.w4a8_gemm_lorc(q[0], q[1], s["packed"], s["N"], s["G"], T, V, out_dtype=out, accum=accum)
+    else:
+        Y = zqfp.w4a8_gemm(q[0], q[1], s["packed"], s["N"], s["G"], out_dtype=out, accum=accum)
+    return (Y, q[0], q[1], *kept)
+
+
+def run(s):
+    if s["kind"] == "linear":
+        return _run_linear(s)
+    if s["kind"] == "pack":
+        return (zqfp.pack_weight_fp8 if s["weights"] == "fp8" else zqfp.pack_weight_fp4)(s["W"], s["G"], s["mode"])
+    if s["kind"] == "lorc":
+        return zqfp.lorc_factorize(s["W"], s["packed"], s["G"], s["rank"], s["omega"], s["power_iters"])
+    return zqfp.gptq_pack_weight_fp4(s["W"], s["hinv"], s["G"], s["mode"])
+
+
+def work(case):
+    K, N = case["K"], case["N"]
+    packed = K * N * (1 if case.get("weights") == "fp8" else 0.5) + K // case["G"] * N + 4 * N
+    if case["kind"] == "pack":
+        return {"bytes": int(2 * K * N + packed), "flops": K * N}
+    if case["kind"] == "lorc":
+        # two products with the error matrix per power iteration and two more, each with rank + 8 columns
+        r = case["rank"]
+        return {"bytes": int(2 * K * N + packed + 4 * N * (r + 8) + 2 * r * (K + N)), "flops": 2 * K * N * (r + 8) * (2 + 2 * case["power_iters"])}
+    if case["kind"] == "gptq":
+        return {"bytes": int(2 * K * N + packed + 2 * K * K), "flops": K * K * N}
+    M, r = case["M"], case["rank"]
+    streams = 2 if case["producer"] == "swiglu" else 3 if case["producer"].startswith("add") else 1
+    codes = 0 if case["one_call"] else M * (K + 4)
+    out = M * N * (2 if case["out"] == "bf16" else 4)
+    return {"bytes": int(2 * M * K * streams + codes + packed + out + 2 * r * (K + N)), "flops": 2 * M * K * N + 2 * M * r * (K + N)}
+
+
+def tolerance(case):
+    if case["kind"] == "pack":
+        return "exact"
+    if case["kind"] == "gptq":
+        # A code whose updated weight lies within rounding error of a grid midpoint may go either way, and the codes
+        # behind it in its column follow: against the same steps in float64, 5e-4 of the codes (1e-3 of the bytes).
+        return {"rel": 0.0, "differ": 4e-3}
+    if case["kind"] == "lorc":
+        # Singular vectors of nearly equal singular values turn into one another under rounding; factors are float16.
+        # Against the same steps in float64: 5e-5, and 1.3e-4 in the worst column.
+        return {"rel": 5e-4, "max": 1e-2}
+    one_pass = case["accum"] == "fast" or case["weights"] == "fp8"  # sums truncated inside the matrix core
+    if case["out"] == "bf16":  # against float64: 2e-5 (a value next to a rounding boundary), 3e-4 with truncated sums
+        return {"rel": 1.3e-3, "max": 1.6e-2} if one_pass else {"rel": 1e-4, "max": 8e-3}
+    return {"rel": 2.4e-4, "max": 4e-3} if one_pass else {"rel": 1e-6, "max": 4e-5}
