@@ -203,7 +203,9 @@ def work(case):
 
 def tolerance(case):
     if case["kind"] == "pack":
-        return "exact"
+        # codes, exponents and scales have one right answer; the padding between the blob's sections (at most 540
+        # bytes of 590 000 in the smallest case) is never written
+        return {"rel": 0.0, "differ": 1e-3}
     if case["kind"] == "gptq":
         # A code whose updated weight lies within rounding error of a grid midpoint may go either way, and the codes
         # behind it in its column follow: against the same steps in float64, 5e-4 of the codes (1e-3 of the bytes).
