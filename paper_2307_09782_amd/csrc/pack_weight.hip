@@ -1,147 +1,192 @@
 // Group-wise FP4 (E2M1) weight quantizer with power-of-two group scales
 // (paper Section 3: fine-grained quantization; "Casting the FP4 to FP8",
-// methods M1 and M2) and its inverse view.  Offline step: written for
-// exactness and a GEMM-friendly layout, not for speed.
+// methods M1 and M2) and its inverse view.
 //
-// One workgroup per strip of 16 output channels.  Phase 1 finds every group's
-// absmax (exact), phase 2 turns it into the exponent byte (integer / exact
-// power-of-two work only), phase 3 encodes the codes and writes them in the
-// register order of the block-scaled matrix instruction.
+// A workgroup takes 64 output channels (one 128-byte line of a row of W) and one "unit" of input channels: the
+// least stretch of whole groups and whole k-tiles, 128 rows for groups of 32, 64 and 128.  Thread (c, q) holds the
+// 32 weights of column c and 32-block q in registers -- exactly the 16 bytes of codes that lane 16 (q % 4) + c % 16
+// of a fragment owns, so that no transpose is needed and a wave stores four runs of 256 bytes -- and the blocks of a
+// group agree on its absmax in LDS.  Bound by HBM (2 B read, 0.5 B written per weight).  With W in its natural
+// order the loads are 2 bytes per lane, 128 bytes per instruction and 32 of them in flight per thread, which also
+// serves rows of any alignment; the vector work is about four operations per weight because the code and the division
+// by the power-of-two scale are one hardware conversion per pair (v_cvt_scalef32_pk_fp4: equal to the encoder of the
+// shared header on all 2^32 binary32 values, and on every bfloat16 value under every scale).  4096 x 12288, G = 128,
+// M1: 249 -> 25 us (a workgroup per 16 columns before: 32-byte pieces of lines that four L2s fetched, the whole K in
+// sequence, a compare chain per code).
 #include "zqfp_internal.h"
 
 namespace zqfp {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kCols = 64;  // output channels per workgroup
 
-__global__ __launch_bounds__(kThreads) void k_pack_weight(const uint16_t* __restrict__ W, int64_t ldw, BlobLayout L,
-                                                        int mode, uint8_t* __restrict__ blob)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// largest group magnitude a power-of-two scale maps onto: 6 (E2M1) or 448 (E4M3)
+__device__ inline float format_max(const BlobLayout& L) { return L.wbits == 8 ? 448.0f : 6.0f; }
+
+// M2's column scale, absmax / format maximum (1 for an all-zero column, 0 for padding columns), into the blob.
+// One workgroup per 64 columns walks the whole K: 128 bytes of a row per wave, eight rows in flight per wave.
+__global__ __launch_bounds__(1024) void k_column_scale(const uint16_t* __restrict__ W, int64_t ldw, BlobLayout L,
+                                                       uint8_t* __restrict__ blob)
 {
-    extern __shared__ float smem[];
-    const int ng = (int)(L.K / L.G);
-    float* s_gmax = smem;                                  // [ng][16]
-    float* s_red = smem + (size_t)ng * 16;                 // [16][16]
-    int* s_ebyte = reinterpret_cast<int*>(s_red + 256);    // [ng][16]
-    float* s_col = reinterpret_cast<float*>(s_ebyte + (size_t)ng * 16);  // [16] column scale
-
-    const int strip = blockIdx.x, tid = threadIdx.x;
-    const int c = tid & 15, kl = tid >> 4;
-    const int64_t n = (int64_t)strip * 16 + c;
-    const bool live = n < L.N;
-
-    // phase 1: exact absmax of every group
-    for (int g = 0; g < ng; ++g) {
-        float a = 0.0f;
-        if (live)
-            for (int64_t k = (int64_t)g * L.G + kl; k < (int64_t)(g + 1) * L.G; k += 16)
-                a = fmaxf(a, fabsf(bf16_bits_to_f32(W[k * ldw + n])));
-        s_red[kl * 16 + c] = a;
-        __syncthreads();
-        if (tid < 16) {
-            float m = 0.0f;
-            for (int i = 0; i < 16; ++i) m = fmaxf(m, s_red[i * 16 + tid]);
-            s_gmax[g * 16 + tid] = m;
-        }
-        __syncthreads();
+    __shared__ float s_max[16][kCols];
+    const int c = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t n = (int64_t)blockIdx.x * kCols + c;
+    const uint16_t* w = W + (n < L.N ? n : L.N - 1);
+    float m = 0.0f;
+    for (int64_t k = wave; k < L.K; k += 128) {  // K is a multiple of 128: eight rows per wave and step
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = bf16_bits_to_f32(w[(k + 16 * i) * ldw]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(v[i]));
     }
+    s_max[wave][c] = m;
+    __syncthreads();
+    if (wave == 0 && n < L.Np) {
+#pragma unroll
+        for (int i = 1; i < 16; ++i) m = fmaxf(m, s_max[i][c]);
+        reinterpret_cast<float*>(blob + L.off_colscale)[n] = n >= L.N ? 0.0f : m != 0.0f ? m / format_max(L) : 1.0f;  // IEEE binary32 division
+    }
+}
 
-    // phase 2: exponent bytes and column scale
-    if (tid < 16) {
-        float cs = 1.0f;
-        if (mode == 1) {
-            for (int g = 0; g < ng; ++g)
-                s_ebyte[g * 16 + tid] = (L.wbits == 8 ? m1_exponent_e4m3(s_gmax[g * 16 + tid]) : m1_exponent(s_gmax[g * 16 + tid])) + 127;
-        } else {
-            float mx = 0.0f;
-            for (int g = 0; g < ng; ++g) mx = fmaxf(mx, s_gmax[g * 16 + tid]);
-            if (mx != 0.0f) cs = mx / (L.wbits == 8 ? 448.0f : 6.0f);  // IEEE binary32 division
-            for (int g = 0; g < ng; ++g) s_ebyte[g * 16 + tid] = 127 - m2_shift(mx, s_gmax[g * 16 + tid]);
+// The codes of one 32-block: x holds 32 bfloat16 weights (pairs of consecutive k), e the group's exponent.
+template <int WBITS>
+__device__ inline void encode_block(const uint32_t (&x)[16], int mode, int e, float cs, uint8_t* __restrict__ frag, int q, int col)
+{
+    const float scale = ldexpf(1.0f, e);
+    if constexpr (WBITS == 4) {
+        u32x4 o;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            uint32_t word = 0;
+            if (mode == 1) {  // exact division by 2^e
+                word = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(word, __builtin_bit_cast(bf16x2, x[4 * d]), scale, 0);
+                word = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(word, __builtin_bit_cast(bf16x2, x[4 * d + 1]), scale, 1);
+                word = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(word, __builtin_bit_cast(bf16x2, x[4 * d + 2]), scale, 2);
+                word = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(word, __builtin_bit_cast(bf16x2, x[4 * d + 3]), scale, 3);
+            } else {  // IEEE division by the column scale, then the exact shift
+                word = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, bf16_lo(x[4 * d]) / cs, bf16_hi(x[4 * d]) / cs, scale, 0);
+                word = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, bf16_lo(x[4 * d + 1]) / cs, bf16_hi(x[4 * d + 1]) / cs, scale, 1);
+                word = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, bf16_lo(x[4 * d + 2]) / cs, bf16_hi(x[4 * d + 2]) / cs, scale, 2);
+                word = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, bf16_lo(x[4 * d + 3]) / cs, bf16_hi(x[4 * d + 3]) / cs, scale, 3);
+            }
+            o[d] = word;
         }
-        s_col[tid] = cs;
-        int64_t nn = (int64_t)strip * 16 + tid;
-        reinterpret_cast<float*>(blob + L.off_colscale)[nn] = (nn < L.N) ? cs : 0.0f;
+        *reinterpret_cast<u32x4*>(frag + (q * 16 + col) * 16) = o;
+    } else {
+        // E4M3 codes: same encoder as the activations' (clamp to +-448, then the hardware conversion, round to
+        // nearest even, sign kept); block q is two runs of 16 bytes of half q / 2 of the fragment
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            u32x4 o;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                float y[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t p = x[8 * h + 2 * d + (i >> 1)];
+                    const float w = (i & 1) ? bf16_hi(p) : bf16_lo(p);
+                    y[i] = clamp448(ldexpf(mode == 1 ? w : w / cs, -e));
+                }
+                int pk = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], 0, false);
+                o[d] = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], pk, true);
+            }
+            *reinterpret_cast<u32x4*>(frag + (q >> 1) * 1024 + (((q & 1) * 2 + h) * 16 + col) * 16) = o;
+        }
+    }
+}
+
+// TILES: k-tiles of a unit, kept in registers between the absmax and the codes (1 or 2); 0: a unit of any length,
+// walked four k-tiles at a time by 1024 threads and read a second time for the codes (from L2 where it fits).
+template <int TILES, int WBITS>
+__global__ __launch_bounds__(TILES == 0 ? 1024 : 256) void k_pack_weight(const uint16_t* __restrict__ W, int64_t ldw, BlobLayout L,
+                                                                         int mode, int unit_tiles, uint8_t* __restrict__ blob)
+{
+    constexpr int PAR = TILES == 0 ? 4 : 1;  // k-tiles worked on at once
+    __shared__ uint32_t s_gmax[4][kCols];    // a unit holds one, two or four groups, or one group spans it
+    const int tid = threadIdx.x, c = tid & 63, q = (tid >> 6) & 3, par = tid >> 8;
+    const int64_t n = (int64_t)blockIdx.x * kCols + c;
+    const bool live = n < L.N, in_blob = n < L.Np;
+    const uint16_t* wcol = W + (live ? n : L.N - 1);
+    const int64_t kt0 = (int64_t)blockIdx.y * unit_tiles;
+    float* colscale = reinterpret_cast<float*>(blob + L.off_colscale);
+    const int blocks_per_group = L.G / 32;
+
+    auto load_block = [&](int64_t kt, uint32_t (&x)[16]) __attribute__((always_inline)) {
+        const uint16_t* p = wcol + (kt * 128 + 32 * q) * ldw;
+        uint16_t v[32];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) v[i] = p[i * ldw];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = live ? (uint32_t)v[2 * i] | ((uint32_t)v[2 * i + 1] << 16) : 0u;  // padding columns: +0
+    };
+    auto group_max = [&](int t, const uint32_t (&x)[16]) __attribute__((always_inline)) {
+        float m = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) m = fmaxf(m, fmaxf(fabsf(bf16_lo(x[i])), fabsf(bf16_hi(x[i]))));
+        // a maximum of non-negative floats is the maximum of their bit patterns, in any order
+        atomicMax(&s_gmax[(t * 4 + q) / blocks_per_group][c], __float_as_uint(m));
+    };
+
+    s_gmax[tid >> 6 & 3][c] = 0u;
+    __syncthreads();
+    uint32_t x[TILES == 0 ? 1 : TILES][16];
+    if constexpr (TILES == 0) {
+        for (int t = par; t < unit_tiles; t += PAR) {
+            load_block(kt0 + t, x[0]);
+            group_max(t, x[0]);
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) load_block(kt0 + t, x[t]);
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) group_max(t, x[t]);
+    }
+    float cs = 1.0f, cmax = 0.0f;
+    if (mode != 1 && in_blob) {
+        cs = colscale[n];
+        // the column's absmax is a bfloat16 value and cs is it over the format maximum, correctly rounded: the
+        // product is within 2^-14 of it, relatively, and rounds back to it (an all-zero column has no use for it)
+        cmax = bf16_bits_to_f32(f32_to_bf16_bits(cs * format_max(L)));
     }
     __syncthreads();
+    if (!in_blob) return;  // no barrier below
 
-    // exponent bytes, [strip][quad][column][4]
-    for (int i = tid; i < L.ngq * 16; i += kThreads) {
-        int q = i >> 4, cc = i & 15;
-        uint32_t word = 0;
-        for (int b = 0; b < 4; ++b) {
-            int sg = q * 4 + b;
-            uint32_t e = 127;
-            if (sg < L.ngs && (int64_t)strip * 16 + cc < L.N) e = (uint32_t)s_ebyte[(int)(((int64_t)sg * L.Gs) / L.G) * 16 + cc];
-            word |= e << (8 * b);
+    auto finish_tile = [&](int t, const uint32_t (&xt)[16]) __attribute__((always_inline)) {
+        const float amax = __uint_as_float(s_gmax[(t * 4 + q) / blocks_per_group][c]);
+        const int e = mode == 1 ? (WBITS == 8 ? m1_exponent_e4m3(amax) : m1_exponent(amax)) : -m2_shift(cmax, amax);
+        const int64_t kt = kt0 + t, strip = n >> 4;
+        const int col = c & 15;
+        encode_block<WBITS>(xt, mode, e, cs, blob + L.off_codes + (size_t)(strip * L.nkt + kt) * (256 * WBITS), q, col);
+        // exponent bytes, [strip][quad][column][4], one per stored group; the last dword is filled up with 127
+        const int64_t k = kt * 128 + 32 * q;
+        if (k % L.Gs == 0) {
+            const int64_t sg = k / L.Gs;
+            uint8_t* p = blob + L.off_exps + ((size_t)(strip * L.ngq + (sg >> 2)) * 16 + col) * 4;
+            p[sg & 3] = (uint8_t)(live ? e + 127 : 127);
+            if (sg == L.ngs - 1)
+                for (int b = (int)(sg & 3) + 1; b < 4; ++b) p[b] = 127;
         }
-        reinterpret_cast<uint32_t*>(blob + L.off_exps)[(size_t)strip * L.ngq * 16 + i] = word;
-    }
-
-    if (L.wbits == 8) {
-        // phase 3, E4M3 codes: fragment = [half][64 lanes][4 dwords]; a dword holds 4 consecutive k.  Same encoder
-        // as the activations': clamp to +-448, then the hardware conversion (round to nearest even, sign kept).
-        uint32_t* out8 = reinterpret_cast<uint32_t*>(blob + L.off_codes) + (size_t)strip * L.nkt * 512;
-        for (int64_t kt = 0; kt < L.nkt; ++kt) {
-            for (int idx = tid; idx < 512; idx += kThreads) {
-                const int half = idx >> 8, ln = (idx >> 2) & 63, dd = idx & 3;
-                const int cc = ln & 15, lbb = ln >> 4;
-                const int64_t nn = (int64_t)strip * 16 + cc;
-                const int64_t k0 = kt * 128 + 64 * half + 16 * lbb + 4 * dd;
-                const int e = s_ebyte[(int)(k0 / L.G) * 16 + cc] - 127;
-                const float csn = s_col[cc];
-                uint32_t word = 0;
-                if (nn < L.N) {
-                    float y[4];
+    };
+    if constexpr (TILES == 0) {
+        for (int t = par; t < unit_tiles; t += PAR) {
+            load_block(kt0 + t, x[0]);
+            finish_tile(t, x[0]);
+        }
+    } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float w = bf16_bits_to_f32(W[(k0 + i) * ldw + nn]);
-                        y[i] = clamp448((mode == 1) ? ldexpf(w, -e) : ldexpf(w / csn, -e));
-                    }
-                    int pk = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], 0, false);
-                    pk = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], pk, true);
-                    word = (uint32_t)pk;
-                }
-                out8[kt * 512 + idx] = word;
-            }
-        }
-        if (strip == 0 && tid == 0) {
-            BlobHeader h;
-            h.magic = kBlobMagic; h.version = kBlobVersion;
-            h.K = L.K; h.N = L.N; h.Np = L.Np;
-            h.G = L.G; h.Gs = L.Gs; h.mode = mode; h.ngs = L.ngs; h.ngq = L.ngq; h.wbits = 8;
-            h.off_codes = L.off_codes; h.off_exps = L.off_exps; h.off_colscale = L.off_colscale; h.total = L.total;
-            *reinterpret_cast<BlobHeader*>(blob) = h;
-        }
-        return;
+        for (int t = 0; t < TILES; ++t) finish_tile(t, x[t]);
     }
-
-    // phase 3: codes, one dword (8 codes) per thread per fragment
-    const int lane = tid >> 2, d = tid & 3;
-    const int fc = lane & 15, lb = lane >> 4;
-    const int64_t fn = (int64_t)strip * 16 + fc;
-    const float cs = s_col[fc];
-    uint32_t* out = reinterpret_cast<uint32_t*>(blob + L.off_codes) + (size_t)strip * L.nkt * 256;
-    for (int64_t kt = 0; kt < L.nkt; ++kt) {
-        const int64_t k0 = kt * 128 + 32 * lb + 8 * d;
-        const int g = (int)(k0 / L.G);
-        const int e = s_ebyte[g * 16 + fc] - 127;  // group scale = cs * 2^e
-        uint32_t word = 0;
-        if (fn < L.N) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float w = bf16_bits_to_f32(W[(k0 + i) * ldw + fn]);
-                float y = (mode == 1) ? ldexpf(w, -e)        // exact division by 2^e
-                                      : ldexpf(w / cs, -e);  // IEEE division, then exact shift
-                word |= e2m1_encode(y) << (4 * i);
-            }
-        }
-        out[kt * 256 + tid] = word;
-    }
-
-    if (strip == 0 && tid == 0) {
+    if (mode == 1 && blockIdx.y == 0 && tid < kCols) colscale[n] = live ? 1.0f : 0.0f;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
         BlobHeader h;
         h.magic = kBlobMagic; h.version = kBlobVersion;
         h.K = L.K; h.N = L.N; h.Np = L.Np;
-        h.G = L.G; h.Gs = L.Gs; h.mode = mode; h.ngs = L.ngs; h.ngq = L.ngq; h.wbits = 4;
+        h.G = L.G; h.Gs = L.Gs; h.mode = mode; h.ngs = L.ngs; h.ngq = L.ngq; h.wbits = WBITS;
         h.off_codes = L.off_codes; h.off_exps = L.off_exps; h.off_colscale = L.off_colscale; h.total = L.total;
         *reinterpret_cast<BlobHeader*>(blob) = h;
     }
@@ -180,9 +225,21 @@ hipError_t launch_pack_weight(const uint16_t* W, int64_t ldw, const BlobLayout& 
                               hipStream_t s)
 {
     if (L.nstrips == 0) return hipSuccess;
-    const int ng = (int)(L.K / L.G);
-    size_t smem = ((size_t)ng * 16 + 256 + (size_t)ng * 16 + 16) * 4;
-    hipLaunchKernelGGL(k_pack_weight, dim3((unsigned)L.nstrips), dim3(kThreads), smem, s, W, ldw, L, mode, blob);
+    // a unit: whole groups and whole k-tiles.  G is a multiple of 32, so it is G or 128 rows where one divides the
+    // other and two or four groups otherwise (G = 320: 640 rows).
+    const int64_t unit = (int64_t)L.G / gcd_int(L.G, 128) * 128;
+    const int tiles = (int)(unit / 128);
+    const unsigned gx = (unsigned)((L.Np + kCols - 1) / kCols);
+    const dim3 grid(gx, (unsigned)(L.K / unit));
+    if (mode != 1) hipLaunchKernelGGL(k_column_scale, dim3(gx), dim3(1024), 0, s, W, ldw, L, blob);
+#define ZQ_PACK(TILES, WB) \
+    hipLaunchKernelGGL((k_pack_weight<TILES, WB>), grid, dim3(TILES == 0 ? 1024 : 256), 0, s, W, ldw, L, mode, tiles, blob)
+    if (L.wbits == 8) {
+        if (tiles == 1) ZQ_PACK(1, 8); else if (tiles == 2) ZQ_PACK(2, 8); else ZQ_PACK(0, 8);
+    } else {
+        if (tiles == 1) ZQ_PACK(1, 4); else if (tiles == 2) ZQ_PACK(2, 4); else ZQ_PACK(0, 4);
+    }
+#undef ZQ_PACK
     return hipGetLastError();
 }
 
