@@ -147,7 +147,7 @@ __global__ __launch_bounds__(TILES == 0 ? 1024 : 256) void k_pack_weight(const u
         for (int t = 0; t < TILES; ++t) group_max(t, x[t]);
     }
     float cs = 1.0f, cmax = 0.0f;
-    if (mode != 1 && in_blob) {
+    if (mode != 1 && live) {  // padding columns: +0 over 1
         cs = colscale[n];
         // the column's absmax is a bfloat16 value and cs is it over the format maximum, correctly rounded: the
         // product is within 2^-14 of it, relatively, and rounds back to it (an all-zero column has no use for it)

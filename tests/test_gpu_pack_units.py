@@ -31,6 +31,9 @@ def test_fp4_units_bit_exact(K, N, G, mode):
     codes_o, exps_o, c_o, _ = oracle.pack_weight(W, G, mode)
     assert np.array_equal(codes, codes_o) and np.array_equal(exps, exps_o) and bits_equal_f32(c, c_o)
     zqfp.packed_weight_check(packed, K, N, G)
+    strips = (N + 15) // 16
+    last = packed[256:256 + strips * 8 * K].view(strips, K // 128, 4, 16, 16)[-1, :, :, N - 16 * (strips - 1):]
+    assert int(last.count_nonzero()) == 0  # padding columns hold zero codes
 
 
 @pytest.mark.parametrize("mode", [1, 2])
