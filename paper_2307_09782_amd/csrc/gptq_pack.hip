@@ -5,38 +5,134 @@
 // Input channels (rows of the K x N weight) are quantized in order; the scaled error of channel k is pushed
 // onto the channels behind it with row k of U, the upper Cholesky factor of the inverse Hessian:
 //     q_k = S e2m1(w_k / S);  err = (w_k - q_k) / U[k][k];  w_j -= U[k][j] err   (j > k).
-// Output channels never interact, so a lane owns one output channel.  Rows are taken in blocks of B = 128
-// (256 for groups of 256, so that a group never straddles a block): inside a block the updates are applied at
-// once, on the block's B x 64 slab held in LDS; the rows behind the block receive the block's B errors in
-// one float32 matrix product (rows of U through the scalar cache, error rows through LDS).
+// Output channels never interact, so ONE launch does everything: a workgroup owns C = 16 ... 64 output channels for
+// the whole of K and never waits for another.  It takes the rows in panels of 128.  A panel is first brought up to
+// date with all earlier channels at once,
+//     w[i][n] -= sum_{k < i0} U[k][i] err[k][n],
+// a float32 matrix product with the errors the workgroup itself has left in its part of the workspace: the four waves
+// split k and each accumulates the whole 128 x C panel in registers on the float32 matrix cores
+// (v_mfma_f32_16x16x4_f32; operands straight from L2, 16 bytes per lane, with the rows and columns of the panel
+// dealt to the instructions such that a lane's four consecutive floats feed four instructions).  Then the panel is
+// quantized in sub-blocks of 16 rows: one wave runs the serial chain with the 16 x C values in registers (lane =
+// channel), while the other three push the previous sub-block's errors onto the rows further down, again on the
+// matrix cores, out of LDS.
+//
+// K^2 N / 2 multiply-adds are the bound: 1.34 ms at the 154 TFLOP/s that a large float32 product reaches, for
+// 4096 x 12288; K^2 / 2 floats of U per workgroup come from L2.  C is the least that lets every workgroup have a
+// compute unit of its own, so that N = 4096 runs on all of them as N = 12288 does.
 #include "zqfp_internal.h"
 
 namespace zqfp {
 namespace {
 
-// Working copy of W in float32, column absmax of the original W, and the blob's frame: header, zero codes,
-// exponent bytes 127, column scales (1 under M1, absmax / 6 under M2, 0 for padding columns).
-__global__ __launch_bounds__(256) void k_gptq_init(const uint16_t* __restrict__ W, int64_t ldw, BlobLayout L, int mode,
-                                                   float* __restrict__ Wf, float* __restrict__ colmax, uint8_t* __restrict__ blob)
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+
+constexpr int kPanel = 128;  // rows brought up to date at once
+constexpr int kSub = 16;     // rows quantized by one serial chain
+
+// NT floats in a row, 4-byte aligned (one load of 4 NT bytes)
+template <int NT>
+struct __attribute__((packed, aligned(4))) Floats {
+    float v[NT];
+};
+
+// acc[h][r][t] += sum_{k in [ka, kb)} U[k][i0 + row] err[k][col], this wave's quarter of the k (chunks of 16, or of 8
+// where 64 columns leave fewer registers, dealt in turn; kb - ka is a multiple of 128).  Instruction (h, r, t) holds rows 64 h + 4 i + r (i = 0..15) and columns
+// NT j + t (j = 0..15): a lane's 16 bytes of a row of U are the A operands of four instructions.
+template <int NT>
+__device__ __forceinline__ void accumulate_panel(v4f (&acc)[2][4][NT], const float* __restrict__ U, int64_t K, int64_t i0,
+                                                 const float* err, int64_t ka, int64_t kb, int wave, int lane)
 {
-    const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x, nthreads = (int64_t)gridDim.x * 256;
-    uint32_t* codes = reinterpret_cast<uint32_t*>(blob + L.off_codes);
-    for (int64_t i = tid; i < (int64_t)((L.off_exps - L.off_codes) / 4); i += nthreads) codes[i] = 0u;
-    uint32_t* exps = reinterpret_cast<uint32_t*>(blob + L.off_exps);
-    for (int64_t i = tid; i < L.nstrips * L.ngq * 16; i += nthreads) exps[i] = 0x7F7F7F7Fu;
-    float* cs = reinterpret_cast<float*>(blob + L.off_colscale);
-    for (int64_t n = tid; n < L.Np; n += nthreads) {
-        float mx = 0.0f;
-        if (n < L.N)
-            for (int64_t k = 0; k < L.K; ++k) {
-                const float w = bf16_bits_to_f32(W[k * ldw + n]);
-                Wf[k * L.N + n] = w;
-                mx = fmaxf(mx, fabsf(w));
-            }
-        if (n < L.N) colmax[n] = mx;
-        cs[n] = n >= L.N ? 0.0f : mode == 1 ? 1.0f : mx != 0.0f ? mx / 6.0f : 1.0f;  // IEEE binary32 division
+    constexpr int C = 16 * NT;
+    const int j = lane & 15, lb = lane >> 4;
+    constexpr int S = NT == 4 ? 2 : 4;             // steps of 4 k in a chunk
+    const int n = (int)((kb - ka) / (16 * S));     // chunks of this wave: even
+    struct Chunk {
+        v4f a[S][2];
+        Floats<NT> b[S];
+    };
+    auto load = [&](Chunk& c, int i) __attribute__((always_inline)) {
+        const int64_t k0 = ka + 4 * S * (4 * (int64_t)min(i, n - 1) + wave) + lb;  // past the end: the last one again, unused
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const float* u = U + (k0 + 4 * s) * K + i0 + 4 * j;
+            c.a[s][0] = *reinterpret_cast<const v4f*>(u);
+            c.a[s][1] = *reinterpret_cast<const v4f*>(u + 64);
+            c.b[s] = *reinterpret_cast<const Floats<NT>*>(err + (k0 + 4 * s) * C + NT * j);
+        }
+    };
+    auto multiply = [&](const Chunk& c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        acc[h][r][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.a[s][h][r], c.b[s].v[t], acc[h][r][t], 0, 0, 0);
+    };
+    if (n == 0) return;
+    Chunk c0, c1;
+    load(c0, 0);
+    for (int i = 0; i < n; i += 2) {
+        load(c1, i + 1);
+        multiply(c0);
+        load(c0, i + 2);
+        multiply(c1);
     }
-    if (tid == 0) {
+}
+
+template <int NT>
+__global__ __launch_bounds__(256, 2) void k_gptq(const uint16_t* __restrict__ W, int64_t ldw, const float* __restrict__ U, BlobLayout L,
+                                                 int mode, float* ws_err, float* ws_held, uint8_t* __restrict__ blob)
+{
+    constexpr int C = 16 * NT;
+    constexpr int LDW = C + 4;    // slab row: the four row groups of a 16 x 16 tile fall on disjoint banks
+    constexpr int LDE = C + 16;   // error row, for the same reason
+    constexpr int LDU = kPanel + 16;
+    __shared__ __attribute__((aligned(16))) float s_w[kPanel][LDW];       // the panel's weights as they stand
+    __shared__ __attribute__((aligned(16))) float s_u[2][kSub][LDU];      // a sub-block's rows of U, columns of the panel
+    __shared__ float s_rdiag[2][kSub];                                    // 1 / U[k][k]
+    __shared__ float s_err[2][kSub][LDE];                                 // a sub-block's errors, negated
+    __shared__ float s_amax[4][C];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j16 = lane & 15, lb = lane >> 4;
+    const int64_t n0 = (int64_t)blockIdx.x * C;
+    const int64_t K = L.K;
+    float* err = ws_err + (int64_t)blockIdx.x * K * C;            // [K][C], this workgroup's own
+    float* held = ws_held + (int64_t)blockIdx.x * kPanel * C;     // [128][C]: groups of 256 only
+    float* colscale = reinterpret_cast<float*>(blob + L.off_colscale);
+
+    // the channel of this lane where a wave's lanes are channels
+    const int64_t n = n0 + lane;
+    const bool chan = lane < C && n < L.Np, live = lane < C && n < L.N;
+
+    // ---- column scales (M2: from the original column) and header
+    float cmax = 0.0f, cs = 1.0f;
+    if (mode != 1) {
+        float m = 0.0f;
+        if (live)
+            for (int64_t k = wave; k < K; k += 32) {  // K is a multiple of 128
+                float v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = bf16_bits_to_f32(W[(k + 4 * i) * ldw + n]);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(v[i]));
+            }
+        if (lane < C) s_amax[wave][lane] = m;
+        __syncthreads();
+        if (lane < C) cmax = fmaxf(fmaxf(s_amax[0][lane], s_amax[1][lane]), fmaxf(s_amax[2][lane], s_amax[3][lane]));
+        if (cmax != 0.0f) cs = cmax / 6.0f;  // IEEE binary32 division
+        __syncthreads();
+    }
+    if (wave == 0 && chan) colscale[n] = live ? cs : 0.0f;
+    // w / c in the chain below: lifted by 2^60 in columns so small that its residuals would leave the normal range
+    const float lift = cs < 0x1p-60f ? 0x1p60f : 1.0f, lcs = cs * lift, rcs = 1.0f / lcs;
+    if (blockIdx.x == 0 && tid == 0) {
         BlobHeader h;
         h.magic = kBlobMagic; h.version = kBlobVersion;
         h.K = L.K; h.N = L.N; h.Np = L.Np;
@@ -44,136 +140,208 @@ __global__ __launch_bounds__(256) void k_gptq_init(const uint16_t* __restrict__ 
         h.off_codes = L.off_codes; h.off_exps = L.off_exps; h.off_colscale = L.off_colscale; h.total = L.total;
         *reinterpret_cast<BlobHeader*>(blob) = h;
     }
-}
 
-// Rows [i0, i0 + B) of the working copy, 64 output channels per workgroup (one wave, lane = channel).
-__global__ __launch_bounds__(64) void k_gptq_block(float* __restrict__ Wf, const float* __restrict__ U, BlobLayout L, int mode,
-                                                  int B, int64_t i0, const float* __restrict__ colmax,
-                                                  float* __restrict__ Err, uint8_t* __restrict__ blob)
-{
-    extern __shared__ float s_w[];  // [B][64]
-    const int lane = threadIdx.x;
-    const int64_t n = (int64_t)blockIdx.x * 64 + lane;
-    if (n >= L.N) return;  // a lane works on its own column only: nothing below synchronises
-    for (int r = 0; r < B; ++r) s_w[r * 64 + lane] = Wf[(i0 + r) * L.N + n];
-    const float cs = reinterpret_cast<const float*>(blob + L.off_colscale)[n];
-    const float cmax = colmax[n];
+    // panel i0 as it stands after channels < kb, into s_w: from the weights and the errors of [0, kb), or from the held
+    // copy (which has seen the channels before ka) and the errors of [ka, kb).  Ends behind a barrier.
+    auto bring_up_to_date = [&](int64_t i0, int64_t ka, int64_t kb) __attribute__((always_inline)) {
+        v4f acc[2][4][NT];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[h][r][t] = (v4f){0.f, 0.f, 0.f, 0.f};
+        for (int idx = tid; idx < kPanel * C; idx += 256) {
+            const int r = idx / C, c = idx % C;
+            s_w[r][c] = ka > 0 ? held[idx] : n0 + c < L.N ? bf16_bits_to_f32(W[(i0 + r) * ldw + n0 + c]) : 0.0f;
+        }
+        accumulate_panel<NT>(acc, U, K, i0, err, ka, kb, wave, lane);
+        // the waves' sums come off in four rounds, a quarter of the rows each, so that all four work: a fixed order
+        for (int round = 0; round < 4; ++round) {
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (((wave + round) & 3) == q) {
+#pragma unroll
+                    for (int rr = 0; rr < 2; ++rr)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int h = q >> 1, r = 2 * (q & 1) + rr;
+                            float* w = &s_w[64 * h + 16 * lb + 4 * i + r][NT * j16];
+#pragma unroll
+                            for (int t = 0; t < NT; ++t) w[t] -= acc[h][r][t][i];
+                        }
+                }
+        }
+        __syncthreads();
+    };
+    // absmax of `rows` rows of s_w from row r0 on, per channel, over all four waves; combined by combined_max()
+    auto partial_max = [&](int r0, int rows, float m) __attribute__((always_inline)) {
+        if (lane < C) {
+            for (int r = wave; r < rows; r += 4) m = fmaxf(m, fabsf(s_w[r0 + r][lane]));
+            s_amax[wave][lane] = m;
+        }
+        return m;
+    };
+    // rows of U of the sub-block at row k0 = i0 + 16 t, columns i0 + [0, 128): thread -> 8 floats
+    auto fetch_u = [&](v4f (&u)[2], float& d, int64_t k0, int64_t i0) __attribute__((always_inline)) {
+        const float* p = U + (k0 + (tid >> 4)) * K + i0 + 8 * (tid & 15);
+        u[0] = *reinterpret_cast<const v4f*>(p);
+        u[1] = *reinterpret_cast<const v4f*>(p + 4);
+        d = U[(k0 + (tid & 15)) * K + k0 + (tid & 15)];
+    };
+    auto store_u = [&](const v4f (&u)[2], float d, int buf) __attribute__((always_inline)) {
+        float* p = &s_u[buf][tid >> 4][8 * (tid & 15)];
+        *reinterpret_cast<v4f*>(p) = u[0];
+        *reinterpret_cast<v4f*>(p + 4) = u[1];
+        if (tid < kSub) s_rdiag[buf][tid] = 1.0f / d;  // IEEE binary32 division: correctly rounded
+    };
+    // 16 x 16 tile (row block rb of the panel, column block cb) -= its share of a sub-block's errors
+    auto push_tile = [&](int rb, int cb, int buf) __attribute__((always_inline)) {
+        v4f a;
+        float* w = &s_w[16 * rb + 4 * lb][16 * cb + j16];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] = w[q * LDW];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            a = __builtin_amdgcn_mfma_f32_16x16x4f32(s_u[buf][4 * s + lb][16 * rb + j16], s_err[buf][4 * s + lb][16 * cb + j16], a, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[q * LDW] = a[q];
+    };
+
+    int e = 0;                     // the current group's exponent (wave 0's lanes)
+    uint32_t ebytes = 0x7F7F7F7Fu;  // and the dword of exponent bytes being filled
     const int64_t strip = n >> 4;
-    const int c = (int)(n & 15);
-    uint8_t* code_bytes = blob + L.off_codes;
-    uint8_t* exp_bytes = blob + L.off_exps;
-    int e = 0;
-    float S = 1.0f;
-    uint32_t low = 0;
-    for (int j = 0; j < B; ++j) {
-        const int64_t k = i0 + j;
-        if (k % L.G == 0) {  // a new group: its scale from the weights as they stand now
-            float amax = 0.0f;
-            for (int g = 0; g < L.G; ++g) amax = fmaxf(amax, fabsf(s_w[(j + g) * 64 + lane]));
-            e = mode == 1 ? m1_exponent(amax) : -m2_shift(cmax, amax);
-            S = mode == 1 ? ldexpf(1.0f, e) : ldexpf(cs, e);
-            const int64_t sg = k / L.Gs;  // G is 32, 64, 128 or 256 here: stored groups are the groups
-            exp_bytes[((size_t)(strip * L.ngq + (sg >> 2)) * 16 + c) * 4 + (sg & 3)] = (uint8_t)(e + 127);
-        }
-        const float w = s_w[j * 64 + lane];
-        const float y = mode == 1 ? ldexpf(w, -e) : ldexpf(w / cs, -e);
-        const uint32_t code = e2m1_encode(y);
-        const float q = mode == 1 ? ldexpf(e2m1_value(code), e) : ldexpf(e2m1_value(code), e) * cs;
-        const float* urow = U + k * L.K + i0;  // the same for every lane
-        const float err = (w - q) / urow[j];
-        Err[(int64_t)j * L.N + n] = err;
-        for (int jj = j + 1; jj < B; ++jj) s_w[jj * 64 + lane] = fmaf(-urow[jj], err, s_w[jj * 64 + lane]);
-        if ((k & 1) == 0) {
-            low = code;
+    for (int64_t i0 = 0; i0 < K; i0 += kPanel) {
+        // ---- the panel, and the absmax of a group that begins with it
+        if (L.G == 256) {
+            if ((i0 & 255) == 0) {  // the group's second panel comes first and waits in the workspace
+                bring_up_to_date(i0 + kPanel, 0, i0);
+                const float m = partial_max(0, kPanel, 0.0f);
+                for (int idx = tid; idx < kPanel * C; idx += 256) held[idx] = s_w[idx / C][idx % C];
+                __syncthreads();
+                bring_up_to_date(i0, 0, i0);
+                partial_max(0, kPanel, m);
+            } else {
+                bring_up_to_date(i0, i0 - kPanel, i0);
+            }
         } else {
-            const int kk = (int)(k & 127), lb = kk >> 5, p = kk & 31;
-            code_bytes[((size_t)(strip * L.nkt + (k >> 7)) * 64 + (lb * 16 + c)) * 16 + (p >> 1)] = (uint8_t)(low | (code << 4));
+            bring_up_to_date(i0, 0, i0);
+            partial_max(0, L.G, 0.0f);
+        }
+        v4f u[2];
+        float d;
+        fetch_u(u, d, i0, i0);
+        store_u(u, d, 0);
+        fetch_u(u, d, i0 + kSub, i0);
+        __syncthreads();
+
+        for (int t = 0; t < kPanel / kSub; ++t) {
+            const int buf = t & 1;
+            const int64_t k0 = i0 + kSub * t;
+            if (wave == 0) {
+                // ---- the serial chain of sub-block t, lane = channel
+                if (lane < C) {
+                    if (k0 % L.G == 0) {  // a new group: its scale from the weights as they stand now
+                        const float amax = fmaxf(fmaxf(s_amax[0][lane], s_amax[1][lane]), fmaxf(s_amax[2][lane], s_amax[3][lane]));
+                        e = mode == 1 ? m1_exponent(amax) : -m2_shift(cmax, amax);
+                        const int64_t sg = k0 / L.Gs;  // G is 32, 64, 128 or 256 here: stored groups are the groups
+                        const int b = (int)(sg & 3);
+                        if (b == 0) ebytes = 0x7F7F7F7Fu;
+                        ebytes = (ebytes & ~(0xFFu << (8 * b))) | ((uint32_t)(live ? e + 127 : 127) << (8 * b));
+                        if (chan && (b == 3 || sg == L.ngs - 1))
+                            reinterpret_cast<uint32_t*>(blob + L.off_exps)[(size_t)(strip * L.ngq + (sg >> 2)) * 16 + (lane & 15)] = ebytes;
+                    }
+                    const float scale = ldexpf(1.0f, e);
+                    float w[kSub];
+#pragma unroll
+                    for (int r = 0; r < kSub; ++r) w[r] = s_w[kSub * t + r][lane];
+                    uint32_t code[2] = {0u, 0u};
+#pragma unroll
+                    for (int r = 0; r < kSub; ++r) {
+                        // code of w / S and its value, by the hardware conversions (exact: see pack_weight.hip);
+                        // under M2 w / c first, rounded correctly: two residual corrections of w times the
+                        // correctly rounded reciprocal (the second one starts within one ulp, as Markstein's theorem asks)
+                        float x = w[r];
+                        if (mode != 1) {
+                            x *= lift;
+                            float y = x * rcs;
+                            y = fmaf(fmaf(-y, lcs, x), rcs, y);
+                            x = fmaf(fmaf(-y, lcs, x), rcs, y);
+                        }
+                        const uint32_t c4 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, x, 0.0f, scale, 0);
+                        const v2f q2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c4, scale, 0);
+                        const float q = mode == 1 ? q2[0] : q2[0] * cs;
+                        code[r >> 3] |= (c4 & 15u) << (4 * (r & 7));
+                        const float diff = w[r] - q, diag = s_u[buf][r][kSub * t + r], rd = s_rdiag[buf][r];
+                        const float y = diff * rd;
+                        const float ev = fmaf(fmaf(-y, diag, diff), rd, y);  // (w - q) / U[k][k]
+#pragma unroll
+                        for (int s = r + 1; s < kSub; ++s) w[s] = fmaf(-s_u[buf][r][kSub * t + s], ev, w[s]);
+                        s_err[buf][r][lane] = -ev;
+                        err[(k0 + r) * C + lane] = ev;
+                    }
+                    if (chan) {
+                        const int kk = (int)(k0 & 127);
+                        *reinterpret_cast<uint2*>(blob + L.off_codes + ((size_t)(strip * L.nkt + (k0 >> 7)) * 64 + (kk >> 5) * 16 + (lane & 15)) * 16 +
+                                                  ((kk >> 4) & 1) * 8) = live ? make_uint2(code[0], code[1]) : make_uint2(0u, 0u);
+                    }
+                }
+            } else if (t > 0 && (k0 % L.G) != 0) {
+                // ---- meanwhile: the previous sub-block's errors onto the rows beyond this one
+                const int tiles = (kPanel / kSub - 1 - t) * NT;
+                for (int i = wave - 1; i < tiles; i += 3) push_tile(t + 1 + i / NT, i % NT, buf ^ 1);
+            }
+            __syncthreads();
+            if (t + 1 == kPanel / kSub) break;
+            // ---- the errors onto the next sub-block's rows; onto all rows further down where a group begins with it
+            const bool starts_group = ((k0 + kSub) % L.G) == 0;
+            const int tiles = starts_group ? (kPanel / kSub - 1 - t) * NT : NT;
+            for (int i = wave; i < tiles; i += 4) push_tile(t + 1 + i / NT, i % NT, buf);
+            store_u(u, d, buf ^ 1);
+            if (t + 2 < kPanel / kSub) fetch_u(u, d, k0 + 2 * kSub, i0);
+            __syncthreads();
+            if (starts_group) {
+                partial_max(kSub * (t + 1), L.G, 0.0f);
+                __syncthreads();
+            }
         }
     }
 }
 
-// Wf[r][n] -= sum_j U[i0 + j][r] Err[j][n] for the rows r behind the block.  64 x 64 tile per workgroup,
-// 4 x 4 outputs per thread, B walked in steps of 16 through LDS.
-__global__ __launch_bounds__(256) void k_gptq_trail(float* __restrict__ Wf, const float* __restrict__ U, int64_t K, int64_t N,
-                                                  int B, int64_t i0, const float* __restrict__ Err)
+// output channels per workgroup: the least multiple of 16 that leaves every workgroup a compute unit, at most 64
+int gptq_tiles(int64_t Np)
 {
-    __shared__ float s_u[16][64 + 4], s_e[16][64 + 4];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int64_t r0 = i0 + B + (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
-    float acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = 0.f;
-    for (int j0 = 0; j0 < B; j0 += 16) {
-        for (int idx = tid; idx < 16 * 64; idx += 256) {
-            const int jj = idx >> 6, cc = idx & 63;
-            s_u[jj][cc] = U[(i0 + j0 + jj) * K + r0 + cc];  // r0 + 63 < K: the rows behind a block come in 128s
-            s_e[jj][cc] = n0 + cc < N ? Err[(int64_t)(j0 + jj) * N + n0 + cc] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            float u[4], ev[4];
-#pragma unroll
-            for (int a = 0; a < 4; ++a) u[a] = s_u[jj][ty * 4 + a];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) ev[b] = s_e[jj][tx * 4 + b];
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) acc[a][b] = fmaf(u[a], ev[b], acc[a][b]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int64_t r = r0 + ty * 4 + a, n = n0 + tx * 4 + b;
-            if (n < N) Wf[r * N + n] -= acc[a][b];
-        }
+    const int64_t cus = compute_units();
+    for (int nt = 1; nt < 4; ++nt)
+        if ((Np + 16 * nt - 1) / (16 * nt) <= cus) return nt;
+    return 4;
 }
 
 }  // namespace
 
-// float32 working copy [K][N], the current block's errors [B][N], column absmax [N]
+// the errors of every workgroup, [K][C] float32, and (groups of 256) a panel held back, [128][C]; C divides the
+// channel count rounded up to whole workgroups, which is less than N + 64
 size_t gptq_workspace_bytes(int64_t K, int64_t N, int G)
 {
     const int64_t B = G > 128 ? G : 128;
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
-    return up((size_t)K * N * 4) + up((size_t)B * N * 4) + up((size_t)N * 4);
+    return up((size_t)K * (N + 63) * 4) + up((size_t)B * (N + 63) * 4);
 }
 
 hipError_t launch_gptq_pack(const uint16_t* W, int64_t ldw, const BlobLayout& L, int mode, const float* U, uint8_t* blob,
                             void* workspace, hipStream_t s)
 {
-    const int64_t K = L.K, N = L.N;
-    const int B = L.G > 128 ? L.G : 128;
-    uint8_t* p = static_cast<uint8_t*>(workspace);
-    auto take = [&](size_t bytes) {
-        uint8_t* q = p;
-        p += (bytes + 255) / 256 * 256;
-        return q;
-    };
-    float* Wf = reinterpret_cast<float*>(take((size_t)K * N * 4));
-    float* Err = reinterpret_cast<float*>(take((size_t)B * N * 4));
-    float* colmax = reinterpret_cast<float*>(take((size_t)N * 4));
-    hipLaunchKernelGGL(k_gptq_init, dim3((unsigned)((L.Np + 255) / 256)), dim3(256), 0, s, W, ldw, L, mode, Wf, colmax, blob);
-    const size_t lds = (size_t)B * 64 * 4;
-    static OnceStatus attr;  // 256-row blocks need more than the default dynamic-LDS limit
-    if (hipError_t e = run_once(attr, [&] {
-            return hipFuncSetAttribute(reinterpret_cast<const void*>(k_gptq_block), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       256 * 64 * 4);
-        }); e != hipSuccess)
-        return e;
-    for (int64_t i0 = 0; i0 < K; i0 += B) {
-        hipLaunchKernelGGL(k_gptq_block, dim3((unsigned)((N + 63) / 64)), dim3(64), lds, s, Wf, U, L, mode, B, i0, colmax, Err, blob);
-        const int64_t behind = K - (i0 + B);
-        if (behind > 0)
-            hipLaunchKernelGGL(k_gptq_trail, dim3((unsigned)((N + 63) / 64), (unsigned)(behind / 64)), dim3(256), 0, s, Wf, U, K,
-                               N, B, i0, Err);
-    }
+    const int nt = gptq_tiles(L.Np);
+    const int64_t wgs = (L.Np + 16 * nt - 1) / (16 * nt);
+    float* err = static_cast<float*>(workspace);
+    float* held = err + ((size_t)L.K * (wgs * 16 * nt) * 4 + 255) / 256 * 64;
+#define ZQ_GPTQ(NT) hipLaunchKernelGGL(k_gptq<NT>, dim3((unsigned)wgs), dim3(256), 0, s, W, ldw, U, L, mode, err, held, blob)
+    if (nt == 1) ZQ_GPTQ(1);
+    else if (nt == 2) ZQ_GPTQ(2);
+    else if (nt == 3) ZQ_GPTQ(3);
+    else ZQ_GPTQ(4);
+#undef ZQ_GPTQ
     return hipGetLastError();
 }
 

@@ -1,0 +1,41 @@
+"""GPTQ at every width of a workgroup (16, 32, 48 and 64 output channels, chosen by the channel count): the plain
+packer's result under an identity Hessian, bit for bit, and with feedback the oracle's within the bars of
+test_gpu_gptq.py."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2307_09782_amd import zqfp
+from _util import bf16_tensor
+from test_gpu_gptq import _hessian, _unpacked, _w
+
+pytestmark = pytest.mark.gpu
+
+# the last workgroup partly filled in each; 256 compute units
+SHAPES = [(384, 15), (256, 4110), (512, 4083), (256, 8300), (256, 12391), (256, 16500)]
+
+
+@pytest.mark.parametrize("K,N", SHAPES)
+@pytest.mark.parametrize("G,mode", [(32, 2), (64, 1), (128, 2), (256, 2)])
+def test_identity_hessian(K, N, G, mode):
+    if K % G:
+        pytest.skip("K is not a multiple of G")
+    W = _w(K, N, K + N)
+    W[W == 0x8000] = 0  # a negative zero loses its sign when zero times an error is added to it
+    Wd = bf16_tensor(W)
+    got = zqfp.gptq_pack_weight_fp4(Wd, torch.eye(K, dtype=torch.float32, device="cuda"), G, mode)
+    for a, b in zip(_unpacked(got, K, N, G), _unpacked(zqfp.pack_weight_fp4(Wd, G, mode), K, N, G)):
+        assert np.array_equal(a, b)
+    zqfp.packed_weight_check(got, K, N, G)
+
+
+@pytest.mark.parametrize("K,N,G,mode", [(384, 15, 64, 1), (256, 4110, 32, 1), (256, 8300, 128, 2), (256, 12391, 256, 1), (256, 16500, 64, 2),
+                                        (512, 4083, 256, 2)])
+def test_feedback(K, N, G, mode):
+    W = _w(K, N, 3 * K + N)
+    _, _, U = _hessian(K, K)
+    codes, exps, c = _unpacked(zqfp.gptq_pack_weight_fp4(bf16_tensor(W), torch.from_numpy(U.astype(np.float32)).cuda(), G, mode), K, N, G)
+    codes_o, exps_o, c_o, _ = oracle.gptq_fp4(W, U, G, mode)
+    assert np.array_equal(c, c_o) and np.array_equal(codes[0], codes_o[0]) and np.array_equal(exps[0], exps_o[0])
+    assert np.mean(codes == codes_o) >= 0.995 and np.mean(exps == exps_o) >= 0.995
