@@ -272,7 +272,7 @@ int zqfp_packed_weight_check(const void *header, int64_t K, int64_t N, int G);
  *   U        [K, r] binary16      V  [r, N] binary16                     (out)
  *   sigma    [r] float32: the r leading singular values of E, descending (out)
  *   workspace  zqfp_lorc_workspace_bytes(K, N, r) bytes of device memory,
- *            256-byte aligned (E in float32 and the iteration's blocks)
+ *            256-byte aligned (the iteration's blocks and partial sums)
  * Returns ZQFP_E_SHAPE for a rank or iteration count outside the limits.
  */
 size_t zqfp_lorc_workspace_bytes(int64_t K, int64_t N, int r);

@@ -99,3 +99,28 @@ def test_argument_checks():
     with pytest.raises(zqfp.ZqfpError):
         zqfp.lorc_factorize(Wd, packed, cfg.G, 8, _omega(cfg.N, 16, 0), power_iters=9)
     assert zqfp.lib().zqfp_lorc_workspace_bytes(256, 256, 0) == 0
+
+
+@pytest.mark.parametrize("K,N,G,mode,r", [(128, 9, 32, 1, 1), (128, 67, 32, 2, 3), (384, 129, 128, 1, 8), (1152, 65, 96, 2, 24),
+                                         (640, 1031, 64, 1, 7), (256, 193, 256, 2, 41), (256, 300, 128, 1, 64)])
+def test_ragged_edges_of_the_passes(K, N, G, mode, r):
+    """Channel counts around the widths of a chunk (64) and of a column block (128 or 64), every padded block width
+    (r + 8 up to 16, 32, 48, 64, 80), an odd row stride with rows that start at odd elements, and groups whose exponent bytes
+    change inside a k-tile.  Planted rank-r matrix far above the quantization noise: singular values and product are unique.
+    The bars are those of the gap test above; the product is compared relative to the planted matrix."""
+    cfg = dataclasses.replace(inputs.CONFIGS["tiny"], K=K, N=N, G=G, mode=mode, seed=K + N)
+    W0 = inputs.make_w(cfg)
+    rng = np.random.default_rng(11)
+    m = min(r, N - 8)
+    P, _ = np.linalg.qr(rng.standard_normal((K, m)))
+    Q, _ = np.linalg.qr(rng.standard_normal((N, m)))
+    W = inputs.f32_to_bf16_bits((inputs.bf16_bits_to_f32(W0) + (P * np.geomspace(40.0, 4.0, m)) @ Q.T).astype(np.float32))
+    wide = torch.full((K, N + 2), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wide[:, 1:N + 1] = bf16_tensor(W)
+    packed = zqfp.pack_weight_fp4(bf16_tensor(W0), G, mode)
+    U, V, sigma = zqfp.lorc_factorize(wide[:, 1:N + 1], packed, G, r, _omega(N, r + 8, 3), 2)
+    codes, exps, c, _ = oracle.pack_weight(W0, G, mode)
+    Uo, Vo, so, _ = oracle.lorc_factors(W, codes, exps, c, G, r)
+    U, V, sigma = (t.double().cpu().numpy() for t in (U, V, sigma))
+    assert np.all(np.abs(sigma - so[:r]) <= 2e-3 * so[:r]), (sigma, so[:r])
+    assert np.linalg.norm(U @ V - Uo @ Vo) <= 2e-2 * np.linalg.norm(Uo @ Vo)
