@@ -1,0 +1,268 @@
+// W4A8 / W8A8 GEMM for a few dozen tokens (small serving batches, verification of drafts).
+//
+//   Y[m,n] = (sx[m] c[n]) * sum_k a[m,k] * q[k,n] * 2^e[g(k),n]   (+ T.V, LoRC)
+//
+// (paper Sections 1 and 3.)  Neither the matrix cores nor HBM bound these sizes but the latency of a workgroup's
+// first loads and the number of compute units that get work at all: 64 tokens x 12288 channels are 96 tiles of the
+// tiled kernel for 256 compute units.  Here a workgroup takes S strips of 16 channels, S chosen so that the strips
+// come out in whole rounds of compute units, and up to 64 tokens; its eight waves split K.  A wave therefore needs
+// every activation byte of its k-tiles exactly once, so operands go from memory straight into registers, NB k-tiles
+// ahead, with no barrier before the partial tiles meet in LDS at the end (fixed order, no atomics, no second launch).
+// What is left at 64 tokens is the 64 * K bytes of activations that every compute unit fetches (4096 x 12288: 5.3 of 14.7 us
+// against 16 tokens; 9.4 of 17.5 before a row's line was loaded by eight lanes).
+#include "zqfp_internal.h"
+
+namespace zqfp {
+namespace {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kWaves = 8;
+
+// MT: blocks of 16 tokens, S: strips of 16 channels, NB: k-tiles in flight per wave, WB: weight bits
+template <int MT, int S, int NB, bool EXACT, int WB>
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_mid(
+    const uint8_t* __restrict__ Xq, const float* __restrict__ sx, int64_t M, const uint8_t* __restrict__ blob, BlobLayout L,
+    Lorc lorc, void* __restrict__ Y, int64_t ldy, int out_dtype, int mblocks)
+{
+    extern __shared__ __attribute__((aligned(16))) float s_part[];  // [S * MT][kWaves][64][4]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, lb = lane >> 4;
+    const int nkt = (int)L.nkt;
+    // Consecutive workgroup ids sit on consecutive XCDs: each XCD gets a contiguous run of units, so that its L2 merges
+    // the parts of a line of Y and serves the strips of one group to all its token blocks.
+    const int units = (int)gridDim.x, xcd = (int)blockIdx.x & 7;
+    const int unit = xcd * (units >> 3) + min(xcd, units & 7) + ((int)blockIdx.x >> 3);
+    const int group = unit / mblocks;
+    const int64_t m_base = (int64_t)(unit - group * mblocks) * (16 * MT);
+    const int64_t strip0 = (int64_t)group * S;
+
+    const uint8_t* codes = blob + L.off_codes;
+    const uint32_t* exq = reinterpret_cast<const uint32_t*>(blob + L.off_exps);
+
+    // A operand: lane (row = lane % 16, lb) needs the bytes k = 16 lb + [0, 16) and 64 + 16 lb + [0, 16) of a k-tile.
+    // Loaded like that every lane of an instruction touches a line of its own (16 B a clock and compute unit), so
+    // eight lanes load a row's 128 bytes instead and the wave's own slice of LDS turns them round (chunk c of row r at
+    // slot c ^ (r % 8), which keeps both sides free of bank conflicts; a wave's LDS operations stay in order).  A row past M
+    // repeats row M - 1, a strip past the last one repeats it: neither is stored.
+    const uint8_t* xbase = Xq + m_base * L.K;
+    uint32_t arow[2 * MT];
+#pragma unroll
+    for (int j = 0; j < 2 * MT; ++j) arow[j] = (uint32_t)(min((int64_t)(j * 8 + (lane >> 3)), M - 1 - m_base) * L.K) + 16u * (uint32_t)(lane & 7);
+    uint8_t* turn = reinterpret_cast<uint8_t*>(s_part) + wave * (MT * 2048);
+    uint8_t* turn_w = turn + (lane >> 3) * 128 + ((lane & 7) ^ (lane >> 3)) * 16;
+    const uint8_t* turn_r0 = turn + col * 128 + (lb ^ (col & 7)) * 16;
+    const uint8_t* turn_r1 = turn + col * 128 + ((lb + 4) ^ (col & 7)) * 16;
+    int64_t strip[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) strip[s] = min(strip0 + s, L.nstrips - 1);
+
+    u32x4 a[NB][2 * MT], b[NB][S], bh[WB == 8 ? NB : 1][S];
+    uint32_t e[NB][S];
+    int esh[NB];
+    auto issue = [&](int buf, int kt_unclamped) {
+        const int kt = min(kt_unclamped, nkt - 1);  // past the end: loaded again, never used
+        const int blk = kt * 4 + lb;
+        const int sg = L.gsb_shift >= 0 ? blk >> L.gsb_shift : blk / L.gsb;
+        esh[buf] = 8 * (sg & 3);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const u32x4* f = reinterpret_cast<const u32x4*>(codes + ((strip[s] * nkt + kt) << (WB == 8 ? 11 : 10)));
+            b[buf][s] = f[lane];
+            if constexpr (WB == 8) bh[buf][s] = f[64 + lane];
+            e[buf][s] = (exq + strip[s] * L.ngq * 16)[(sg >> 2) * 16 + col];
+        }
+        const uint8_t* x = xbase + (int64_t)kt * 128;
+#pragma unroll
+        for (int j = 0; j < 2 * MT; ++j) a[buf][j] = *reinterpret_cast<const u32x4*>(x + arow[j]);
+    };
+
+    v4f acc[S][MT];
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int t = 0; t < MT; ++t) acc[s][t] = (v4f){0.f, 0.f, 0.f, 0.f};
+
+    auto multiply = [&](int buf) {
+        __builtin_amdgcn_wave_barrier();  // behind the reads of the k-tile before
+#pragma unroll
+        for (int j = 0; j < 2 * MT; ++j) *reinterpret_cast<u32x4*>(turn_w + j * 1024) = a[buf][j];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            const u32x4 a0 = *reinterpret_cast<const u32x4*>(turn_r0 + t * 2048), a1 = *reinterpret_cast<const u32x4*>(turn_r1 + t * 2048);
+            const v8i av = {(int)a0[0], (int)a0[1], (int)a0[2], (int)a0[3], (int)a1[0], (int)a1[1], (int)a1[2], (int)a1[3]};
+            v8i hi = av, lo = av;
+            if constexpr (EXACT) split_exponent_bands(av, hi, lo);
+            constexpr int BLGP = WB == 8 ? 0 : 4;  // B is E4M3 or E2M1; A is E4M3 with scale byte 127 = 2^0
+#pragma unroll
+            for (int band = 0; band < (EXACT ? 2 : 1); ++band)
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    v8i bv = {(int)b[buf][s][0], (int)b[buf][s][1], (int)b[buf][s][2], (int)b[buf][s][3], 0, 0, 0, 0};
+                    if constexpr (WB == 8) {
+                        bv[4] = (int)bh[buf][s][0]; bv[5] = (int)bh[buf][s][1]; bv[6] = (int)bh[buf][s][2]; bv[7] = (int)bh[buf][s][3];
+                    }
+                    acc[s][t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(band ? lo : hi, bv, acc[s][t], 0, BLGP, 0, 127, 0,
+                                                                                (int)(e[buf][s] >> esh[buf]));
+                }
+        }
+    };
+
+    // k-tiles wave, wave + 8, ...; the loop is unrolled by NB so that the buffers are addressed statically
+#pragma unroll
+    for (int i = 0; i < NB; ++i) issue(i, wave + kWaves * i);
+    for (int kt = wave; kt < nkt;) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            multiply(i);
+            issue(i, kt + kWaves * NB);
+            __builtin_amdgcn_sched_barrier(0);
+            kt += kWaves;
+            if (kt >= nkt) break;
+        }
+    }
+
+    __syncthreads();  // the waves' slices of LDS become the partial tiles
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int t = 0; t < MT; ++t) *reinterpret_cast<v4f*>(s_part + (((s * MT + t) * kWaves + wave) * 64 + lane) * 4) = acc[s][t];
+    __syncthreads();
+
+    // D[row][col] sits in lane 16 * (row / 4) + col, register row % 4: a thread adds up the four rows of one lane
+    const float* colscale = reinterpret_cast<const float*>(blob + L.off_colscale);
+    for (int o = tid; o < S * MT * 64; o += 64 * kWaves) {
+        const int tile = o >> 6, ln = o & 63;
+        const int s = tile / MT, t = tile - s * MT;
+        const int64_t n = (strip0 + s) * 16 + (ln & 15), m0 = m_base + t * 16 + 4 * (ln >> 4);
+        if (n >= L.N) continue;
+        v4f sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) sum += *reinterpret_cast<const v4f*>(s_part + ((tile * kWaves + w) * 64 + ln) * 4);
+        const float cs = colscale[n];
+        float y[4];
+        const float* tr[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t m = min(m0 + i, M - 1);
+            y[i] = (sx[m] * cs) * sum[i];
+            tr[i] = lorc.T + m * lorc.r;
+        }
+        for (int j = 0; j < lorc.r; ++j) {
+            const float v = half_bits_to_f32(lorc.V[(int64_t)j * L.N + n]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[i] = fmaf(tr[i][j], v, y[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (m0 + i >= M) break;
+            if (out_dtype == 0) reinterpret_cast<float*>(Y)[(m0 + i) * ldy + n] = y[i];
+            else reinterpret_cast<uint16_t*>(Y)[(m0 + i) * ldy + n] = f32_to_bf16_bits(y[i]);
+        }
+    }
+}
+
+template <int MT, int S, bool EXACT, int WB>
+hipError_t launch_cfg(int mblocks, const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob, const BlobLayout& L,
+                      Lorc lorc, void* Y, int64_t ldy, int out_dtype, hipStream_t s)
+{
+    constexpr int NB = MT == 1 ? 4 : MT == 2 ? 3 : 2;
+    constexpr size_t smem = (size_t)(S > 2 ? S : 2) * MT * kWaves * 1024;  // partial tiles, the waves' slices before them
+    auto kern = k_gemm_mid<MT, S, NB, EXACT, WB>;
+    if constexpr (smem > 65536) {  // above the default limit of dynamic LDS, which is a per-function setting
+        static OnceStatus attr;
+        if (hipError_t e = run_once(attr, [&] {
+                return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+            }); e != hipSuccess)
+            return e;
+    }
+    const unsigned grid = (unsigned)((L.nstrips + S - 1) / S * mblocks);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), smem, s, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, mblocks);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+namespace {
+
+// Microseconds of a launch with S strips per workgroup: whole rounds of compute units, each a fixed part, the partial
+// tiles and the k-tiles (fitted to 600 timings: ten weight shapes with 8 ... 224 k-tiles, 4 ... 256 tokens; within 11 % on
+// average, and its choice of S was the fastest one at every point).
+float mid_us(int64_t M, const BlobLayout& L, int S)
+{
+    const int64_t mblocks = (M + 63) / 64;
+    const float mt = (float)(((M + 15) / 16 + mblocks - 1) / mblocks), s = (float)S, nkt = (float)L.nkt;
+    const float rounds = (float)(((L.nstrips + S - 1) / S * mblocks + 255) / 256);
+    if (L.wbits == 8) return rounds * (3.3f + 0.159f * s * mt + nkt * (0.034f + 0.0223f * mt + 0.0482f * s));
+    return rounds * (3.1f + 0.163f * s * mt + nkt * (0.003f + 0.0335f * mt + 0.0242f * s));
+}
+
+int best_strips(int64_t M, const BlobLayout& L)
+{
+    int best = 1;
+    for (int S = 2; S <= 4; ++S)
+        if (mid_us(M, L, S) < mid_us(M, L, best)) best = S;
+    return best;
+}
+
+}  // namespace
+
+// Where this form is the faster one (graph-timed, weights beyond the last-level cache, exact mode, before -> after in us).
+bool gemm_mid_wins(int64_t M, const BlobLayout& L)
+{
+    if (M <= 16) {
+        // E4M3 weights: K beyond the registers of the persistent kernel, which left it to the streaming one (11008 x 4096,
+        // 16 tokens: 15.2 -> 13.7; 16384 x 12288, 1 token: 45.1 -> 40.5).  At most 8 tokens and two strips per compute
+        // unit: two of the streaming kernel's workgroups share a unit and are ahead (9216 x 8192: 17.2 against 18.3).
+        if (L.wbits == 8) return L.nkt > 40 && (M > 8 || L.nstrips <= 256 || (L.nstrips > 512 && L.nstrips <= 768));
+        // K in one piece instead of chunks and a second launch (11008 x 4096, 4 tokens: 11.6 -> 9.5; 28672 x 8192: 28.8 -> 26.4;
+        // 16384 x 12288, 16 tokens: 28.8 -> 25.1).  Beyond one round of compute units the persistent kernel's stream wins,
+        // as it does where 16 tokens' activations would outweigh a single strip's weights for long (28672 x 4096: 19.5 against 21.2).
+        if (L.nkt > 64)
+            return L.nstrips <= 768 && !(M > 8 && L.nkt > 128 && L.nstrips <= 256 && L.nstrips * plan_decode(L.nkt).chunks >= 1024);
+        // A strip per compute unit: the persistent kernel's prologue serves no second one (8192 x 1024, 16 tokens:
+        // 8.2 -> 6.2; 5120 x 4096: 7.1 -> 6.6).  With few tokens it is as short (8192 x 2048, 1 token: 6.2 against 6.7).
+        return M > 4 && L.nkt > 32 && L.nstrips <= 256;
+    }
+    // More tokens: against the tiled kernel's estimate (4096 x 12288, 24 / 64 tokens: 18.5 -> 10.6 / 19.9 -> 14.7; 4096 x 4096, 128
+    // tokens: 18.7 -> 11.3; 8192 x 28672 and 28672 x 8192 at 64 tokens stay there, 35.7 against 47.0 and 39.1 against 52.6).
+    const TilePlan p = effective_tile_plan(M, L.Np, L.nkt);
+    if (p.forced) return false;
+    if (L.N < 64) return true;  // the tiled kernel has no such tile
+    const float us = mid_us(M, L, best_strips(M, L));
+    if (L.wbits == 8) {
+        if (M <= 32 && L.nkt < 16) return false;  // the streaming kernel (1024 x 1024, 24 tokens: 3.8 against 4.3)
+        // 64 x 128 tiles, one per compute unit, no K-split: fitted (4096 x 12288, 64 tokens: 24.4 -> 18.8; 28672 x 8192:
+        // 111 -> 64.7; 14336 x 2048, 300 tokens: 57.0 -> 32.5)
+        const int64_t tiles = (M + 63) / 64 * ((L.Np + 127) / 128);
+        return tiles <= 256 && us < 7.0f + 0.465f * (float)L.nkt * (tiles > 180 ? (float)tiles / 180.0f : 1.0f);
+    }
+    return us < p.us;
+}
+
+hipError_t launch_gemm_mid(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob, const BlobLayout& L,
+                           Lorc lorc, void* Y, int64_t ldy, int out_dtype, int accum, hipStream_t s)
+{
+    if (M == 0 || L.N == 0) return hipSuccess;
+    const int mblocks = (int)((M + 63) / 64), mt = (int)(((M + 15) / 16 + mblocks - 1) / mblocks), S = best_strips(M, L);
+#define ZQ_MID(MT_, S_) \
+    if (mt == MT_ && S == S_) { \
+        if (L.wbits == 8) return accum == 0 ? launch_cfg<MT_, S_, true, 8>(mblocks, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, s) \
+                                            : launch_cfg<MT_, S_, false, 8>(mblocks, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, s); \
+        return accum == 0 ? launch_cfg<MT_, S_, true, 4>(mblocks, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, s) \
+                          : launch_cfg<MT_, S_, false, 4>(mblocks, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, s); \
+    }
+#define ZQ_MID_ALL(MT_) ZQ_MID(MT_, 1) ZQ_MID(MT_, 2) ZQ_MID(MT_, 3) ZQ_MID(MT_, 4)
+    ZQ_MID_ALL(1) ZQ_MID_ALL(2) ZQ_MID_ALL(3) ZQ_MID_ALL(4)
+#undef ZQ_MID_ALL
+#undef ZQ_MID
+    return hipErrorInvalidValue;
+}
+
+}  // namespace zqfp

@@ -1,18 +1,16 @@
-// W4A8 GEMM, weight-streaming form for small token counts (decode): bound by
-// reading the packed FP4 weights once from HBM.
+// W8A8 GEMM, weight-streaming form for small token counts where no other kernel is the better one: at most 8 tokens with
+// two strips per compute unit and long K, or 17 to 32 tokens with K below 2048.  Bound by reading the packed E4M3
+// weights once from HBM.
 //
 //   Y[m,n] = (sx[m] c[n]) * sum_k a[m,k] * q[k,n] * 2^e[g(k),n]   (+ T.V, LoRC)
 //
-// (paper Sections 1 and 3: FP8 activations x FP4 weights with power-of-two
-// group scales.)  The power of two is never multiplied in: the E8M0 exponent
-// byte goes to the block-scaled matrix instruction
-// v_mfma_scale_f32_16x16x128_f8f6f4 (A = E4M3, B = E2M1), which applies it per
-// 32-element block of K inside the matrix core.
+// (paper Section 4: FP8 activations x FP8 weights with power-of-two group scales.)  The power of two is never
+// multiplied in: the E8M0 exponent byte goes to the block-scaled matrix instruction
+// v_mfma_scale_f32_16x16x128_f8f6f4, which applies it per 32-element block of K inside the matrix core.
 //
-// Work split: one workgroup (8 waves) per strip of 16 output channels and per
-// block of up to 64 tokens; the 8 waves split K (k-tile i goes to wave i % 8)
-// and meet in LDS, so the sum needs neither atomics nor a second pass and its
-// order is fixed.  Each weight fragment is a contiguous 1 KB read (16 B/lane).
+// Work split: one workgroup (8 waves) per strip of 16 output channels; the 8 waves split K (k-tile i goes to
+// wave i % 8) and meet in LDS, so the sum needs neither atomics nor a second pass and its order is fixed.
+// Each half of a weight fragment is a contiguous 1 KB read (16 B/lane).
 #include "zqfp_internal.h"
 
 namespace zqfp {
@@ -26,9 +24,9 @@ constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
 constexpr int kUnroll = 4;  // k-tiles whose loads are issued before their matrix instructions
 
-// W8: the weights are E4M3 codes (W8A8, paper Section 4): a fragment is two 1 KB halves, the B operand has eight
-// registers and the instruction's format field says FP8 on both sides.
-template <int MT, bool EXACT, bool W8 = false>
+// A fragment is two 1 KB halves, the B operand has eight registers and the instruction's format field says FP8 on
+// both sides.
+template <int MT, bool EXACT>
 __global__ __launch_bounds__(kThreads) void k_gemm_stream(const uint8_t* __restrict__ Xq, const float* __restrict__ sx,
                                                         int64_t M, const uint8_t* __restrict__ blob, BlobLayout L,
                                                         Lorc lorc, void* __restrict__ Y, int64_t ldy, int out_dtype)
@@ -40,7 +38,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_stream(const uint8_t* __restr
     const int64_t m_base = (int64_t)blockIdx.y * (16 * MT);
     const int nkt = (int)L.nkt;
 
-    constexpr int kFragVec = W8 ? 128 : 64;  // 16-byte vectors per fragment
+    constexpr int kFragVec = 128;  // 16-byte vectors per fragment
     const u32x4* bfrag = reinterpret_cast<const u32x4*>(blob + L.off_codes) + strip * nkt * kFragVec + lane;
     const uint32_t* ex = reinterpret_cast<const uint32_t*>(blob + L.off_exps) + strip * L.ngq * 16 + col;
 
@@ -60,7 +58,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_stream(const uint8_t* __restr
     for (int t = 0; t < MT; ++t) acc[t] = (v4f){0.f, 0.f, 0.f, 0.f};
 
     for (int kt0 = wave; kt0 < nkt; kt0 += kWaves * kUnroll) {
-        u32x4 b[kUnroll], b2[W8 ? kUnroll : 1];
+        u32x4 b[kUnroll], b2[kUnroll];
         uint32_t e[kUnroll];
         u32x4 a_lo[kUnroll][MT], a_hi[kUnroll][MT];
 #pragma unroll
@@ -68,7 +66,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_stream(const uint8_t* __restr
             const int kt = kt0 + u * kWaves;
             if (kt < nkt) {
                 b[u] = bfrag[(int64_t)kt * kFragVec];
-                if constexpr (W8) b2[u] = bfrag[(int64_t)kt * kFragVec + 64];
+                b2[u] = bfrag[(int64_t)kt * kFragVec + 64];
                 const int blk = kt * 4 + lb;  // 32-element block index along K
                 const int sg = (L.gsb_shift >= 0) ? (blk >> L.gsb_shift) : (blk / L.gsb);
                 e[u] = ex[(sg >> 2) * 16] >> (8 * (sg & 3));
@@ -88,14 +86,14 @@ __global__ __launch_bounds__(kThreads) void k_gemm_stream(const uint8_t* __restr
         for (int u = 0; u < kUnroll; ++u) {
             const int kt = kt0 + u * kWaves;
             if (kt < nkt) {
-                v8i bv = {(int)b[u][0], (int)b[u][1], (int)b[u][2], (int)b[u][3], 0, 0, 0, 0};
-                if constexpr (W8) { bv[4] = (int)b2[u][0]; bv[5] = (int)b2[u][1]; bv[6] = (int)b2[u][2]; bv[7] = (int)b2[u][3]; }
-                constexpr int kBlgp = W8 ? 0 : 4;  // format of B: 0 = E4M3, 4 = E2M1
+                v8i bv = {(int)b[u][0], (int)b[u][1], (int)b[u][2], (int)b[u][3],
+                          (int)b2[u][0], (int)b2[u][1], (int)b2[u][2], (int)b2[u][3]};
+                constexpr int kBlgp = 0;  // format of B: E4M3
 #pragma unroll
                 for (int t = 0; t < MT; ++t) {
                     v8i av = {(int)a_lo[u][t][0], (int)a_lo[u][t][1], (int)a_lo[u][t][2], (int)a_lo[u][t][3],
                               (int)a_hi[u][t][0], (int)a_hi[u][t][1], (int)a_hi[u][t][2], (int)a_hi[u][t][3]};
-                    // cbsz 0: A is E4M3; blgp 4: B is E2M1; A scale byte 127 = 2^0; B scale = group exponent
+                    // cbsz 0: A is E4M3; A scale byte 127 = 2^0; B scale = group exponent
                     if constexpr (EXACT) {
                         v8i hi, lo;
                         split_exponent_bands(av, hi, lo);
@@ -137,9 +135,8 @@ template <int MT>
 void launch_mt(dim3 grid, bool exact, const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob,
                const BlobLayout& L, Lorc lorc, void* Y, int64_t ldy, int out_dtype, hipStream_t s)
 {
-#define ZQ_STREAM(EX, W8) hipLaunchKernelGGL((k_gemm_stream<MT, EX, W8>), grid, dim3(kThreads), 0, s, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype)
-    if (L.wbits == 8) { if (exact) ZQ_STREAM(true, true); else ZQ_STREAM(false, true); }
-    else { if (exact) ZQ_STREAM(true, false); else ZQ_STREAM(false, false); }
+#define ZQ_STREAM(EX) hipLaunchKernelGGL((k_gemm_stream<MT, EX>), grid, dim3(kThreads), 0, s, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype)
+    if (exact) ZQ_STREAM(true); else ZQ_STREAM(false);
 #undef ZQ_STREAM
 }
 
@@ -152,8 +149,7 @@ hipError_t launch_gemm_stream(const uint8_t* Xq, const float* sx, int64_t M, con
     const bool exact = accum == 0;
     const unsigned ns = (unsigned)L.nstrips;
     if (M <= 16) launch_mt<1>(dim3(ns, 1), exact, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, s);
-    else if (M <= 32) launch_mt<2>(dim3(ns, 1), exact, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, s);
-    else launch_mt<4>(dim3(ns, (unsigned)((M + 63) / 64)), exact, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, s);
+    else launch_mt<2>(dim3(ns, (unsigned)((M + 31) / 32)), exact, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, s);
     return hipGetLastError();
 }
 

@@ -777,6 +777,7 @@ TilePlan plan_tiles(int64_t M, int64_t Np, int64_t nkt)
             if (split_us < unsplit_us) {
                 p.kslice = kslice;
                 p.ksplit = ksplit;
+                p.us = 3.0f + split_us;
                 return p;
             }
         }
@@ -795,6 +796,7 @@ TilePlan plan_tiles(int64_t M, int64_t Np, int64_t nkt)
         const float cost = 3.0f + per_cu * (k.e + k.s * (float)nkt) * (lone_waves ? 1.3f : 1.0f);
         if (!have || cost < best) { best = cost; have = true; p.bm = k.bm; p.bn = k.bn; p.kg = k.kg; }
     }
+    p.us = best;
     return p;
 }
 

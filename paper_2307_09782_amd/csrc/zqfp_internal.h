@@ -250,6 +250,7 @@ struct TilePlan {
     int kg;           // wave groups per workgroup (1 or 2)
     int ksplit;       // number of K slices (1: none)
     int kslice;       // k-tiles per slice
+    float us = 0.f;   // estimated time (0: many rounds of large tiles, not estimated)
     bool forced = false;  // set through the tuning hook (zqfp_probe_force_tile_plan), not planned
 };
 TilePlan plan_tiles(int64_t M, int64_t Np, int64_t nkt);
@@ -309,6 +310,11 @@ hipError_t launch_gemm_tile(const uint8_t* Xq, const float* sx, int64_t M, const
                             const BlobLayout& L, Lorc lorc, void* Y, int64_t ldy, int out_dtype,
                             int accum, void* workspace, hipStream_t s);
 bool gemm_tile_supported(int64_t M, const BlobLayout& L);
+// few tokens, any shape, both weight formats; gemm_mid_wins: faster than the other forms for this problem
+bool gemm_mid_wins(int64_t M, const BlobLayout& L);
+hipError_t launch_gemm_mid(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob,
+                           const BlobLayout& L, Lorc lorc, void* Y, int64_t ldy, int out_dtype,
+                           int accum, hipStream_t s);
 // The plan the tiled form runs for a problem: plan_tiles, unless the tuning hook has fixed one (tile shape and
 // number of K slices for every following call; 0, 0, 0 returns to automatic planning; false = not a shape the kernel has).
 TilePlan effective_tile_plan(int64_t M, int64_t Np, int64_t nkt);
