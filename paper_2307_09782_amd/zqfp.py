@@ -7,6 +7,7 @@ step of the path is computed here and there is no fallback: if the library
 is missing or a call fails, an exception is raised.
 """
 import ctypes
+import functools
 import os
 
 import torch
@@ -112,11 +113,13 @@ def _check(rc):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # a plain integer: the declared argument types turn it into a pointer
+    return None if t is None else t.data_ptr()
 
 
 def _stream(t):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    # the current stream's handle without a Stream object around it (2 us a call)
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
 def _dev(t, dtype, ndim):
@@ -243,8 +246,18 @@ def swiglu_quantize_act_fp8(G, Up, U=None, H=None):
     return (Xq, sx) if U is None else (Xq, sx, T)
 
 
-def packed_weight_bytes(K, N, G):
+@functools.lru_cache(maxsize=1024)
+def _blob_bytes(K, N, G):
     return int(lib().zqfp_packed_weight_bytes(K, N, G))
+
+
+@functools.lru_cache(maxsize=1024)
+def _blob_bytes_fp8(K, N, G):
+    return int(lib().zqfp_packed_weight_fp8_bytes(K, N, G))
+
+
+def packed_weight_bytes(K, N, G):
+    return _blob_bytes(K, N, G)
 
 
 def pack_weight_fp4(W, G, mode):
@@ -281,16 +294,20 @@ def _workspace(M, K, N, device):
     return torch.empty((n,), dtype=torch.uint8, device=device) if n else None
 
 
-def check_gemm_args(M, K, N, G, packed_numel, workspace_numel, out_shape, out_dtype, out_stride, out_is_cuda=True):
-    """Host-side refusals of the GEMM wrappers, on plain numbers (the library cannot look into device memory
-    without a synchronization, so sizes that it takes on trust are compared here): raises ZqfpError(-2 / -6 / -4)
-    for a blob whose size is not that of (K, N, G), a workspace smaller than the query's answer, an output that
-    is not a [M, N] float32 / bfloat16 tensor with contiguous rows."""
+def _check_blob_args(K, N, G, packed_numel):
     need = packed_weight_bytes(K, N, G)
     if need == 0:
         raise ZqfpError(-2, f"(K={K}, N={N}, G={G}) outside the shape limits")
     if packed_numel != need:
         raise ZqfpError(-2, f"packed blob has {packed_numel} bytes, a blob of (K={K}, N={N}, G={G}) has {need}")
+
+
+def check_gemm_args(M, K, N, G, packed_numel, workspace_numel, out_shape, out_dtype, out_stride, out_is_cuda=True):
+    """Host-side refusals of the GEMM wrappers, on plain numbers (the library cannot look into device memory
+    without a synchronization, so sizes that it takes on trust are compared here): raises ZqfpError(-2 / -6 / -4)
+    for a blob whose size is not that of (K, N, G), a workspace smaller than the query's answer, an output that
+    is not a [M, N] float32 / bfloat16 tensor with contiguous rows."""
+    _check_blob_args(K, N, G, packed_numel)
     if workspace_numel is not None and workspace_numel < gemm_workspace_bytes(M, K, N):
         raise ZqfpError(-6, f"workspace has {workspace_numel} bytes, zqfp_gemm_workspace_bytes says "
                             f"{gemm_workspace_bytes(M, K, N)}")
@@ -298,6 +315,18 @@ def check_gemm_args(M, K, N, G, packed_numel, workspace_numel, out_shape, out_dt
         raise ZqfpError(-4, f"output dtype {out_dtype}: float32 or bfloat16")
     if not out_is_cuda or tuple(out_shape) != (M, N) or (N > 1 and out_stride[1] != 1) or (M > 1 and out_stride[0] < N):
         raise ZqfpError(-2, f"output must be a CUDA [M={M}, N={N}] tensor with contiguous rows")
+
+
+def _output(M, K, N, G, packed, workspace_numel, out_dtype, out, device):
+    """The output tensor, its row stride and its type code after every refusal of check_gemm_args; an output made
+    here has the right shape and strides."""
+    if out is not None or workspace_numel is not None or (out_dtype is not torch.float32 and out_dtype is not torch.bfloat16):
+        Y = torch.empty((M, N), dtype=out_dtype, device=device) if out is None else out
+        check_gemm_args(M, K, N, G, packed.numel(), workspace_numel, Y.shape, Y.dtype, Y.stride(), Y.is_cuda)
+        return Y, Y.stride(0), OUT_F32 if Y.dtype == torch.float32 else OUT_BF16
+    Y = torch.empty((M, N), dtype=out_dtype, device=device)
+    _check_blob_args(K, N, G, packed.numel())
+    return Y, Y.stride(0), OUT_F32 if out_dtype is torch.float32 else OUT_BF16
 
 
 def packed_weight_check(packed, K, N, G):
@@ -321,20 +350,18 @@ def _gemm_call(Xq, sx, packed, N, G, T, V, out_dtype, accum, out, workspace):
         r = T.shape[1]
         if T.shape[0] != M or tuple(V.shape) != (r, N):
             raise ZqfpError(-2, "LoRC factor shapes")
-    Y = torch.empty((M, N), dtype=out_dtype, device=Xq.device) if out is None else out
     no_ws = workspace is False  # run without the K-split (the library accepts NULL)
     if workspace is not None and not no_ws:
         _dev(workspace, torch.uint8, 1)
-    check_gemm_args(M, K, N, G, packed.numel(), None if (workspace is None or no_ws) else workspace.numel(), Y.shape,
-                    Y.dtype, Y.stride(), Y.is_cuda)
-    code = OUT_F32 if Y.dtype == torch.float32 else OUT_BF16
+    Y, ldy, code = _output(M, K, N, G, packed, None if (workspace is None or no_ws) else workspace.numel(), out_dtype, out,
+                           Xq.device)
     ws = None if no_ws else workspace if workspace is not None else _workspace(M, K, N, Xq.device)
     nws = 0 if ws is None else ws.numel()
     if r:
         _check(lib().zqfp_w4a8_gemm_lorc(_ptr(Xq), _ptr(sx), M, K, _ptr(packed), N, G, _ptr(T), _ptr(V), r, _ptr(Y),
-                                         Y.stride(0), code, accum, _ptr(ws), nws, _stream(Xq)))
+                                         ldy, code, accum, _ptr(ws), nws, _stream(Xq)))
     else:
-        _check(lib().zqfp_w4a8_gemm(_ptr(Xq), _ptr(sx), M, K, _ptr(packed), N, G, _ptr(Y), Y.stride(0), code, accum,
+        _check(lib().zqfp_w4a8_gemm(_ptr(Xq), _ptr(sx), M, K, _ptr(packed), N, G, _ptr(Y), ldy, code, accum,
                                     _ptr(ws), nws, _stream(Xq)))
     return Y
 
@@ -389,8 +416,7 @@ def w4a8_linear(X, packed, N, G, U=None, V=None, out_dtype=torch.float32, accum=
         r = U.shape[1]
         if U.shape[0] != K or tuple(V.shape) != (r, N):
             raise ZqfpError(-2, "LoRC factor shapes")
-    Y = torch.empty((M, N), dtype=out_dtype, device=X.device) if out is None else out
-    check_gemm_args(M, K, N, G, packed.numel(), None, Y.shape, Y.dtype, Y.stride(), Y.is_cuda)
+    Y, ldy, code = _output(M, K, N, G, packed, None, out_dtype, out, X.device)
     fused = linear_is_fused(M, K, r)
     Xq = sx = T = None
     if want_codes or not fused:
@@ -399,9 +425,8 @@ def w4a8_linear(X, packed, N, G, U=None, V=None, out_dtype=torch.float32, accum=
     if r:
         T = torch.empty((M, r), dtype=torch.float32, device=X.device)
     ws = None if fused else _workspace(M, K, N, X.device)
-    code = OUT_F32 if Y.dtype == torch.float32 else OUT_BF16
     _check(lib().zqfp_w4a8_linear(_ptr(X), X.stride(0), M, K, _ptr(packed), N, G, _ptr(U), _ptr(V), r, _ptr(Xq), _ptr(sx),
-                                  _ptr(T), _ptr(Y), Y.stride(0), code, accum, _ptr(ws), 0 if ws is None else ws.numel(),
+                                  _ptr(T), _ptr(Y), ldy, code, accum, _ptr(ws), 0 if ws is None else ws.numel(),
                                   _stream(X)))
     return (Y, Xq, sx) if want_codes else Y
 
@@ -410,7 +435,7 @@ def pack_weight_fp8(W, G, mode):
     """W [K,N] bf16 -> packed blob of E4M3 weights with power-of-two group scales (W8A8; G a multiple of 128)."""
     _rows(W, torch.bfloat16)
     K, N = W.shape
-    nbytes = int(lib().zqfp_packed_weight_fp8_bytes(K, N, G))
+    nbytes = _blob_bytes_fp8(K, N, G)
     if nbytes == 0:
         raise ZqfpError(-2, f"(K={K}, N={N}, G={G})")
     packed = torch.empty((nbytes,), dtype=torch.uint8, device=W.device)
@@ -421,7 +446,7 @@ def pack_weight_fp8(W, G, mode):
 def unpack_codes_fp8(packed, K, N, G):
     """packed E4M3 blob -> codes [K,N] uint8 (E4M3), exps [K/G,N] uint8, colscale [N] f32."""
     _dev(packed, torch.uint8, 1)
-    if packed.numel() != int(lib().zqfp_packed_weight_fp8_bytes(K, N, G)) or packed.numel() == 0:
+    if packed.numel() != _blob_bytes_fp8(K, N, G) or packed.numel() == 0:
         raise ZqfpError(-2, "blob size is not that of an E4M3 blob of (K, N, G)")
     codes = torch.empty((K, N), dtype=torch.uint8, device=packed.device)
     exps = torch.empty((K // G, N), dtype=torch.uint8, device=packed.device)
@@ -434,7 +459,7 @@ def w8a8_gemm(Xq, sx, packed, N, G, T=None, V=None, out_dtype=torch.float32, acc
     """Y [M,N] = (sx c) * (Xq . Wq8) (+ T . V): E4M3 weights."""
     _dev(Xq, torch.uint8, 2), _dev(sx, torch.float32, 1), _dev(packed, torch.uint8, 1)
     M, K = Xq.shape
-    if packed.numel() != int(lib().zqfp_packed_weight_fp8_bytes(K, N, G)) or packed.numel() == 0 or sx.shape[0] != M:
+    if packed.numel() != _blob_bytes_fp8(K, N, G) or packed.numel() == 0 or sx.shape[0] != M:
         raise ZqfpError(-2, "blob size is not that of an E4M3 blob of (K, N, G)")
     r = 0
     if T is not None:
