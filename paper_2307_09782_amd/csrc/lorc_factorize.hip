@@ -563,13 +563,15 @@ __global__ __launch_bounds__(256) void k_lorc_eig(const double* __restrict__ gra
                 }
             };
             if constexpr (SMALL) {
-                if (tx < half && ty < half) {
-                    const int pa = s_pair[tau][ty], pb = s_pair[tau][tx];
-                    const int p = pa & 255, q = pa >> 8 & 255, u = pb & 255, v = pb >> 8 & 255;
+                if (tx < half) {  // all eight ty: the vectors have mm rows, of which ty < half alone would leave some out
+                    const int pb = s_pair[tau][tx], u = pb & 255, v = pb >> 8 & 255;
                     double cb, sb;
                     jacobi_rotation(pb >> (sweep == 0 ? 17 : 16) & 1, M[u * ld + v], M[v * ld + v] - M[u * ld + u], cb, sb);
-                    const double ca = __shfl(cb, ty), sa = __shfl(sb, ty);  // lane ty has tx = ty
-                    rotate_block(p, q, u, v, ca, sa, cb, sb, tx == ty && sb != 0.0);
+                    const double ca = __shfl(cb, ty), sa = __shfl(sb, ty);  // lane ty has tx = ty; unused where ty >= half
+                    if (ty < half) {
+                        const int pa = s_pair[tau][ty];
+                        rotate_block(pa & 255, pa >> 8 & 255, u, v, ca, sa, cb, sb, tx == ty && sb != 0.0);
+                    }
                     rotate_vectors(u, v, cb, sb);
                 }
             } else {

@@ -124,3 +124,21 @@ def test_ragged_edges_of_the_passes(K, N, G, mode, r):
     U, V, sigma = (t.double().cpu().numpy() for t in (U, V, sigma))
     assert np.all(np.abs(sigma - so[:r]) <= 2e-3 * so[:r]), (sigma, so[:r])
     assert np.linalg.norm(U @ V - Uo @ Vo) <= 2e-2 * np.linalg.norm(Uo @ Vo)
+
+
+@pytest.mark.parametrize("r", [1, 2, 3, 4, 5, 6, 7, 8, 9, 13, 24, 33, 57])
+def test_factors_hold_the_energy_of_their_singular_values_on_a_flat_spectrum(r):
+    """On quantization noise no vector is distinguished, so every coefficient of the small eigenproblem's vectors counts:
+    the columns of U and the rows of V are orthogonal with squared norms sigma, and U V takes sum(sigma^2) out of
+    |E|^2.  Both hold up to the binary16 rounding of the factors (2^-11 of each element): with u = U_i and its
+    rounding d, |u.d| <= 2^-11 |u|^2, twice that in a Gram entry; in the energy 2 <E - U V, d V> <= 2^-10 sigma_1 sum(sigma)."""
+    K, N, G = 384, 328, 128
+    cfg = dataclasses.replace(inputs.CONFIGS["llama7b_qkv"], K=K, N=N, G=G, seed=r)
+    W = inputs.make_w(cfg)
+    U, V, sigma, _, _, so, E = _run(W, W, G, 1 + r % 2, r, 2)
+    bar = 1.1 * 2.0 ** -10
+    root = np.sqrt(np.outer(sigma, sigma))
+    assert np.all(np.abs(U.T @ U - np.diag(sigma)) <= bar * root), np.abs((U.T @ U - np.diag(sigma)) / root).max()
+    assert np.all(np.abs(V @ V.T - np.diag(sigma)) <= bar * root), np.abs((V @ V.T - np.diag(sigma)) / root).max()
+    captured = np.linalg.norm(E) ** 2 - np.linalg.norm(E - U @ V) ** 2
+    assert abs(captured - np.sum(sigma ** 2)) <= bar * so[0] * np.sum(sigma), (captured, np.sum(sigma ** 2))
