@@ -386,6 +386,11 @@ __global__ __launch_bounds__(512) void k_lorc_gram(const float* part, int slices
 // A <- A C^-T with C C^T = the summed Gram matrix (Cholesky).  Every workgroup eliminates the matrix and, beside it, the
 // identity, which leaves C^-1; thread t holds elements t, t + 256, ... of both in registers and a step costs one barrier.
 // Then a wave takes blocks of 16 rows through the float64 matrix cores.
+// A column that depends on the ones before it (E of lower rank than l, or singular values that fall by 2^-22 and more within l
+// columns) has a pivot of nothing but rounding: what float32 left of the column, (2^-24)^2 of its squared norm, and
+// l 2^-53 from the sums.  Dividing by such a pivot, however it is bounded from below, blows up the later rows step by step
+// until they overflow, so a column with a pivot below 2^-44 of its squared norm is dropped: zeros, here and in all that follows
+// from it.  What it could add lies below 2^-22 of what is kept, the factors' binary16 is 2^-11.
 template <int NJ>
 __global__ __launch_bounds__(256) void k_lorc_orth(float* __restrict__ A, int64_t blocks, int l, const double* __restrict__ gram, int nparts)
 {
@@ -407,9 +412,6 @@ __global__ __launch_bounds__(256) void k_lorc_orth(float* __restrict__ A, int64_
     }
     for (int idx = tid; idx < LP * LDT; idx += 256) s_t[idx] = 0.0;
     __syncthreads();
-    double mx = 0.0;
-    for (int j = 0; j < l; ++j) mx = fmax(mx, s_diag[j]);
-    const double floor = fmax(mx * 1e-28, 1e-300);  // a vanishing pivot (rank-deficient input) stays finite
     for (int j = 0; j < l; ++j) {
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
@@ -418,12 +420,14 @@ __global__ __launch_bounds__(256) void k_lorc_orth(float* __restrict__ A, int64_
             if (i == j) s_t[j * LDT + k] = w[e];
         }
         __syncthreads();
-        const double d = fmax(s_col[j & 1][j], floor), inv = recip(d);
-        if (tid == 0) s_d[j] = d;
+        const double d = s_col[j & 1][j];
+        const bool drop = d <= 0x1p-44 * s_diag[j];  // false for NaN, which goes on to the results
+        const double inv = drop ? 0.0 : recip(d);
+        if (tid == 0) s_d[j] = drop ? 0.0 : recip_sqrt(d);
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
             const int idx = tid + 256 * e, i = idx / LP, k = idx % LP;
-            if (i > j && i < l) {
+            if (i > j && i < l && !drop) {
                 const double f = s_col[j & 1][i] * inv;
                 g[e] -= f * s_col[j & 1][k];
                 w[e] -= f * s_t[j * LDT + k];
@@ -431,7 +435,7 @@ __global__ __launch_bounds__(256) void k_lorc_orth(float* __restrict__ A, int64_
         }
     }
     __syncthreads();
-    for (int idx = tid; idx < l * LP; idx += 256) s_t[idx / LP * LDT + idx % LP] *= recip_sqrt(s_d[idx / LP]);
+    for (int idx = tid; idx < l * LP; idx += 256) s_t[idx / LP * LDT + idx % LP] *= s_d[idx / LP];
     __syncthreads();
     for (int64_t blk = (int64_t)blockIdx.x * 4 + wave; blk < blocks; blk += 4 * (int64_t)gridDim.x) {
         float* a = A + blk * LP * 16;

@@ -142,3 +142,42 @@ def test_factors_hold_the_energy_of_their_singular_values_on_a_flat_spectrum(r):
     assert np.all(np.abs(V @ V.T - np.diag(sigma)) <= bar * root), np.abs((V @ V.T - np.diag(sigma)) / root).max()
     captured = np.linalg.norm(E) ** 2 - np.linalg.norm(E - U @ V) ** 2
     assert abs(captured - np.sum(sigma ** 2)) <= bar * so[0] * np.sum(sigma), (captured, np.sum(sigma ** 2))
+
+
+def _steep(K, N, kind, l):
+    """A matrix that bfloat16 holds exactly and its singular values, largest first: single elements of falling size, or
+    outer products of +-1 patterns with disjoint supports (dense dependent columns)."""
+    rng = np.random.default_rng(3)
+    E, n = np.zeros((K, N)), min(K, N)
+    if kind.startswith("blocks"):
+        nb, ratio = (3, 1.0) if kind == "blocks3" else (l, 4.0)
+        ks, ns = K // nb, N // nb
+        for i in range(nb):
+            E[i * ks:(i + 1) * ks, i * ns:(i + 1) * ns] = np.outer(rng.choice([-1.0, 1.0], ks), rng.choice([-1.0, 1.0], ns)) * ratio ** -i
+        s = np.concatenate([np.sqrt(ks * ns) * ratio ** -np.arange(nb), np.zeros(n - nb)])
+    else:
+        s = {"zero": np.zeros(n), "rank3": (np.arange(n) < 3) * 1.0, "rank r": (np.arange(n) < l - 8) * 1.0,
+             "fourths": 4.0 ** -np.arange(n, dtype=float), "sixteenths": 16.0 ** -np.minimum(np.arange(n, dtype=float), 30)}[kind]
+        E[rng.permutation(K)[:n], rng.permutation(N)[:n]] = s
+    return inputs.f32_to_bf16_bits(E.astype(np.float32)), s
+
+
+@pytest.mark.parametrize("kind", ["zero", "rank3", "rank r", "fourths", "sixteenths", "blocks3", "blocks by fourths"])
+@pytest.mark.parametrize("r", [1, 4, 8, 16, 40])
+@pytest.mark.parametrize("q", [0, 2])
+def test_error_matrices_of_low_rank_or_with_a_steep_spectrum(kind, r, q):
+    """Fewer independent columns than r + 8, exactly or to working precision.  Bars: singular values to max(K, N) 2^-24 of the
+    largest (a float32 sum of n terms; the blocks' terms are equal, so that its roundings do add up: 27 2^-24 seen; the basis
+    itself keeps all above 2^-22), U V to the optimum plus the factors' binary16 rounding (2^-10 |sigma|, and
+    2^-24 per element where they are subnormal); without power iterations the optimum is not reached, results are finite."""
+    K, N, G = 384, 320, 128
+    W, s = _steep(K, N, kind, r + 8)
+    packed = zqfp.pack_weight_fp4(bf16_tensor(np.zeros_like(W)), G, 1)
+    U, V, sigma = (t.double().cpu().numpy() for t in zqfp.lorc_factorize(bf16_tensor(W), packed, G, r, _omega(N, r + 8, 1), q))
+    assert np.isfinite(U).all() and np.isfinite(V).all() and np.isfinite(sigma).all()
+    if q or not np.any(s[r:]):
+        E = inputs.bf16_bits_to_f32(W).astype(np.float64)
+        bar = max(K, N) * 2.0 ** -24 * s[0]
+        assert np.all(np.abs(sigma - s[:r]) <= bar), (sigma, s[:r])
+        under = 2.0 ** -24 * np.sqrt(max(K, N) * r * max(s[0], 0.0)) * 2
+        assert np.linalg.norm(E - U @ V) <= np.linalg.norm(s[r:]) + 2.0 ** -10 * np.linalg.norm(s[:r]) + under + bar * np.sqrt(r)
