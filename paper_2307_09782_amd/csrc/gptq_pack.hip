@@ -93,9 +93,9 @@ __global__ __launch_bounds__(256, 2) void k_gptq(const uint16_t* __restrict__ W,
     constexpr int LDE = C + 16;   // error row, for the same reason
     constexpr int LDU = kPanel + 16;
     __shared__ __attribute__((aligned(16))) float s_w[kPanel][LDW];       // the panel's weights as they stand
-    __shared__ __attribute__((aligned(16))) float s_u[2][kSub][LDU];      // a sub-block's rows of U, columns of the panel
-    __shared__ float s_rdiag[2][kSub];                                    // 1 / U[k][k]
-    __shared__ float s_err[2][kSub][LDE];                                 // a sub-block's errors, negated
+    __shared__ __attribute__((aligned(16))) float s_u[2][kSub][LDU];      // a sub-block's rows of U / 2^x, columns of the panel
+    __shared__ v2f s_rdiag[2][kSub];                                      // 1 / (U[k][k] / 2^x), and x (an int's bits)
+    __shared__ float s_err[2][kSub][LDE];                                 // a sub-block's errors times 2^x, negated
     __shared__ float s_amax[4][C];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -183,18 +183,30 @@ __global__ __launch_bounds__(256, 2) void k_gptq(const uint16_t* __restrict__ W,
         }
         return m;
     };
-    // rows of U of the sub-block at row k0 = i0 + 16 t, columns i0 + [0, 128): thread -> 8 floats
-    auto fetch_u = [&](v4f (&u)[2], float& d, int64_t k0, int64_t i0) __attribute__((always_inline)) {
+    // rows of U of the sub-block at row k0 = i0 + 16 t, columns i0 + [0, 128): thread -> 8 floats of row tid / 16, that row's
+    // diagonal, and the diagonal of row tid % 16
+    auto fetch_u = [&](v4f (&u)[2], float& d, float& dr, int64_t k0, int64_t i0) __attribute__((always_inline)) {
         const float* p = U + (k0 + (tid >> 4)) * K + i0 + 8 * (tid & 15);
         u[0] = *reinterpret_cast<const v4f*>(p);
         u[1] = *reinterpret_cast<const v4f*>(p + 4);
         d = U[(k0 + (tid & 15)) * K + k0 + (tid & 15)];
+        dr = U[(k0 + (tid >> 4)) * K + k0 + (tid >> 4)];
     };
-    auto store_u = [&](const v4f (&u)[2], float d, int buf) __attribute__((always_inline)) {
+    // A row of U and its error times the inverse power of two are the same row: every row is held over the 2^x that brings
+    // its diagonal into [1/2, 1), so that neither the reciprocal nor the residual below leaves the normal range.
+    auto store_u = [&](const v4f (&u)[2], float d, float dr, int buf) __attribute__((always_inline)) {
+        const int x = __builtin_amdgcn_frexp_expf(dr);
         float* p = &s_u[buf][tid >> 4][8 * (tid & 15)];
-        *reinterpret_cast<v4f*>(p) = u[0];
-        *reinterpret_cast<v4f*>(p + 4) = u[1];
-        if (tid < kSub) s_rdiag[buf][tid] = 1.0f / d;  // IEEE binary32 division: correctly rounded
+        v4f a, b;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a[i] = ldexpf(u[0][i], -x);
+            b[i] = ldexpf(u[1][i], -x);
+        }
+        *reinterpret_cast<v4f*>(p) = a;
+        *reinterpret_cast<v4f*>(p + 4) = b;
+        if (tid < kSub)  // IEEE binary32 division: correctly rounded
+            s_rdiag[buf][tid] = (v2f){1.0f / __builtin_amdgcn_frexp_mantf(d), __int_as_float(__builtin_amdgcn_frexp_expf(d))};
     };
     // 16 x 16 tile (row block rb of the panel, column block cb) -= its share of a sub-block's errors
     auto push_tile = [&](int rb, int cb, int buf) __attribute__((always_inline)) {
@@ -230,10 +242,10 @@ __global__ __launch_bounds__(256, 2) void k_gptq(const uint16_t* __restrict__ W,
             partial_max(0, L.G, 0.0f);
         }
         v4f u[2];
-        float d;
-        fetch_u(u, d, i0, i0);
-        store_u(u, d, 0);
-        fetch_u(u, d, i0 + kSub, i0);
+        float d, dr;
+        fetch_u(u, d, dr, i0, i0);
+        store_u(u, d, dr, 0);
+        fetch_u(u, d, dr, i0 + kSub, i0);
         __syncthreads();
 
         for (int t = 0; t < kPanel / kSub; ++t) {
@@ -273,13 +285,18 @@ __global__ __launch_bounds__(256, 2) void k_gptq(const uint16_t* __restrict__ W,
                         const v2f q2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c4, scale, 0);
                         const float q = mode == 1 ? q2[0] : q2[0] * cs;
                         code[r >> 3] |= (c4 & 15u) << (4 * (r & 7));
-                        const float diff = w[r] - q, diag = s_u[buf][r][kSub * t + r], rd = s_rdiag[buf][r];
+                        // (w - q) / U[k][k], times 2^x.  One residual correction of the product with the correctly rounded
+                        // reciprocal rounds correctly: it is within 1.5 * 2^-24 ulp of the quotient before its last rounding, and
+                        // quotients that near the middle of two floats leave remainders of a few units; the 2.6e8 mantissa pairs
+                        // that do (every divisor, up to 9 units) all come out as the IEEE division has them.
+                        const v2f rdx = s_rdiag[buf][r];
+                        const float diff = w[r] - q, diag = s_u[buf][r][kSub * t + r], rd = rdx[0];
                         const float y = diff * rd;
-                        const float ev = fmaf(fmaf(-y, diag, diff), rd, y);  // (w - q) / U[k][k]
+                        const float ev = fmaf(fmaf(-y, diag, diff), rd, y);
 #pragma unroll
                         for (int s = r + 1; s < kSub; ++s) w[s] = fmaf(-s_u[buf][r][kSub * t + s], ev, w[s]);
                         s_err[buf][r][lane] = -ev;
-                        err[(k0 + r) * C + lane] = ev;
+                        err[(k0 + r) * C + lane] = ldexpf(ev, -__float_as_int(rdx[1]));
                     }
                     if (chan) {
                         const int kk = (int)(k0 & 127);
@@ -298,8 +315,8 @@ __global__ __launch_bounds__(256, 2) void k_gptq(const uint16_t* __restrict__ W,
             const bool starts_group = ((k0 + kSub) % L.G) == 0;
             const int tiles = starts_group ? (kPanel / kSub - 1 - t) * NT : NT;
             for (int i = wave; i < tiles; i += 4) push_tile(t + 1 + i / NT, i % NT, buf);
-            store_u(u, d, buf ^ 1);
-            if (t + 2 < kPanel / kSub) fetch_u(u, d, k0 + 2 * kSub, i0);
+            store_u(u, d, dr, buf ^ 1);
+            if (t + 2 < kPanel / kSub) fetch_u(u, d, dr, k0 + 2 * kSub, i0);
             __syncthreads();
             if (starts_group) {
                 partial_max(kSub * (t + 1), L.G, 0.0f);

@@ -39,3 +39,19 @@ def test_feedback(K, N, G, mode):
     codes_o, exps_o, c_o, _ = oracle.gptq_fp4(W, U, G, mode)
     assert np.array_equal(c, c_o) and np.array_equal(codes[0], codes_o[0]) and np.array_equal(exps[0], exps_o[0])
     assert np.mean(codes == codes_o) >= 0.995 and np.mean(exps == exps_o) >= 0.995
+
+
+@pytest.mark.parametrize("power", [-125, -60, 60, 126])
+@pytest.mark.parametrize("mode", [1, 2])
+def test_a_power_of_two_on_the_factor_changes_nothing(power, mode):
+    """err = (w - q) / U[k][k] and w -= U[k][j] err: a factor 2^n on U cancels exactly, up to the ends of binary32 (at 2^-125
+    the reciprocals of diagonals of 1 / 8 are out of range).  U has 8-bit entries of at least 2^-16, so none loses a bit."""
+    K, N, G = 256, 100, 64
+    Wd = bf16_tensor(_w(K, N, 5))
+    U = torch.from_numpy((_hessian(K, K)[2] * 0.125).astype(np.float32)).cuda().bfloat16().float()
+    U = torch.where(U.abs() < 2.0 ** -16, torch.zeros_like(U), U).contiguous()
+    assert 2.0 ** -20 < U.diagonal().min().item() and U.diagonal().min().item() < 0.5 and U.diagonal().max().item() < 4
+    want = zqfp.gptq_pack_weight_fp4(Wd, U, G, mode)
+    got = zqfp.gptq_pack_weight_fp4(Wd, (U.double() * 2.0 ** power).float(), G, mode)
+    for a, b in zip(_unpacked(got, K, N, G), _unpacked(want, K, N, G)):
+        assert np.array_equal(a, b)
