@@ -246,12 +246,12 @@ def swiglu_quantize_act_fp8(G, Up, U=None, H=None):
     return (Xq, sx) if U is None else (Xq, sx, T)
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)  # 4096.0 is another key than 4096, and refused
 def _blob_bytes(K, N, G):
     return int(lib().zqfp_packed_weight_bytes(K, N, G))
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)  # 4096.0 is another key than 4096, and refused
 def _blob_bytes_fp8(K, N, G):
     return int(lib().zqfp_packed_weight_fp8_bytes(K, N, G))
 

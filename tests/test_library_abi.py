@@ -177,3 +177,13 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=300)
     assert r.returncode != 0 and "ONE GPU" in r.stderr
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+def test_sizes_that_are_no_integers_stay_refused_after_an_equal_integer(lib, fp8):
+    """The binding keeps blob sizes by (K, N, G); 4096.0 equals 4096 as a key and is no size."""
+    query = zqfp._blob_bytes_fp8 if fp8 else zqfp.packed_weight_bytes
+    assert query(4096, 1024, 128) > 0
+    for args in ((4096.0, 1024, 128), (4096, 1024.0, 128), (4096, 1024, 128.0)):
+        with pytest.raises(ctypes.ArgumentError):
+            query(*args)
