@@ -30,8 +30,9 @@
  *     X, Xq, U, Y, Omega, gain / bias / residual pointers and workspaces must be
  *     16-byte aligned, packed blobs 256-byte aligned, and ldx (and the other
  *     activation row strides) multiples of 8 elements (ZQFP_E_ALIGN).  The
- *     offline weight-side calls read W element by element: W needs only its
- *     natural 2-byte alignment and ldw >= N.
+ *     offline weight-side calls ask for no more than natural alignment of
+ *     what they quantize: W may start at any even address with any ldw >= N,
+ *     Hinv_u at any multiple of 4 bytes.
  *   - Thread safety: calls may be made from several host threads; the error
  *     text is per thread, one-time kernel set-up is serialised inside.
  */

@@ -36,6 +36,8 @@ template <int NT>
 struct __attribute__((packed, aligned(4))) Floats {
     float v[NT];
 };
+// four of the caller's floats, which may start at any of them
+struct __attribute__((packed, aligned(4))) Row4 { v4f v; };
 
 // acc[h][r][t] += sum_{k in [ka, kb)} U[k][i0 + row] err[k][col], this wave's quarter of the k (chunks of 16, or of 8
 // where 64 columns leave fewer registers, dealt in turn; kb - ka is a multiple of 128).  Instruction (h, r, t) holds rows 64 h + 4 i + r (i = 0..15) and columns
@@ -57,8 +59,8 @@ __device__ __forceinline__ void accumulate_panel(v4f (&acc)[2][4][NT], const flo
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const float* u = U + (k0 + 4 * s) * K + i0 + 4 * j;
-            c.a[s][0] = *reinterpret_cast<const v4f*>(u);
-            c.a[s][1] = *reinterpret_cast<const v4f*>(u + 64);
+            c.a[s][0] = reinterpret_cast<const Row4*>(u)->v;
+            c.a[s][1] = reinterpret_cast<const Row4*>(u + 64)->v;
             c.b[s] = *reinterpret_cast<const Floats<NT>*>(err + (k0 + 4 * s) * C + NT * j);
         }
     };
@@ -187,8 +189,8 @@ __global__ __launch_bounds__(256, 2) void k_gptq(const uint16_t* __restrict__ W,
     // diagonal, and the diagonal of row tid % 16
     auto fetch_u = [&](v4f (&u)[2], float& d, float& dr, int64_t k0, int64_t i0) __attribute__((always_inline)) {
         const float* p = U + (k0 + (tid >> 4)) * K + i0 + 8 * (tid & 15);
-        u[0] = *reinterpret_cast<const v4f*>(p);
-        u[1] = *reinterpret_cast<const v4f*>(p + 4);
+        u[0] = reinterpret_cast<const Row4*>(p)->v;
+        u[1] = reinterpret_cast<const Row4*>(p + 4)->v;
         d = U[(k0 + (tid & 15)) * K + k0 + (tid & 15)];
         dr = U[(k0 + (tid >> 4)) * K + k0 + (tid >> 4)];
     };

@@ -55,3 +55,19 @@ def test_a_power_of_two_on_the_factor_changes_nothing(power, mode):
     got = zqfp.gptq_pack_weight_fp4(Wd, (U.double() * 2.0 ** power).float(), G, mode)
     for a, b in zip(_unpacked(got, K, N, G), _unpacked(want, K, N, G)):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("K,N,G", [(256, 100, 64), (512, 4110, 256)])
+def test_operands_at_natural_alignment(K, N, G):
+    """The factor starts one float into a buffer, the weight one element into each of its rows: the aligned call's blob."""
+    W, U = _w(K, N, 9), _hessian(K, K)[2].astype(np.float32)
+    wide = torch.zeros((K, N + 3), dtype=torch.bfloat16, device="cuda")
+    wide[:, 1:N + 1] = bf16_tensor(W)
+    flat = torch.empty(K * K + 1, dtype=torch.float32, device="cuda")
+    off = flat[1:].view(K, K)
+    off.copy_(torch.from_numpy(U))
+    assert off.data_ptr() % 16 == 4
+    want = zqfp.gptq_pack_weight_fp4(bf16_tensor(W), torch.from_numpy(U).cuda(), G, 1)
+    got = zqfp.gptq_pack_weight_fp4(wide[:, 1:N + 1], off, G, 1)
+    for a, b in zip(_unpacked(got, K, N, G), _unpacked(want, K, N, G)):
+        assert np.array_equal(a, b)
