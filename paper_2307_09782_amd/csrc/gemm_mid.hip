@@ -10,6 +10,8 @@
 // ahead, with no barrier before the partial tiles meet in LDS at the end (fixed order, no atomics, no second launch).
 // What is left at 64 tokens is the 64 * K bytes of activations that every compute unit fetches (4096 x 12288: 5.3 of 14.7 us
 // against 16 tokens; 9.4 of 17.5 before a row's line was loaded by eight lanes).
+#include <type_traits>
+
 #include "zqfp_internal.h"
 
 namespace zqfp {
@@ -154,11 +156,28 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
             y[i] = (sx[m] * cs) * sum[i];
             tr[i] = lorc.T + m * lorc.r;
         }
-        for (int j = 0; j < lorc.r; ++j) {
-            const float v = half_bits_to_f32(lorc.V[(int64_t)j * L.N + n]);
+        // ranks eight and then four at a time, every load ahead of the sums (clamped to the last rank): one after the other they
+        // cost 0.2 us each
+        auto ranks = [&](auto count, int j0) __attribute__((always_inline)) {
+            constexpr int C = decltype(count)::value;
+            float v[C], tv[4][C];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) y[i] = fmaf(tr[i][j], v, y[i]);
-        }
+            for (int q = 0; q < C; ++q) {
+                const int j = min(j0 + q, lorc.r - 1);
+                v[q] = half_bits_to_f32(lorc.V[(int64_t)j * L.N + n]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) tv[i][q] = tr[i][j];
+            }
+#pragma unroll
+            for (int q = 0; q < C; ++q)
+                if (j0 + q < lorc.r) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) y[i] = fmaf(tv[i][q], v[q], y[i]);
+                }
+        };
+        int j0 = 0;
+        for (; j0 + 8 <= lorc.r; j0 += 8) ranks(std::integral_constant<int, 8>{}, j0);
+        for (; j0 < lorc.r; j0 += 4) ranks(std::integral_constant<int, 4>{}, j0);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (m0 + i >= M) break;
