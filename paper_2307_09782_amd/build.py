@@ -32,7 +32,8 @@ def sources():
 # Kernels that issue LDS reads by hand (inline asm) and wait for them by count: a register spill
 # between such a read and its wait would save a value that has not arrived yet, so these must
 # compile without scratch memory.  The compiler's resource remarks are checked after every build.
-NO_SCRATCH_KERNELS = ("k_gemm_tile",)
+# The register-fed GEMM has no hand-issued reads, but a spill inside its loop costs a quarter of its time.
+NO_SCRATCH_KERNELS = ("k_gemm_tile", "k_gemm_mid")
 # The same kernels' device assembly is kept by the compile and checked for another thing the compiler may do to
 # such reads: copy their destination register before the wait (see check_lds_waits).
 HAND_WAIT_SOURCES = {"gemm_tile.hip": "k_gemm_tile"}
@@ -58,7 +59,7 @@ def _check_no_scratch(remarks):
         elif name and any(k in name for k in NO_SCRATCH_KERNELS):
             for key in ("ScratchSize [bytes/lane]:", "VGPRs Spill:"):
                 if text.startswith(key) and int(text[len(key):].split("[")[0]) != 0:
-                    raise RuntimeError(f"{name}: '{text}' -- this kernel must not spill (hand-scheduled LDS reads)")
+                    raise RuntimeError(f"{name}: '{text}' -- this kernel must not spill")
 
 
 def build_lib(verbose=False, jobs=8):

@@ -191,7 +191,9 @@ template <int MT, int S, bool EXACT, int WB>
 hipError_t launch_cfg(int mblocks, const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob, const BlobLayout& L,
                       Lorc lorc, void* Y, int64_t ldy, int out_dtype, hipStream_t s)
 {
-    constexpr int NB = MT == 1 ? 4 : MT == 2 ? 3 : 2;
+    // FP8 weights, 64 tokens and four strips in one pass: a second k-tile in flight does not fit the registers (12288 x 16384, 64
+    // tokens: 57.2 us with 20 bytes a lane spilled, 45.2 with one; 28672 x 8192, 128 tokens: 82.3 -> 70.9)
+    constexpr int NB = MT == 1 ? 4 : MT == 2 ? 3 : WB == 8 && !EXACT && MT * S == 16 ? 1 : 2;
     constexpr size_t smem = (size_t)(S > 2 ? S : 2) * MT * kWaves * 1024;  // partial tiles, the waves' slices before them
     auto kern = k_gemm_mid<MT, S, NB, EXACT, WB>;
     if constexpr (smem > 65536) {  // above the default limit of dynamic LDS, which is a per-function setting

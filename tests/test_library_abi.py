@@ -154,6 +154,14 @@ def test_build_rejects_spills_in_hand_scheduled_kernels():
         build._check_no_scratch(bad)
 
 
+def test_build_rejects_spills_in_the_register_fed_gemm():
+    from paper_2307_09782_amd import build
+    spilled = ("x.hip:1:1: remark: Function Name: _ZN4zqfp10k_gemm_midILi4ELi4ELi2ELb0ELi8EEEv [-Rpass-analysis=kernel-resource-usage]\n"
+               "x.hip:1:1: remark:     ScratchSize [bytes/lane]: 20 [-Rpass-analysis=kernel-resource-usage]\n")
+    with pytest.raises(RuntimeError):
+        build._check_no_scratch(spilled)
+
+
 def test_workspace_query_is_pure_host_logic():
     """zqfp_gemm_workspace_bytes plans on the host (no GPU needed): zero for every benchmark
     configuration, [slices][M][Np] floats where K is split."""
