@@ -57,6 +57,20 @@ int zqfp_probe_force_tile_plan(int bm, int bn, int ksplit, int kg);
  */
 int zqfp_probe_force_decode_waves(int nw);
 
+/*
+ * zqfp_probe_gemm_form -- which kernel serves zqfp_w4a8_gemm* (wbits 4) or
+ * zqfp_w8a8_gemm (wbits 8) for a problem of this size, rank (0: no low-rank
+ * correction) and accumulation mode, with a workspace or without one.  Host
+ * only: nothing is enqueued.  Returns ZQFP_FORM_*, ZQFP_E_SHAPE or
+ * ZQFP_E_MODE.
+ */
+#define ZQFP_FORM_DECODE 1 /* persistent, at most 16 tokens (long K in chunks through the workspace) */
+#define ZQFP_FORM_MID 2    /* a few dozen tokens, long K, few channels: operands straight into registers */
+#define ZQFP_FORM_TILE 3   /* tiles through LDS (K slices through the workspace) */
+#define ZQFP_FORM_STREAM 4 /* weight-streaming, E4M3 weights only */
+int zqfp_probe_gemm_form(int64_t M, int64_t K, int64_t N, int G, int wbits,
+                         int r, int accum, int have_workspace);
+
 #ifdef __cplusplus
 }
 #endif

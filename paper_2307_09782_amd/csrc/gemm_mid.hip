@@ -235,13 +235,15 @@ int best_strips(int64_t M, const BlobLayout& L)
 }  // namespace
 
 // Where this form is the faster one (graph-timed, weights beyond the last-level cache, exact mode, before -> after in us).
-bool gemm_mid_wins(int64_t M, const BlobLayout& L)
+bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum)
 {
+    const bool fast = accum != 0;
     if (M <= 16) {
         // E4M3 weights: K beyond the registers of the persistent kernel, which left it to the streaming one (11008 x 4096,
-        // 16 tokens: 15.2 -> 13.7; 16384 x 12288, 1 token: 45.1 -> 40.5).  At most 8 tokens and two strips per compute
-        // unit: two of the streaming kernel's workgroups share a unit and are ahead (9216 x 8192: 17.2 against 18.3).
-        if (L.wbits == 8) return L.nkt > 40 && (M > 8 || L.nstrips <= 256 || (L.nstrips > 512 && L.nstrips <= 768));
+        // 16 tokens: 15.2 -> 13.7; 16384 x 12288, 1 token: 45.1 -> 40.5).  Up to 11 tokens and two strips per compute
+        // unit: two of the streaming kernel's workgroups share a unit and are ahead (9216 x 8192, 8 / 9 tokens: 17.2 against 18.3 /
+        // 17.7 against 18.6; 12 tokens: 17.8 against 17.8).
+        if (L.wbits == 8) return L.nkt > 40 && (M > 11 || L.nstrips <= 256 || (L.nstrips > 512 && L.nstrips <= 768));
         // K in one piece instead of chunks and a second launch (11008 x 4096, 4 tokens: 11.6 -> 9.5; 28672 x 8192: 28.8 -> 26.4;
         // 16384 x 12288, 16 tokens: 28.8 -> 25.1).  Beyond one round of compute units the persistent kernel's stream wins,
         // as it does where 16 tokens' activations would outweigh a single strip's weights for long (28672 x 4096: 19.5 against 21.2).
@@ -258,13 +260,30 @@ bool gemm_mid_wins(int64_t M, const BlobLayout& L)
     if (L.N < 64) return true;  // the tiled kernel has no such tile
     const float us = mid_us(M, L, best_strips(M, L));
     if (L.wbits == 8) {
-        if (M <= 32 && L.nkt < 16) return false;  // the streaming kernel (1024 x 1024, 24 tokens: 3.8 against 4.3)
+        if (M <= 32 && L.nstrips <= 256) {
+            // The streaming kernel, a strip per compute unit as here and no LDS on the way of the activations: short K (1024 x 1024,
+            // 24 tokens: 3.8 against 4.3; 2048 x 4096, 17 tokens: 5.2 against 5.6), and in the one-pass mode, where it waits for
+            // memory only, while its stream fills the chip (4096 x 4096, 24 tokens: 7.3 against 7.8; 3072 x 3072: 5.7
+            // against 5.5).  From rank 8 on its epilogue, one rank after the other, decides (4096 x 4096, rank 8: 9.1 against 8.3).
+            if (L.nkt < 16 || (r < 8 && L.nkt <= 20 && M < 24)) return false;
+            if (fast && r < 8 && L.nkt <= 40 && L.nstrips >= 192 && L.nkt * L.nstrips >= 5120) return false;
+        }
         // 64 x 128 tiles, one per compute unit, no K-split: fitted (4096 x 12288, 64 tokens: 24.4 -> 18.8; 28672 x 8192:
-        // 111 -> 64.7; 14336 x 2048, 300 tokens: 57.0 -> 32.5)
+        // 111 -> 64.7; 14336 x 2048, 300 tokens: 57.0 -> 32.5).  Near 256 tiles the tiled kernel is 6 to 13 % above its estimate and
+        // this one, bound by HBM or in a second round, 10 to 25 % (12288 x 16384, 96 tokens: 57.9 against 65.8 us; 28672 x 8192, 256 tokens:
+        // 119 against 140; 8192 x 28672, 32 tokens: 49.3 against 53.3).
         const int64_t tiles = (M + 63) / 64 * ((L.Np + 127) / 128);
-        return tiles <= 256 && us < 7.0f + 0.465f * (float)L.nkt * (tiles > 180 ? (float)tiles / 180.0f : 1.0f);
+        return tiles <= 256 && us < 7.0f + 0.465f * (float)L.nkt;
     }
-    return us < p.us;
+    // Both estimates are those of the exact mode.  One pass takes an un-split tiled launch down by 13 to 20 %, this one, which waits for
+    // memory, by 3 to 5 (8192 x 28672, 32 tokens: 29.8 against 33.9; 6144 x 24576, 24 tokens: 22.1 against 24.1), and the
+    // low-rank correction costs the tiled kernel, which stages its factors, half as much (3072 x 20000, 32 tokens, rank 8: 18.7
+    // against 19.1).  Beyond 16384 rows this kernel is slower than its estimate (28672 x 8192, 32 tokens: 37.3 against 38.2 us; one
+    // pass 33.3 against 37.7; 96 tokens, one pass: 43.7 against 46.3).
+    float bar = p.us;
+    if (L.nkt > 128) bar *= fast ? 0.87f : 0.97f;
+    else if (p.ksplit == 1) bar *= fast ? 0.87f : r > 0 ? 0.95f : 1.0f;
+    return us < bar;
 }
 
 hipError_t launch_gemm_mid(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob, const BlobLayout& L,

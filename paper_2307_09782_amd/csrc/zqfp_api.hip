@@ -35,6 +35,20 @@ size_t gemm_workspace_need(int64_t M, int64_t K, int64_t N)
     return p.ksplit > 1 ? (size_t)p.ksplit * (size_t)M * (size_t)Np * sizeof(float) : 0;
 }
 
+// The kernel that serves a GEMM call, with rank r and the caller's workspace or without one (nullptr)
+int gemm_form(int64_t M, const zqfp::BlobLayout& L, int r, int accum, const void* workspace)
+{
+    if (zqfp::gemm_mid_wins(M, L, r, accum)) return ZQFP_FORM_MID;
+    if (L.wbits == 8) {
+        if (zqfp::gemm_w8_decode_supported(M, L)) return ZQFP_FORM_DECODE;
+        // the streaming kernel: at most 16 tokens with long K, or up to 32 tokens on a small matrix
+        const bool small = M <= 32 && L.K * L.N <= (int64_t)1 << 26;
+        return !zqfp::gemm_tile_supported(M, L) || small ? ZQFP_FORM_STREAM : ZQFP_FORM_TILE;
+    }
+    if (zqfp::gemm_decode_supported(M, L, workspace)) return ZQFP_FORM_DECODE;
+    return zqfp::gemm_tile_supported(M, L) ? ZQFP_FORM_TILE : ZQFP_FORM_MID;
+}
+
 int gemm_common(const uint8_t* Xq, const float* sx, int64_t M, int64_t K, const void* packed, int64_t N, int G,
                 const float* T, const void* V, int r, void* Y, int64_t ldy, int out_dtype, int accum, void* workspace,
                 size_t workspace_bytes, void* stream)
@@ -57,13 +71,12 @@ int gemm_common(const uint8_t* Xq, const float* sx, int64_t M, int64_t K, const 
     zqfp::Lorc lorc{r > 0 ? T : nullptr, r > 0 ? static_cast<const uint16_t*>(V) : nullptr, r};
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint8_t* blob = static_cast<const uint8_t*>(packed);
-    hipError_t e = zqfp::gemm_mid_wins(M, L)
-                       ? zqfp::launch_gemm_mid(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, s)
-                   : zqfp::gemm_decode_supported(M, L, workspace)
-                       ? zqfp::launch_gemm_decode(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, workspace, s)
-                   : zqfp::gemm_tile_supported(M, L)
-                       ? zqfp::launch_gemm_tile(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, workspace, s)
-                       : zqfp::launch_gemm_mid(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, s);
+    hipError_t e;
+    switch (gemm_form(M, L, r, accum, workspace)) {
+    case ZQFP_FORM_DECODE: e = zqfp::launch_gemm_decode(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, workspace, s); break;
+    case ZQFP_FORM_TILE: e = zqfp::launch_gemm_tile(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, workspace, s); break;
+    default: e = zqfp::launch_gemm_mid(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, s);
+    }
     return e == hipSuccess ? ZQFP_OK : hip_fail(e);
 }
 
@@ -249,15 +262,13 @@ int zqfp_w8a8_gemm(const uint8_t* Xq, const float* sx, int64_t M, int64_t K, con
     zqfp::Lorc lorc{r > 0 ? T : nullptr, r > 0 ? static_cast<const uint16_t*>(V) : nullptr, r};
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint8_t* blob = static_cast<const uint8_t*>(packed);
-    // the streaming kernel: at most 16 tokens with long K, or up to 32 tokens on a small matrix
-    const bool small = M <= 32 && K * N <= (int64_t)1 << 26;
-    hipError_t e = zqfp::gemm_mid_wins(M, L)
-                       ? zqfp::launch_gemm_mid(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, s)
-                   : zqfp::gemm_w8_decode_supported(M, L)
-                       ? zqfp::launch_gemm_w8_decode(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, s)
-                   : !zqfp::gemm_tile_supported(M, L) || small
-                       ? zqfp::launch_gemm_stream(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, s)
-                       : zqfp::launch_gemm_w8_tile(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, s);
+    hipError_t e;
+    switch (gemm_form(M, L, r, accum, nullptr)) {
+    case ZQFP_FORM_DECODE: e = zqfp::launch_gemm_w8_decode(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, s); break;
+    case ZQFP_FORM_TILE: e = zqfp::launch_gemm_w8_tile(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, s); break;
+    case ZQFP_FORM_STREAM: e = zqfp::launch_gemm_stream(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, s); break;
+    default: e = zqfp::launch_gemm_mid(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, accum, s);
+    }
     return e == hipSuccess ? ZQFP_OK : hip_fail(e);
 }
 
@@ -410,6 +421,14 @@ int zqfp_probe_stream_read(const void* src, int64_t bytes, void* sink, int workg
 int zqfp_probe_force_tile_plan(int bm, int bn, int ksplit, int kg)
 {
     return zqfp::force_tile_plan(bm, bn, ksplit, kg) ? ZQFP_OK : ZQFP_E_SHAPE;
+}
+
+int zqfp_probe_gemm_form(int64_t M, int64_t K, int64_t N, int G, int wbits, int r, int accum, int have_workspace)
+{
+    zqfp::BlobLayout L;
+    if (M <= 0 || N <= 0 || r < 0 || r > 64 || !zqfp::make_layout(K, N, G, &L, wbits)) return ZQFP_E_SHAPE;
+    if (accum != ZQFP_ACCUM_EXACT && accum != ZQFP_ACCUM_FAST) return ZQFP_E_MODE;
+    return gemm_form(M, L, r, accum, have_workspace ? &L : nullptr);
 }
 
 int zqfp_probe_force_decode_waves(int nw)

@@ -311,7 +311,7 @@ hipError_t launch_gemm_tile(const uint8_t* Xq, const float* sx, int64_t M, const
                             int accum, void* workspace, hipStream_t s);
 bool gemm_tile_supported(int64_t M, const BlobLayout& L);
 // few tokens, any shape, both weight formats; gemm_mid_wins: faster than the other forms for this problem
-bool gemm_mid_wins(int64_t M, const BlobLayout& L);
+bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum);
 hipError_t launch_gemm_mid(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob,
                            const BlobLayout& L, Lorc lorc, void* Y, int64_t ldy, int out_dtype,
                            int accum, hipStream_t s);

@@ -19,6 +19,7 @@ LIB_PATH = os.environ.get("ZQFP_LIB_PATH") or os.path.join(_HERE, "libzqfp.so")
 SCALE_M1, SCALE_M2 = 1, 2
 OUT_F32, OUT_BF16 = 0, 1
 ACCUM_EXACT, ACCUM_FAST = 0, 1
+FORM_DECODE, FORM_MID, FORM_TILE, FORM_STREAM = 1, 2, 3, 4  # probe_gemm_form
 
 _ERR = {-1: "ZQFP_E_NULL", -2: "ZQFP_E_SHAPE", -3: "ZQFP_E_ALIGN", -4: "ZQFP_E_MODE", -5: "ZQFP_E_HIP",
         -6: "ZQFP_E_WORKSPACE", -7: "ZQFP_E_BLOB"}
@@ -101,6 +102,8 @@ def lib():
         L.zqfp_probe_force_tile_plan.argtypes = [c.c_int, c.c_int, c.c_int, c.c_int]
         L.zqfp_probe_force_decode_waves.restype = c.c_int
         L.zqfp_probe_force_decode_waves.argtypes = [c.c_int]
+        L.zqfp_probe_gemm_form.restype = c.c_int
+        L.zqfp_probe_gemm_form.argtypes = [i64, i64, i64, c.c_int, c.c_int, c.c_int, c.c_int, c.c_int]
         L.zqfp_probe_mfma.restype = c.c_int
         L.zqfp_probe_mfma.argtypes = [p, p, c.c_int, c.c_int, p]
         _lib = L
@@ -539,3 +542,11 @@ def probe_force_tile_plan(bm=0, bn=0, ksplit=0, kg=1):
 def probe_force_decode_waves(nw=8):
     """Tuning hook: 8 or 16 waves per workgroup of the decode GEMM (K <= 4096)."""
     _check(lib().zqfp_probe_force_decode_waves(nw))
+
+
+def probe_gemm_form(M, K, N, G=128, wbits=4, r=0, accum=ACCUM_EXACT, have_workspace=True):
+    """Which kernel (FORM_*) serves a GEMM call of this size, rank and accumulation mode; nothing is enqueued."""
+    form = lib().zqfp_probe_gemm_form(M, K, N, G, wbits, r, accum, int(have_workspace))
+    if form < 0:
+        raise ZqfpError(form)
+    return form

@@ -38,10 +38,21 @@ def _case(name, M, K=None, N=None, rank=None):
     return X, Y, step, ws_bytes
 
 
-CASES = [("llama70b_ffn_decode", 16, None, 2048, None),   # decode form with LoRC
-         ("llama7b_qkv", 300, None, 1024, 0),              # tiled form
-         ("llama7b_qkv", 64, 11008, 512, 8),               # tiled form with a K-split through the workspace
-         ("llama7b_qkv", 12, 28672, 8192, 0)]              # decode form, K in chunks through the workspace
+CASES = [("llama70b_ffn_decode", 16, None, 2048, None),   # a few dozen tokens' form at its fewest, with LoRC
+         ("llama70b_ffn_decode", 4, 4096, 2048, None),      # decode form with LoRC
+         ("llama7b_qkv", 300, None, 1024, 0),               # 300 tokens, few channels
+         ("llama7b_qkv", 300, 512, 4000, 0),                # tiled form
+         ("llama7b_qkv", 64, 11008, 512, 8),                # tiled form with a K-split through the workspace
+         ("llama7b_qkv", 12, 28672, 8192, 0),               # K in one piece, no workspace touched
+         ("llama7b_qkv", 12, 24704, 4090, 0)]               # decode form, K in chunks through the workspace
+FORMS = [zqfp.FORM_MID, zqfp.FORM_DECODE, zqfp.FORM_MID, zqfp.FORM_TILE, zqfp.FORM_TILE, zqfp.FORM_MID, zqfp.FORM_DECODE]
+
+
+def test_the_cases_reach_the_kernels_they_name():
+    for (name, M, K, N, rank), form in zip(CASES, FORMS):
+        cfg = CFG[name]
+        r = cfg.rank if rank is None else rank
+        assert zqfp.probe_gemm_form(M, K or cfg.K, N, cfg.G, r=r) == form, (name, M, K, N)
 
 
 @pytest.mark.parametrize("name,M,K,N,rank", CASES)
@@ -62,7 +73,7 @@ def test_step_on_a_side_stream_matches_the_default_stream(name, M, K, N, rank):
 @pytest.mark.parametrize("name,M,K,N,rank", CASES)
 def test_captured_step_replays_to_the_bits_of_the_eager_step(name, M, K, N, rank):
     X, Y, step, ws_bytes = _case(name, M, K, N, rank)
-    if name == "llama7b_qkv" and M in (64, 12):
+    if K in (11008, 24704):
         assert ws_bytes > 0  # these cases are here for the workspace paths
     X2 = torch.flip(X, dims=[0]).contiguous()
     wants = []

@@ -195,3 +195,34 @@ def test_sizes_that_are_no_integers_stay_refused_after_an_equal_integer(lib, fp8
     for args in ((4096.0, 1024, 128), (4096, 1024.0, 128), (4096, 1024, 128.0)):
         with pytest.raises(ctypes.ArgumentError):
             query(*args)
+
+
+D, M_, T, S = zqfp.FORM_DECODE, zqfp.FORM_MID, zqfp.FORM_TILE, zqfp.FORM_STREAM
+
+
+@pytest.mark.parametrize("wbits,M,K,N,r,accum,form", [
+    # one pass, or a low-rank correction: the tiled kernel gains more from the first and loses less to the second
+    (4, 24, 8192, 28672, 0, 0, M_), (4, 24, 8192, 28672, 0, 1, T), (4, 32, 8192, 28672, 8, 0, T), (4, 17, 6144, 24576, 4, 1, T),
+    (4, 32, 3072, 20000, 8, 0, T), (4, 32, 3072, 20000, 0, 1, T), (4, 64, 4096, 12288, 8, 1, M_),
+    # K beyond 16384 rows
+    (4, 32, 28672, 8192, 0, 0, T), (4, 96, 28672, 8192, 0, 1, T), (4, 65, 28672, 8192, 0, 0, M_), (4, 64, 11008, 4096, 0, 0, M_),
+    # E4M3 weights: near 256 tiles, weights beyond what HBM hides; the streaming kernel's corners
+    (8, 96, 12288, 16384, 0, 0, T), (8, 64, 12288, 16384, 0, 1, M_), (8, 256, 28672, 8192, 0, 0, T), (8, 32, 8192, 28672, 0, 0, T),
+    (8, 24, 6144, 24576, 0, 1, T), (8, 9, 9216, 8192, 0, 0, S), (8, 12, 9216, 8192, 0, 0, M_), (8, 17, 2048, 4096, 0, 0, S),
+    (8, 17, 2048, 4096, 8, 0, M_), (8, 24, 4096, 4096, 0, 1, S), (8, 24, 4096, 4096, 0, 0, M_), (8, 24, 3072, 3072, 0, 1, M_),
+    (8, 16, 4096, 4096, 0, 0, D), (4, 16, 28672, 4096, 0, 0, D), (4, 16, 4096, 12288, 0, 0, D)])
+def test_which_kernel_serves_a_gemm(lib, wbits, M, K, N, r, accum, form):
+    """The choice is host logic; each of these is where one kernel measured faster than the other by 3 % or more
+    (the figures stand at the rule), or a plain member of a form's range."""
+    assert zqfp.probe_gemm_form(M, K, N, 128, wbits, r, accum) == form
+
+
+def test_gemm_form_query_refuses_what_the_gemm_refuses(lib):
+    for args in ((0, 4096, 4096), (1, 4000, 4096), (1, 4096, 0), (1, 4096, 4096, 96), (1, 4096, 4096, 64, 8), (1, 4096, 4096, 128, 5),
+                 (1, 4096, 4096, 128, 4, 65)):
+        with pytest.raises(zqfp.ZqfpError) as e:
+            zqfp.probe_gemm_form(*args)
+        assert e.value.code == -2
+    with pytest.raises(zqfp.ZqfpError) as e:
+        zqfp.probe_gemm_form(1, 4096, 4096, accum=2)
+    assert e.value.code == -4

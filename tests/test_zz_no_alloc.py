@@ -54,11 +54,13 @@ def _oracle_check(c, Y, what):
 
 
 def test_two_calls_in_a_row_share_the_array_second_one_smaller():
-    print("static entry point: decode form in 4 chunks (M=16 K=28672 N=4096), then one tile split 4 ways (M=64 K=4096 N=128)",
+    print("static entry point: decode form in 4 chunks (M=16 K=28672 N=4096), then two tiles split 10 ways (M=33 K=11008 N=256)",
           flush=True)
     big = _case(16, 28672, 4096, 128, 1, 8, 11)        # 224 k-tiles: 4 chunks of 56, 4 * 16 * 4096 floats of partials
-    small = _case(64, 4096, 128, 128, 1, 8, 12)        # one 64 x 128 tile, K split 4 ways: 4 * 64 * 128 floats
-    assert zqfp.gemm_workspace_bytes(16, 28672, 4096) > zqfp.gemm_workspace_bytes(64, 4096, 128) > 0
+    small = _case(33, 11008, 256, 128, 1, 8, 12)       # two 64 x 128 tiles, K split 10 ways: 10 * 33 * 256 floats
+    assert zqfp.gemm_workspace_bytes(16, 28672, 4096) > zqfp.gemm_workspace_bytes(33, 11008, 256) > 0
+    assert zqfp.probe_gemm_form(16, 28672, 4096, r=8) == zqfp.FORM_DECODE
+    assert zqfp.probe_gemm_form(33, 11008, 256, r=8) == zqfp.FORM_TILE
     a1, b1 = _both(big)
     a2, b2 = _both(small)
     assert np.array_equal(a1, b1) and np.array_equal(a2, b2)
@@ -71,7 +73,7 @@ def test_two_calls_in_a_row_share_the_array_second_one_smaller():
 
 
 @pytest.mark.parametrize("M,K,N,G,mode,r", [(16, 256, 256, 128, 1, 0), (200, 1280, 400, 256, 2, 0), (33, 11008, 256, 128, 2, 0),
-                                         (100, 3072, 136, 128, 1, 3)])
+                                         (100, 3072, 136, 128, 1, 3), (64, 4096, 128, 128, 1, 8), (100, 14336, 136, 128, 1, 3)])
 def test_static_equals_workspace_form(M, K, N, G, mode, r):
     print(f"static entry point: M={M} K={K} N={N} G={G} mode={mode} r={r}", flush=True)
     c = _case(M, K, N, G, mode, r, 13)
