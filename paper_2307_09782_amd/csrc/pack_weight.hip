@@ -27,9 +27,10 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 // largest group magnitude a power-of-two scale maps onto: 6 (E2M1) or 448 (E4M3)
 __device__ inline float format_max(const BlobLayout& L) { return L.wbits == 8 ? 448.0f : 6.0f; }
 
-// M2's column scale, absmax / format maximum (1 for an all-zero column, 0 for padding columns), into the blob.
+// M2's column scale, absmax / format maximum (1 for an all-zero column, 0 for padding columns), into the blob; where one
+// group spans a column, its exponent byte too.
 // One workgroup per 64 columns walks the whole K: 128 bytes of a row per wave, eight rows in flight per wave.
-__global__ __launch_bounds__(1024) void k_column_scale(const uint16_t* __restrict__ W, int64_t ldw, BlobLayout L,
+__global__ __launch_bounds__(1024) void k_column_scale(const uint16_t* __restrict__ W, int64_t ldw, BlobLayout L, int mode,
                                                        uint8_t* __restrict__ blob)
 {
     __shared__ float s_max[16][kCols];
@@ -49,7 +50,11 @@ __global__ __launch_bounds__(1024) void k_column_scale(const uint16_t* __restric
     if (wave == 0 && n < L.Np) {
 #pragma unroll
         for (int i = 1; i < 16; ++i) m = fmaxf(m, s_max[i][c]);
-        reinterpret_cast<float*>(blob + L.off_colscale)[n] = n >= L.N ? 0.0f : m != 0.0f ? m / format_max(L) : 1.0f;  // IEEE binary32 division
+        reinterpret_cast<float*>(blob + L.off_colscale)[n] = n >= L.N ? 0.0f : mode != 1 && m != 0.0f ? m / format_max(L) : 1.0f;  // IEEE binary32 division
+        if (L.G == L.K) {  // one stored group, one dword per column
+            const int e = mode != 1 ? -m2_shift(m, m) : L.wbits == 8 ? m1_exponent_e4m3(m) : m1_exponent(m);
+            reinterpret_cast<uint32_t*>(blob + L.off_exps)[n] = 0x7F7F7F00u | (uint32_t)(n < L.N ? e + 127 : 127);
+        }
     }
 }
 
@@ -102,7 +107,8 @@ __device__ inline void encode_block(const uint32_t (&x)[16], int mode, int e, fl
 
 // TILES: k-tiles of a unit, kept in registers between the absmax and the codes (1 or 2); 0: a unit of any length,
 // walked four k-tiles at a time by 1024 threads and read a second time for the codes (from L2 where it fits).
-template <int TILES, int WBITS>
+// WHOLE: one group spans a column and k_column_scale has written its scale and exponent; the k-tiles are independent.
+template <int TILES, int WBITS, bool WHOLE = false>
 __global__ __launch_bounds__(TILES == 0 ? 1024 : 256) void k_pack_weight(const uint16_t* __restrict__ W, int64_t ldw, BlobLayout L,
                                                                          int mode, int unit_tiles, uint8_t* __restrict__ blob)
 {
@@ -132,10 +138,14 @@ __global__ __launch_bounds__(TILES == 0 ? 1024 : 256) void k_pack_weight(const u
         atomicMax(&s_gmax[(t * 4 + q) / blocks_per_group][c], __float_as_uint(m));
     };
 
-    s_gmax[tid >> 6 & 3][c] = 0u;
-    __syncthreads();
+    if constexpr (!WHOLE) {
+        s_gmax[tid >> 6 & 3][c] = 0u;
+        __syncthreads();
+    }
     uint32_t x[TILES == 0 ? 1 : TILES][16];
-    if constexpr (TILES == 0) {
+    if constexpr (WHOLE) {
+        load_block(kt0, x[0]);
+    } else if constexpr (TILES == 0) {
         for (int t = par; t < unit_tiles; t += PAR) {
             load_block(kt0 + t, x[0]);
             group_max(t, x[0]);
@@ -150,18 +160,25 @@ __global__ __launch_bounds__(TILES == 0 ? 1024 : 256) void k_pack_weight(const u
     if (mode != 1 && live) {  // padding columns: +0 over 1
         cs = colscale[n];
         // the column's absmax is a bfloat16 value and cs is it over the format maximum, correctly rounded: the
-        // product is within 2^-14 of it, relatively, and rounds back to it (an all-zero column has no use for it)
+        // product is within 2^-23 of it, relatively (2^-9 where cs is subnormal: an absmax below 2^-117, with 448), and
+        // rounds back to it (an all-zero column has no use for it)
         cmax = bf16_bits_to_f32(f32_to_bf16_bits(cs * format_max(L)));
     }
-    __syncthreads();
+    if constexpr (!WHOLE) __syncthreads();
     if (!in_blob) return;  // no barrier below
 
     auto finish_tile = [&](int t, const uint32_t (&xt)[16]) __attribute__((always_inline)) {
-        const float amax = __uint_as_float(s_gmax[(t * 4 + q) / blocks_per_group][c]);
-        const int e = mode == 1 ? (WBITS == 8 ? m1_exponent_e4m3(amax) : m1_exponent(amax)) : -m2_shift(cmax, amax);
+        int e;
+        if constexpr (WHOLE) {
+            e = (int)(reinterpret_cast<const uint32_t*>(blob + L.off_exps)[n] & 0xFFu) - 127;
+        } else {
+            const float amax = __uint_as_float(s_gmax[(t * 4 + q) / blocks_per_group][c]);
+            e = mode == 1 ? (WBITS == 8 ? m1_exponent_e4m3(amax) : m1_exponent(amax)) : -m2_shift(cmax, amax);
+        }
         const int64_t kt = kt0 + t, strip = n >> 4;
         const int col = c & 15;
         encode_block<WBITS>(xt, mode, e, cs, blob + L.off_codes + (size_t)(strip * L.nkt + kt) * (256 * WBITS), q, col);
+        if constexpr (WHOLE) return;
         // exponent bytes, [strip][quad][column][4], one per stored group; the last dword is filled up with 127
         const int64_t k = kt * 128 + 32 * q;
         if (k % L.Gs == 0) {
@@ -181,7 +198,7 @@ __global__ __launch_bounds__(TILES == 0 ? 1024 : 256) void k_pack_weight(const u
 #pragma unroll
         for (int t = 0; t < TILES; ++t) finish_tile(t, x[t]);
     }
-    if (mode == 1 && blockIdx.y == 0 && tid < kCols) colscale[n] = live ? 1.0f : 0.0f;
+    if (!WHOLE && mode == 1 && blockIdx.y == 0 && tid < kCols) colscale[n] = live ? 1.0f : 0.0f;
     if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
         BlobHeader h;
         h.magic = kBlobMagic; h.version = kBlobVersion;
@@ -230,14 +247,20 @@ hipError_t launch_pack_weight(const uint16_t* W, int64_t ldw, const BlobLayout& 
     const int64_t unit = (int64_t)L.G / gcd_int(L.G, 128) * 128;
     const int tiles = (int)(unit / 128);
     const unsigned gx = (unsigned)((L.Np + kCols - 1) / kCols);
-    const dim3 grid(gx, (unsigned)(L.K / unit));
-    if (mode != 1) hipLaunchKernelGGL(k_column_scale, dim3(gx), dim3(1024), 0, s, W, ldw, L, blob);
-#define ZQ_PACK(TILES, WB) \
-    hipLaunchKernelGGL((k_pack_weight<TILES, WB>), grid, dim3(TILES == 0 ? 1024 : 256), 0, s, W, ldw, L, mode, tiles, blob)
+    // One group per column and more than its registers hold: where the absmax takes a launch anyway (M2), or from 1024 rows on, the
+    // exponent comes with it and the codes from as many workgroups as there are k-tiles, instead of one workgroup for the
+    // whole column twice over (FP8, 1024 columns, M2: 384 rows 10.8 -> 7.0 us, 4096 rows 63.2 -> 16.2; M1, 4096 rows 53.5 -> 16.3;
+    // FP4, 512 rows: M1 6.6 in one launch, M2 7.0 in these two).
+    const bool whole = tiles > 2 && L.G == L.K && (mode != 1 || tiles >= 8);
+    const dim3 grid(gx, (unsigned)(whole ? L.nkt : L.K / unit));
+    if (mode != 1 || whole) hipLaunchKernelGGL(k_column_scale, dim3(gx), dim3(1024), 0, s, W, ldw, L, mode, blob);
+#define ZQ_PACK(TILES, WB, ...) \
+    hipLaunchKernelGGL((k_pack_weight<TILES, WB, ##__VA_ARGS__>), grid, dim3(TILES == 0 ? 1024 : 256), 0, s, W, ldw, L, mode, \
+                       whole ? 1 : tiles, blob)
     if (L.wbits == 8) {
-        if (tiles == 1) ZQ_PACK(1, 8); else if (tiles == 2) ZQ_PACK(2, 8); else ZQ_PACK(0, 8);
+        if (whole) ZQ_PACK(1, 8, true); else if (tiles == 1) ZQ_PACK(1, 8); else if (tiles == 2) ZQ_PACK(2, 8); else ZQ_PACK(0, 8);
     } else {
-        if (tiles == 1) ZQ_PACK(1, 4); else if (tiles == 2) ZQ_PACK(2, 4); else ZQ_PACK(0, 4);
+        if (whole) ZQ_PACK(1, 4, true); else if (tiles == 1) ZQ_PACK(1, 4); else if (tiles == 2) ZQ_PACK(2, 4); else ZQ_PACK(0, 4);
     }
 #undef ZQ_PACK
     return hipGetLastError();

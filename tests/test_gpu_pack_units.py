@@ -23,7 +23,8 @@ def _weights(K, N, G, seed):
 
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("K,N,G", [(128, 1, 128), (128, 63, 64), (256, 64, 32), (256, 65, 128), (512, 129, 256), (768, 80, 384),
-                                   (1024, 48, 1024), (1920, 130, 320), (1152, 66, 96), (4096, 191, 128)])
+                                   (1024, 48, 1024), (1920, 130, 320), (1152, 66, 96), (4096, 191, 128), (384, 66, 384), (2048, 17, 2048),
+                                   (896, 64, 896)])
 def test_fp4_units_bit_exact(K, N, G, mode):
     W = _weights(K, N, G, K + N)
     packed = zqfp.pack_weight_fp4(bf16_tensor(W), G, mode)
@@ -37,7 +38,8 @@ def test_fp4_units_bit_exact(K, N, G, mode):
 
 
 @pytest.mark.parametrize("mode", [1, 2])
-@pytest.mark.parametrize("K,N,G", [(128, 63, 128), (512, 65, 256), (1536, 130, 384), (2048, 64, 128)])
+@pytest.mark.parametrize("K,N,G", [(128, 63, 128), (512, 65, 256), (1536, 130, 384), (2048, 64, 128), (384, 20, 384), (1024, 130, 1024),
+                                   (2176, 65, 2176)])
 def test_fp8_units_bit_exact_rows_of_any_stride(K, N, G, mode):
     W = _weights(K, N, G, K + N)
     wide = torch.zeros((K, N + 3), dtype=torch.bfloat16, device="cuda")  # rows start at any 2-byte address
