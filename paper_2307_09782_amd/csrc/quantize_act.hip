@@ -239,11 +239,16 @@ __global__ __launch_bounds__(NT) void k_quantize_act(const uint16_t* __restrict_
     // Rank 8 behind the RMS normalisation: the rows of U that meet the thread's first chunk are loaded here, not behind the
     // normalisation whose result they are multiplied with (300 x 5120: 10.4 -> 8.7 us, 800 x 4096: 12.0 -> 11.1, 16 x 8192:
     // 9.1 -> 8.9; behind the other producers it cost 1 to 4 %).  A row past the end is read as row 0 and zeroed at its use.
+    // In 1024 threads (few tokens, or rows beyond 8192 elements) only where it gains: a thread with several chunks of the row, and
+    // of the residual, ahead of its sums waits for these loads as well (1 x 11008 with a residual: 10.1 us with them, 9.4 without;
+    // 128 x 20480: 13.3, 12.4; 300 x 11008, no residual: 18.5, 17.7; the other way round at 300 x 20480 with one: 26.3, 28.9).
     constexpr bool EARLY_U = RP == 8 && NORM == 1;
     uint4 u0[EARLY_U ? 8 : 1];
     const int64_t k0 = (int64_t)(tid & ~63) * 8 + (tid & 63);
+    const bool early = EARLY_U && r == 8 &&
+                       (NT != 1024 || (K > 4096 && K <= 8192) || (pr.other == nullptr ? K > 12288 : K > 16384 && gridDim.x > 256));
     if constexpr (EARLY_U) {
-        if (r == 8 && (tid & ~63) < nchunk) {
+        if (early && (tid & ~63) < nchunk) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) u0[i] = reinterpret_cast<const uint4*>(U)[k0 + 64 * i < K ? k0 + 64 * i : 0];
         }
@@ -341,7 +346,7 @@ __global__ __launch_bounds__(NT) void k_quantize_act(const uint16_t* __restrict_
 #pragma unroll
             for (int i = 0; i < 8; ++i) x[i] = __uint_as_float((uint32_t)s_x[wave][lane + 64 * i] << 16);
             if constexpr (EARLY_U)
-                if (first && r == 8) {
+                if (first && early) {
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         const bool live = k0 + 64 * i < K;
