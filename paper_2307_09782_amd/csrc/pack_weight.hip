@@ -9,8 +9,8 @@
 // group agree on its absmax in LDS.  Bound by HBM (2 B read, 0.5 B written per weight).  With W in its natural
 // order the loads are 2 bytes per lane, 128 bytes per instruction and 32 of them in flight per thread, which also
 // serves rows of any alignment; the vector work is about four operations per weight because the code and the division
-// by the power-of-two scale are one hardware conversion per pair (v_cvt_scalef32_pk_fp4: equal to the encoder of the
-// shared header on all 2^32 binary32 values, and on every bfloat16 value under every scale).  4096 x 12288, G = 128,
+// by the power-of-two scale are one hardware conversion per pair (v_cvt_scalef32_pk_fp4: round to nearest, ties to the even
+// code, saturating at 6, sign kept -- compared on all 2^32 binary32 values, and on every bfloat16 value under every scale).  4096 x 12288, G = 128,
 // M1: 249 -> 25 us (a workgroup per 16 columns before: 32-byte pieces of lines that four L2s fetched, the whole K in
 // sequence, a compare chain per code).
 #include "zqfp_internal.h"

@@ -185,7 +185,7 @@ __device__ inline void token_scale(uint32_t absmax_bf16_bits, float& scale, floa
 }
 
 // ---------------------------------------------------------------------------
-// E2M1 and scale helpers shared by the weight-side kernels (packer, GPTQ, LoRC error matrix)
+// Scale helpers shared by the weight-side kernels (packer, GPTQ); E2M1 codes come from and go to the hardware conversions
 // ---------------------------------------------------------------------------
 __device__ inline float bf16_bits_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -220,23 +220,6 @@ __device__ inline int m2_shift(float amax_max, float amax_g)
     int k = 0;
     while (k < 15 && amax_max > ldexpf(amax_g, k)) ++k;
     return k;
-}
-
-// round to nearest E2M1 magnitude, ties to the even code, saturating at 6; sign bit copied
-__device__ inline uint32_t e2m1_encode(float y)
-{
-    const float a = fabsf(y);
-    const uint32_t c = a <= 0.25f ? 0u : a < 0.75f ? 1u : a <= 1.25f ? 2u : a < 1.75f ? 3u
-                     : a <= 2.5f ? 4u : a < 3.5f ? 5u : a <= 5.0f ? 6u : 7u;
-    return c | ((__float_as_uint(y) >> 28) & 8u);
-}
-
-// value of an E2M1 code (sign . 2 exponent bits . 1 mantissa bit, bias 1): 0, 0.5, 1, 1.5, 2, 3, 4, 6
-__device__ inline float e2m1_value(uint32_t code)
-{
-    const uint32_t mag = code & 7u;
-    const float v = mag < 2u ? 0.5f * (float)mag : (float)(2u + (mag & 1u)) * (float)(1u << ((mag >> 1) - 1u)) * 0.5f;
-    return (code & 8u) ? -v : v;
 }
 
 // Tile shape, wave groups and K-split of the tiled GEMM for a problem (the launcher and the workspace query
