@@ -282,8 +282,8 @@ def quantizer_rows(name="llama7b_qkv", M=4096):
 
 
 def offline_rows(name="llama7b_qkv", r=8, power_iters=2):
-    """The LoRC factorisation of one layer's quantization error (offline step): time, and the rate at which
-    it streams the float32 error matrix (one write, 2 + 2 * power_iters reads, plus W and the packed weight)."""
+    """The LoRC factorisation of one layer's quantization error (offline step): time, and the rate at which its
+    2 + 2 * power_iters passes read W and the packed codes (2.5 bytes per weight; the error is formed in registers)."""
     cfg = inputs.CONFIGS[name]
     W = bf16_dev(inputs.make_w(cfg))
     packed = zqfp.pack_weight_fp4(W, cfg.G, cfg.mode)
@@ -297,7 +297,7 @@ def offline_rows(name="llama7b_qkv", r=8, power_iters=2):
     b.record()
     torch.cuda.synchronize()
     ms = a.elapsed_time(b) / 3
-    nbytes = cfg.K * cfg.N * (2 + 0.5 + 4 + 4 * (2 + 2 * power_iters))
+    nbytes = cfg.K * cfg.N * (2 + 0.5) * (2 + 2 * power_iters)
     rows = [{"call": "lorc_factorize", "workload": f"{name} K={cfg.K} N={cfg.N} rank {r}, {power_iters} power iterations",
              "ms": round(ms, 4), "gbs": round(nbytes / (ms * 1e-3) / 1e9, 1)}]
     # GPTQ on the same layer: the float32 matrix products behind the row blocks dominate (K^2 N multiply-adds)
@@ -408,6 +408,8 @@ def main():
     main_wl = Workload(args.workload, args.M, accum, copies)
     ms, gemm_ms = main_wl.run(args.steps, args.warmup)
     cfg = main_wl.cfg
+    kernel = {zqfp.FORM_DECODE: "k_gemm_decode", zqfp.FORM_MID: "k_gemm_mid", zqfp.FORM_TILE: "k_gemm_tile"}[
+        zqfp.probe_gemm_form(args.M, cfg.K, cfg.N, cfg.G, r=cfg.rank, accum=accum)]
     value = main_wl.flops / (ms * 1e-3) / 1e12
     if decode:
         gemm_ms = main_wl.gemm_graph_ms()
@@ -415,7 +417,7 @@ def main():
         roofline = {"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                     "frac": round(gbs / PEAK_HBM_GBS, 4),
                     "traffic": measured_traffic(f"{args.workload} M={args.M} {args.accum}"),
-                    "kernel": "k_gemm_decode" if args.M <= 16 else "k_gemm_tile", "kernel_ms": round(gemm_ms, 5),
+                    "kernel": kernel, "kernel_ms": round(gemm_ms, 5),
                     "weight_copies_rotated": copies}
     else:
         gemm_tflops = main_wl.flops / (gemm_ms * 1e-3) / 1e12
@@ -424,7 +426,7 @@ def main():
                     "traffic": measured_traffic(f"{args.workload} M={args.M} {args.accum}"),
                     "traffic_source": "profiles/hbm_traffic.json: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command, "
                                       "calibrated on a 1 GiB copy; a stored figure, not counted in this run",
-                    "kernel": "k_gemm_tile", "kernel_ms": round(gemm_ms, 5),
+                    "kernel": kernel, "kernel_ms": round(gemm_ms, 5),
                     "kernel_ms_median": round(main_wl.kernel_ms_median, 5), "kernel_ms_min": round(main_wl.kernel_ms_min, 5)}
         if args.accum == "exact":
             # every activation tile is fed to the matrix cores twice (two exponent bands): twice the instructions

@@ -262,6 +262,7 @@ int zqfp_packed_weight_check(const void *header, int64_t K, int64_t N, int G);
  * found by a subspace iteration with r + 8 columns and `power_iters` rounds
  * (2 is enough for quantization error, whose spectrum is flat), so that the
  * residual |E - U V|_F is within a fraction of a percent of the optimum.
+ * Singular values below about 2^-22 of the largest may come out as zero.
  *
  *   W        [K, N] bfloat16, row stride ldw                           (in)
  *   packed   the blob zqfp_pack_weight_fp4 made (of W, or of any K x N
@@ -303,8 +304,9 @@ int zqfp_lorc_factorize(const void *W, int64_t K, int64_t N, int64_t ldw,
  *   G         32, 64, 128 or 256
  *   packed    zqfp_packed_weight_bytes(K, N, G) bytes, 256-byte aligned (out)
  *   workspace zqfp_gptq_workspace_bytes(K, N, G) bytes of device memory,
- *             256-byte aligned (a float32 working copy of W and one block
- *             of errors)
+ *             256-byte aligned (every channel's error, K x N float32 in
+ *             stripes of up to 64 output channels, and a panel of 128 rows
+ *             that groups of 256 hold back)
  */
 size_t zqfp_gptq_workspace_bytes(int64_t K, int64_t N, int G);
 int zqfp_gptq_pack_weight_fp4(const void *W, int64_t K, int64_t N, int64_t ldw,
@@ -338,9 +340,11 @@ int zqfp_unpack_codes(const void *packed, int64_t K, int64_t N, int G,
  *   workspace  zqfp_gemm_workspace_bytes(M, K, N) bytes of device memory,
  *            16-byte aligned; contents need not be initialised and are not
  *            preserved.  It is non-zero only where few output tiles meet a long
- *            K (K is then cut into slices whose float32 partial tiles are summed
- *            in fixed order by a second kernel).  NULL is always accepted: the
- *            call then runs without the split (same result within tolerance).
+ *            K (K may then be cut into slices whose float32 partial tiles are
+ *            summed in fixed order by a second kernel; the query knows neither G
+ *            nor r, so it also answers for calls that end up unsplit).  NULL is
+ *            always accepted: the call then runs without the split (same result
+ *            within tolerance).
  *   workspace_bytes  size of what `workspace` points to.  A non-NULL workspace
  *            smaller than the query's answer is refused (ZQFP_E_WORKSPACE) and
  *            nothing is enqueued.

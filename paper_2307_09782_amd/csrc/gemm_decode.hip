@@ -357,13 +357,13 @@ bool gemm_decode_supported(int64_t M, const BlobLayout& L, const void* workspace
     if (L.nkt <= 64) return true;
     if (plan_decode(L.nkt).chunks > compute_units()) return false;  // every chunk needs a workgroup of its own
     // longer K: in chunks through the workspace, if there are strips enough to give every workgroup
-    // several (below that the streaming kernel, one launch and no prologue per chunk, is faster)
+    // several (below that the form for a few dozen tokens, one launch and no prologue per chunk, is faster)
     return workspace != nullptr && L.nstrips * plan_decode(L.nkt).chunks >= 1024;
 }
 
 // E4M3 weights, at most 16 tokens and 40 k-tiles: a fragment is twice the registers of an FP4 one, so a wave holds at
 // most five k-tiles (with two fragment buffers) before it spills, and there are no chunks (the W8A8 entry point takes
-// no workspace).  Longer K stays with the streaming kernel.
+// no workspace).  Longer K goes to the form for a few dozen tokens or to the streaming kernel (gemm_mid_wins).
 bool gemm_w8_decode_supported(int64_t M, const BlobLayout& L) { return M >= 1 && M <= 16 && L.nkt <= 40 && L.N >= 16; }
 
 hipError_t launch_gemm_w8_decode(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob, const BlobLayout& L,

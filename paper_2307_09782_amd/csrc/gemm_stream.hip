@@ -1,6 +1,6 @@
-// W8A8 GEMM, weight-streaming form for small token counts where no other kernel is the better one: at most 8 tokens with
-// two strips per compute unit and long K, or 17 to 32 tokens with K below 2048.  Bound by reading the packed E4M3
-// weights once from HBM.
+// W8A8 GEMM, weight-streaming form for small token counts where no other kernel is the better one: at most 11 tokens with
+// two strips per compute unit (or more than three) and K beyond 5120, or 17 to 32 tokens with a strip per compute unit and short K
+// (gemm_mid_wins has the lines).  Bound by reading the packed E4M3 weights once from HBM.
 //
 //   Y[m,n] = (sx[m] c[n]) * sum_k a[m,k] * q[k,n] * 2^e[g(k),n]   (+ T.V, LoRC)
 //

@@ -224,11 +224,11 @@ def _gemm_case(M, K, N, G, mode, r=0, seed_cfg="tiny", full=True, nsamples=4096,
     (64, 2048, 200, 256, 2, 8),     # 64 x 128 tiles, 16 k-steps, groups of 256, LoRC staged in LDS
     (48, 128, 64, 32, 1, 2),        # a single k-step (no load pipeline to speak of), groups of 32
     (130, 256, 300, 64, 2, 0),      # two k-steps, groups of 64
-    (20, 8320, 48, 128, 1, 0),      # N < 64: streaming fallback
-    (64, 4096, 128, 128, 1, 8),     # one 64 x 128 tile, long K: K split 4 ways through the workspace, LoRC in the reduce
-    (100, 3072, 136, 128, 1, 3),    # 4 tiles, K split 3 ways, ragged M and N
-    (33, 11008, 256, 128, 2, 0),    # a down-projection's K (86 k-tiles): uneven slices
-    (16, 11008, 96, 128, 1, 8),     # M <= 16 beyond 64 k-tiles, few strips: streaming fallback with LoRC
+    (20, 8320, 48, 128, 1, 0),      # N < 64: no tile of that width
+    (64, 4096, 128, 128, 1, 8),     # few channels, long K, with a workspace that goes unused
+    (100, 3072, 136, 128, 1, 3),    # the same, ragged M and N
+    (33, 11008, 256, 128, 2, 0),    # a down-projection's K (86 k-tiles): uneven K slices of tiles
+    (16, 11008, 96, 128, 1, 8),     # M <= 16 beyond 64 k-tiles, few strips: K in one piece, with LoRC
     (3, 8320, 80, 64, 2, 0),        # the same with 65 k-tiles, groups of 64
     (9, 28672, 48, 128, 1, 0),      # the same with 224 k-tiles
     # decode form with a workgroup count that is a multiple of 8 (strips handed out in pairs per XCD):
@@ -261,10 +261,11 @@ def _check_bf16(Y, Y_o, Sabs, what):
     (5, 512, 1664, 128, 2, 0),      # decode form, strips in pairs, column scales
     (7, 512, 48, 128, 2, 16),       # decode form, LoRC read in place
     (16, 8192, 80, 128, 1, 8),      # decode form, upper band in LDS
-    (20, 8320, 48, 128, 1, 0),      # streaming fallback
-    (16, 11008, 96, 128, 1, 8),     # streaming fallback for at most 16 tokens, LoRC
-    (64, 4096, 128, 128, 1, 8),     # K split through the workspace: the reduce kernel stores
-    (100, 3072, 136, 128, 2, 3),    # K split 3 ways, ragged M and N
+    (20, 8320, 48, 128, 1, 0),      # N < 64
+    (16, 11008, 96, 128, 1, 8),     # at most 16 tokens beyond 64 k-tiles, few strips, LoRC
+    (33, 11008, 256, 128, 1, 8),    # K split through the workspace: the reduce kernel stores
+    (64, 4096, 128, 128, 1, 8),     # few channels, long K
+    (100, 3072, 136, 128, 2, 3),    # the same, ragged M and N
     (64, 1024, 272, 128, 1, 8),     # 64 x 128 tiles, two wave groups
     (200, 1280, 400, 256, 2, 0),    # 64 x 128 tiles, several each way
 ])
@@ -656,8 +657,8 @@ def test_fused_layernorm_quantizer_argument_checks():
 
 
 def test_gemm_k_split_is_optional_and_agrees_with_the_unsplit_launch():
-    """Without a workspace the same call runs un-split; both results meet the parity bar and the
-    workspace query names a size exactly when a split is planned."""
+    """With and without a workspace the results meet the parity bar, and the workspace query names a size exactly when
+    the tiled form would plan a split (the split itself: test_gpu_gemm_forms.py)."""
     M, K, N, G = 64, 4096, 128, 128
     assert zqfp.gemm_workspace_bytes(M, K, N) == 4 * M * N * 4
     assert zqfp.gemm_workspace_bytes(4096, 4096, 12288) == 0 and zqfp.gemm_workspace_bytes(16, 8192, 28672) == 0
@@ -672,7 +673,7 @@ def test_gemm_k_split_is_optional_and_agrees_with_the_unsplit_launch():
     Y_plain = _sync_np(zqfp.w4a8_gemm(Xq, sx, packed, N, G, workspace=False))
     check_gemm(Y_split, Y_o, Sabs, "K split")
     check_gemm(Y_plain, Y_o, Sabs, "no workspace")
-    # M <= 16 beyond 64 k-tiles: a workspace is named; with few strips both calls take the streaming kernel
+    # M <= 16 beyond 64 k-tiles: a workspace is named; with few strips both calls take K in one piece
     assert zqfp.gemm_workspace_bytes(8, 8320, 128) == 2 * 8 * 128 * 4
     Yd = _sync_np(zqfp.w4a8_gemm(Xq[:8].contiguous(), sx[:8].contiguous(), packed, N, G))
     Yd0 = _sync_np(zqfp.w4a8_gemm(Xq[:8].contiguous(), sx[:8].contiguous(), packed, N, G,
@@ -714,20 +715,22 @@ def test_binding_and_library_refuse_mismatched_blob_workspace_and_output():
     assert torch.equal(Y, zqfp.w4a8_gemm(Xq, sx, packed, N, G))
 
 
-@pytest.mark.parametrize("M,K,N,G,mode,r", [(16, 8320, 8192, 64, 2, 8),     # 65 k-tiles: chunks of 33 and 32
-                                            (5, 16640, 5504, 128, 1, 0),    # 130 k-tiles: three chunks of 44, 44, 42
-                                            (7, 14080, 8192, 128, 1, 8)])   # 110 k-tiles: two chunks of 55
+@pytest.mark.parametrize("M,K,N,G,mode,r", [(16, 8320, 8192, 64, 2, 8),     # 65 k-tiles
+                                            (5, 16640, 5504, 128, 1, 0),    # 130 k-tiles
+                                            (7, 14080, 8192, 128, 1, 8),    # 110 k-tiles
+                                            (16, 8320, 12304, 64, 2, 8)])   # 65 k-tiles in chunks of 33 and 32
 def test_gemm_decode_long_k_in_chunks(M, K, N, G, mode, r):
-    """Decode form with more than 64 k-tiles and strips enough for the chunked path (partial sums
-    through the workspace, scales and LoRC in the reduce kernel); sampled outputs."""
+    """At most 16 tokens with more than 64 k-tiles, sampled outputs: in one piece up to three strips per compute unit, with
+    more in chunks whose partial sums go through the workspace."""
+    assert zqfp.probe_gemm_form(M, K, N, G, r=r) == (zqfp.FORM_DECODE if N > 12288 else zqfp.FORM_MID)
     assert zqfp.gemm_workspace_bytes(M, K, N) == -(-K // 128 // 64) * M * N * 4
     Y, Y_o, Sabs = _gemm_case(M, K, N, G, mode, r, seed_cfg="llama70b_ffn_decode", full=False, nsamples=2048)
     check_gemm(Y, Y_o, Sabs, f"decode chunks M{M} K{K} N{N}")
 
 
 def test_gemm_seeded_sweep_of_small_shapes():
-    """Forty seeded random shapes across every dispatch branch (decode form, chunked K, streaming
-    fallback, the three tile shapes' smallest members, K split), each compared in full with the oracle."""
+    """Forty seeded random small shapes, by whichever kernel serves them (most are the form for a few dozen tokens;
+    test_gpu_gemm_forms.py names the kernel of each of its shapes), each compared in full with the oracle."""
     rng = np.random.default_rng(20230719)
     done = 0
     while done < 40:
