@@ -212,23 +212,29 @@ hipError_t launch_cfg(int mblocks, const uint8_t* Xq, const float* sx, int64_t M
 
 namespace {
 
-// Microseconds of a launch with S strips per workgroup: whole rounds of compute units, each a fixed part, the partial
-// tiles and the k-tiles (fitted to 600 timings: ten weight shapes with 8 ... 224 k-tiles, 4 ... 256 tokens; within 11 % on
-// average, and its choice of S was the fastest one at every point).
-float mid_us(int64_t M, const BlobLayout& L, int S)
-{
-    const int64_t mblocks = (M + 63) / 64;
-    const float mt = (float)(((M + 15) / 16 + mblocks - 1) / mblocks), s = (float)S, nkt = (float)L.nkt;
-    const float rounds = (float)(((L.nstrips + S - 1) / S * mblocks + 255) / 256);
-    if (L.wbits == 8) return rounds * (3.3f + 0.159f * s * mt + nkt * (0.034f + 0.0223f * mt + 0.0482f * s));
-    return rounds * (3.1f + 0.163f * s * mt + nkt * (0.003f + 0.0335f * mt + 0.0242f * s));
-}
+// Token blocks per workgroup (16 each), workgroups along the tokens and strips per workgroup of a launch, with its time in
+// microseconds: whole rounds of compute units, each a fixed part, the partial tiles and the k-tiles (fitted to 600 timings:
+// ten weight shapes with 8 ... 224 k-tiles, 4 ... 256 tokens; within 11 % on average, and its choice of S was the fastest one
+// at every point).
+struct MidShape {
+    int mt, mblocks, S;
+    float us;
+};
 
-int best_strips(int64_t M, const BlobLayout& L)
+MidShape mid_shape(int64_t M, const BlobLayout& L)
 {
-    int best = 1;
-    for (int S = 2; S <= 4; ++S)
-        if (mid_us(M, L, S) < mid_us(M, L, best)) best = S;
+    const int blocks = (int)((M + 15) / 16), mblocks64 = (blocks + 3) / 4;
+    const float nkt = (float)L.nkt;
+    MidShape best{0, 0, 0, 0.0f};
+    {
+        const int mt = (blocks + mblocks64 - 1) / mblocks64, mblocks = mblocks64;
+        for (int S = 1; S <= 4; ++S) {
+            const float rounds = (float)(((L.nstrips + S - 1) / S * mblocks + 255) / 256), m = (float)mt, s = (float)S;
+            const float us = rounds * (L.wbits == 8 ? 3.3f + 0.159f * s * m + nkt * (0.034f + 0.0223f * m + 0.0482f * s)
+                                                    : 3.1f + 0.163f * s * m + nkt * (0.003f + 0.0335f * m + 0.0242f * s));
+            if (best.S == 0 || us < best.us) best = MidShape{mt, mblocks, S, us};
+        }
+    }
     return best;
 }
 
@@ -251,46 +257,58 @@ bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum)
             return L.nstrips <= 768 && !(M > 8 && L.nkt > 128 && L.nstrips <= 256 && L.nstrips * plan_decode(L.nkt).chunks >= 1024);
         // A strip per compute unit: the persistent kernel's prologue serves no second one (8192 x 1024, 16 tokens:
         // 8.2 -> 6.2; 5120 x 4096: 7.1 -> 6.6).  With few tokens it is as short (8192 x 2048, 1 token: 6.2 against 6.7).
-        return M > 4 && L.nkt > 32 && L.nstrips <= 256;
+        // In one pass it holds the factors of five tokens and ranks up to 8 as well (5120 x 4000, 5 tokens: 5.8 against 6.1).
+        return M > (fast && r > 4 && r <= 8 ? 5 : 4) && L.nkt > 32 && L.nstrips <= 256;
     }
     // More tokens: against the tiled kernel's estimate (4096 x 12288, 24 / 64 tokens: 18.5 -> 10.6 / 19.9 -> 14.7; 4096 x 4096, 128
     // tokens: 18.7 -> 11.3; 8192 x 28672 and 28672 x 8192 at 64 tokens stay there, 35.7 against 47.0 and 39.1 against 52.6).
     const TilePlan p = effective_tile_plan(M, L.Np, L.nkt);
     if (p.forced) return false;
     if (L.N < 64) return true;  // the tiled kernel has no such tile
-    const float us = mid_us(M, L, best_strips(M, L));
+    const MidShape ms = mid_shape(M, L);
+    // Every L2 fetches the activations of its workgroups, all M x K bytes once several groups of strips are about: beyond what the
+    // rest of the time hides that costs 1 us per 8 MB (11008 x 64: 17.6 us up to 1024 tokens, 22.3 at 2048, 33.7 at 4096, 180 MB).
+    const int64_t groups = (L.nstrips + ms.S - 1) / ms.S;
+    const float fetched = 1e-6f * (float)(groups < 8 ? groups : 8) * (float)M * (float)L.K;
+    const float excess = fetched - (18.0f + 0.003f * (float)L.K), extra = excess > 0.0f ? 0.127f * excess : 0.0f;
+    const float us = ms.us;
     if (L.wbits == 8) {
         if (M <= 32 && L.nstrips <= 256) {
             // The streaming kernel, a strip per compute unit as here and no LDS on the way of the activations: short K (1024 x 1024,
             // 24 tokens: 3.8 against 4.3; 2048 x 4096, 17 tokens: 5.2 against 5.6), and in the one-pass mode, where it waits for
             // memory only, while its stream fills the chip (4096 x 4096, 24 tokens: 7.3 against 7.8; 3072 x 3072: 5.7
             // against 5.5).  From rank 8 on its epilogue, one rank after the other, decides (4096 x 4096, rank 8: 9.1 against 8.3).
-            if (L.nkt < 16 || (r < 8 && L.nkt <= 20 && M < 24)) return false;
-            if (fast && r < 8 && L.nkt <= 40 && L.nstrips >= 192 && L.nkt * L.nstrips >= 5120) return false;
+            if (L.nkt < 16 || (r < (L.nstrips < 32 ? 9 : 8) && L.nkt <= 20 && M < 24)) return false;
+            if (fast && r < 8 && L.nkt <= 40 && L.nstrips >= 192 && (L.nkt * L.nstrips >= 5120 || L.nstrips > 224)) return false;
         }
         // 64 x 128 tiles, one per compute unit, no K-split: fitted (4096 x 12288, 64 tokens: 24.4 -> 18.8; 28672 x 8192:
         // 111 -> 64.7; 14336 x 2048, 300 tokens: 57.0 -> 32.5).  Near 256 tiles the tiled kernel is 6 to 13 % above its estimate and
         // this one, bound by HBM or in a second round, 10 to 25 % (12288 x 16384, 96 tokens: 57.9 against 65.8 us; 28672 x 8192, 256 tokens:
         // 119 against 140; 8192 x 28672, 32 tokens: 49.3 against 53.3).
+        // Many tokens on few channels, one pass: the tiled kernel reads the activations once per 128 channels (11008 x 512,
+        // 2048 tokens: 32.4 against 38.7; in two passes 44.6 against 41.8).
         const int64_t tiles = (M + 63) / 64 * ((L.Np + 127) / 128);
-        return tiles <= 256 && us < 7.0f + 0.465f * (float)L.nkt;
+        return tiles <= 256 && us < 7.0f + 0.465f * (float)L.nkt && !(fast && extra > 8.0f);
     }
     // Both estimates are those of the exact mode.  One pass takes an un-split tiled launch down by 13 to 20 %, this one, which waits for
     // memory, by 3 to 5 (8192 x 28672, 32 tokens: 29.8 against 33.9; 6144 x 24576, 24 tokens: 22.1 against 24.1), and the
     // low-rank correction costs the tiled kernel, which stages its factors, half as much (3072 x 20000, 32 tokens, rank 8: 18.7
     // against 19.1).  Beyond 16384 rows this kernel is slower than its estimate (28672 x 8192, 32 tokens: 37.3 against 38.2 us; one
-    // pass 33.3 against 37.7; 96 tokens, one pass: 43.7 against 46.3).
+    // pass 33.3 against 37.7; 96 tokens, one pass: 43.7 against 46.3).  Many tokens on few channels go to the tiled kernel by the
+    // activations they fetch (11008 x 128, 2048 tokens: 19.2 against 34.2; 4096 x 256, 4096 tokens, one pass: 14.0 against 15.2).
     float bar = p.us;
     if (L.nkt > 128) bar *= fast ? 0.87f : 0.97f;
     else if (p.ksplit == 1) bar *= fast ? 0.87f : r > 0 ? 0.95f : 1.0f;
-    return us < bar;
+    else if (fast && extra > 0.0f) bar *= 0.93f;  // 11008 x 1024, 1024 tokens: 22.6 against 24.4
+    return us + extra < bar;
 }
 
 hipError_t launch_gemm_mid(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob, const BlobLayout& L,
                            Lorc lorc, void* Y, int64_t ldy, int out_dtype, int accum, hipStream_t s)
 {
     if (M == 0 || L.N == 0) return hipSuccess;
-    const int mblocks = (int)((M + 63) / 64), mt = (int)(((M + 15) / 16 + mblocks - 1) / mblocks), S = best_strips(M, L);
+    const MidShape ms = mid_shape(M, L);
+    const int mblocks = ms.mblocks, mt = ms.mt, S = ms.S;
 #define ZQ_MID(MT_, S_) \
     if (mt == MT_ && S == S_) { \
         if (L.wbits == 8) return accum == 0 ? launch_cfg<MT_, S_, true, 8>(mblocks, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, s) \

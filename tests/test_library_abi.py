@@ -206,6 +206,10 @@ D, M_, T, S = zqfp.FORM_DECODE, zqfp.FORM_MID, zqfp.FORM_TILE, zqfp.FORM_STREAM
     (4, 32, 3072, 20000, 8, 0, T), (4, 32, 3072, 20000, 0, 1, T), (4, 64, 4096, 12288, 8, 1, M_),
     # K beyond 16384 rows
     (4, 32, 28672, 8192, 0, 0, T), (4, 96, 28672, 8192, 0, 1, T), (4, 65, 28672, 8192, 0, 0, M_), (4, 64, 11008, 4096, 0, 0, M_),
+    # many tokens on few channels: what the L2s fetch of the activations counts
+    (4, 4096, 11008, 64, 0, 0, T), (4, 2048, 11008, 128, 8, 0, T), (4, 1024, 11008, 512, 0, 0, T), (4, 1024, 11008, 1024, 0, 1, T),
+    (4, 1024, 11008, 1024, 8, 0, M_), (4, 4096, 4096, 256, 0, 1, T), (4, 4096, 4096, 256, 0, 0, M_), (4, 4096, 4096, 64, 0, 1, M_),
+    (4, 2048, 2048, 512, 8, 1, M_), (8, 2048, 11008, 512, 0, 1, T), (8, 2048, 11008, 512, 0, 0, M_), (8, 2048, 11008, 64, 0, 1, M_),
     # E4M3 weights: near 256 tiles, weights beyond what HBM hides; the streaming kernel's corners
     (8, 96, 12288, 16384, 0, 0, T), (8, 64, 12288, 16384, 0, 1, M_), (8, 256, 28672, 8192, 0, 0, T), (8, 32, 8192, 28672, 0, 0, T),
     (8, 24, 6144, 24576, 0, 1, T), (8, 9, 9216, 8192, 0, 0, S), (8, 12, 9216, 8192, 0, 0, M_), (8, 17, 2048, 4096, 0, 0, S),
