@@ -116,17 +116,25 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
         }
     };
 
-    // k-tiles wave, wave + 8, ...; the loop is unrolled by NB so that the buffers are addressed statically
+    // k-tiles wave, wave + 8, ...; the loop is unrolled by NB so that the buffers are addressed statically.  At most one of them
+    // (K up to 1024): nothing to run ahead of, and nothing but it is loaded (1024 x 16, 17 tokens: 3.39 -> 2.85 us).
+    if (nkt - wave <= kWaves) {
+        if (wave < nkt) {
+            issue(0, wave);
+            multiply(0);
+        }
+    } else {
 #pragma unroll
-    for (int i = 0; i < NB; ++i) issue(i, wave + kWaves * i);
-    for (int kt = wave; kt < nkt;) {
+        for (int i = 0; i < NB; ++i) issue(i, wave + kWaves * i);
+        for (int kt = wave; kt < nkt;) {
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            multiply(i);
-            issue(i, kt + kWaves * NB);
-            __builtin_amdgcn_sched_barrier(0);
-            kt += kWaves;
-            if (kt >= nkt) break;
+            for (int i = 0; i < NB; ++i) {
+                multiply(i);
+                issue(i, kt + kWaves * NB);
+                __builtin_amdgcn_sched_barrier(0);
+                kt += kWaves;
+                if (kt >= nkt) break;
+            }
         }
     }
 
@@ -226,14 +234,17 @@ MidShape mid_shape(int64_t M, const BlobLayout& L)
     const int blocks = (int)((M + 15) / 16), mblocks64 = (blocks + 3) / 4;
     const float nkt = (float)L.nkt;
     MidShape best{0, 0, 0, 0.0f};
-    {
-        const int mt = (blocks + mblocks64 - 1) / mblocks64, mblocks = mblocks64;
+    // Up to 64 tokens each, except where a few strips are all there is: then fewer, so that more workgroups start at once
+    // (512 x 48, 300 tokens: 4.24 -> 2.94 us; 4096 tokens: 4.51 -> 3.40).
+    for (int mt = L.N < 64 ? 1 : (blocks + mblocks64 - 1) / mblocks64; mt <= 4; ++mt) {
+        const int mblocks = (blocks + mt - 1) / mt;
         for (int S = 1; S <= 4; ++S) {
             const float rounds = (float)(((L.nstrips + S - 1) / S * mblocks + 255) / 256), m = (float)mt, s = (float)S;
             const float us = rounds * (L.wbits == 8 ? 3.3f + 0.159f * s * m + nkt * (0.034f + 0.0223f * m + 0.0482f * s)
                                                     : 3.1f + 0.163f * s * m + nkt * (0.003f + 0.0335f * m + 0.0242f * s));
             if (best.S == 0 || us < best.us) best = MidShape{mt, mblocks, S, us};
         }
+        if (L.N >= 64) break;
     }
     return best;
 }
@@ -264,7 +275,6 @@ bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum)
     // tokens: 18.7 -> 11.3; 8192 x 28672 and 28672 x 8192 at 64 tokens stay there, 35.7 against 47.0 and 39.1 against 52.6).
     const TilePlan p = effective_tile_plan(M, L.Np, L.nkt);
     if (p.forced) return false;
-    if (L.N < 64) return true;  // the tiled kernel has no such tile
     const MidShape ms = mid_shape(M, L);
     // Every L2 fetches the activations of its workgroups, all M x K bytes once several groups of strips are about: beyond what the
     // rest of the time hides that costs 1 us per 8 MB (11008 x 64: 17.6 us up to 1024 tokens, 22.3 at 2048, 33.7 at 4096, 180 MB).
@@ -281,6 +291,7 @@ bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum)
             if (L.nkt < 16 || (r < (L.nstrips < 32 ? 9 : 8) && L.nkt <= 20 && M < 24)) return false;
             if (fast && r < 8 && L.nkt <= 40 && L.nstrips >= 192 && (L.nkt * L.nstrips >= 5120 || L.nstrips > 224)) return false;
         }
+        if (L.N < 64) return true;  // the tiled kernel has no such tile
         // 64 x 128 tiles, one per compute unit, no K-split: fitted (4096 x 12288, 64 tokens: 24.4 -> 18.8; 28672 x 8192:
         // 111 -> 64.7; 14336 x 2048, 300 tokens: 57.0 -> 32.5).  Near 256 tiles the tiled kernel is 6 to 13 % above its estimate and
         // this one, bound by HBM or in a second round, 10 to 25 % (12288 x 16384, 96 tokens: 57.9 against 65.8 us; 28672 x 8192, 256 tokens:
@@ -290,6 +301,7 @@ bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum)
         const int64_t tiles = (M + 63) / 64 * ((L.Np + 127) / 128);
         return tiles <= 256 && us < 7.0f + 0.465f * (float)L.nkt && !(fast && extra > 8.0f);
     }
+    if (L.N < 64) return true;
     // Both estimates are those of the exact mode.  One pass takes an un-split tiled launch down by 13 to 20 %, this one, which waits for
     // memory, by 3 to 5 (8192 x 28672, 32 tokens: 29.8 against 33.9; 6144 x 24576, 24 tokens: 22.1 against 24.1), and the
     // low-rank correction costs the tiled kernel, which stages its factors, half as much (3072 x 20000, 32 tokens, rank 8: 18.7

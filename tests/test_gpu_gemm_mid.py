@@ -63,6 +63,14 @@ def test_ragged_k_groups_and_ranks(M, K, N, G, mode, r, wbits):
     _check(M, K, N, G, mode, r, wbits, torch.bfloat16, zqfp.ACCUM_FAST)
 
 
+# fewer than 64 channels: 16 to 64 tokens per workgroup, whichever starts the most at once, ragged at both ends
+@pytest.mark.parametrize("wbits", [4, 8])
+@pytest.mark.parametrize("M,K,N,r", [(300, 512, 16, 0), (257, 512, 48, 8), (4100, 640, 48, 0), (1023, 2176, 33, 3), (5000, 384, 63, 0)])
+def test_many_tokens_on_a_few_channels(M, K, N, r, wbits):
+    assert zqfp.probe_gemm_form(M, K, N, 128, wbits, r) == zqfp.FORM_MID
+    _check(M, K, N, 128, 1, r, wbits)
+
+
 @pytest.mark.parametrize("G", [32, 64])
 def test_several_groups_per_k_tile(G):
     _check(50, 1408, 600, G, 1, 0, 4)
