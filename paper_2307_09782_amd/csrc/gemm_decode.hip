@@ -40,7 +40,8 @@ struct FusedIn {
 
 // WB: weight bits.  8 = E4M3 weights (the W8A8 rows of the paper's Table 2 with FP8 on both sides): a strip's
 // k-tile is then two 1 KB halves, the first and second four registers of the B operand.
-template <int NW, int KPW, int NB, bool EXACT, bool LR, bool FUSED = false, int WB = 4>
+// LR: no LoRC (0), ranks up to 8 (1), up to 64 (2).
+template <int NW, int KPW, int NB, bool EXACT, int LR, bool FUSED = false, int WB = 4>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void k_gemm_decode(
     const uint8_t* __restrict__ Xq, const float* __restrict__ sx, int M, const uint8_t* __restrict__ blob, BlobLayout L,
     Lorc lorc, void* __restrict__ Y, int64_t ldy, int out_dtype, int nchunks, int chunk_len, float* __restrict__ partial,
@@ -48,8 +49,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 {
     constexpr int kWaves = NW;
     constexpr bool HI_LDS = EXACT && KPW >= 8;
-    static_assert(!FUSED || (KPW <= 4 && !LR), "the fused form keeps a wave's bfloat16 slices in registers and has no LoRC");
+    static_assert(!FUSED || (KPW <= 4 && LR == 0), "the fused form keeps a wave's bfloat16 slices in registers and has no LoRC");
     __shared__ float s_red[2][kWaves][64][4];
+    constexpr int LR_SLOTS = LR == 0 ? 0 : LR == 1 ? 2 : NW;                  // waves that hold ranks, four at a time
+    constexpr int LR_STEPS = LR == 2 ? (64 / 4 + NW - 1) / NW : LR;           // and how many times
+    __shared__ float s_lr[LR ? 2 : 1][LR ? LR_SLOTS : 1][64][4];  // their shares of T . V
     __shared__ uint32_t s_rowmax[FUSED ? kWaves : 1][16];
     __shared__ float s_scale[FUSED ? 16 : 1];
     extern __shared__ __attribute__((aligned(16))) uint8_t s_hi[];  // HI_LDS: NW * KPW * 2048 bytes
@@ -120,26 +124,35 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
     // the reduction and the store.  Every load of the loop is unconditional (addresses are clamped
     // into valid memory instead) and its value is left raw until it is used: the load counter can
     // then be waited on exactly, and a strip's operands never wait for the next strip's.
-    constexpr int RMAX = 8;  // LoRC ranks up to 8 are held in registers, larger ones are read in place
     const int er = (tid >> 4) & 15, ec = tid & 15;
     const bool row_live = tid < 256 && er < M;
-    const int rk = lorc.r;
-    float sx_r = (raw || FUSED) ? 1.0f : sx[min(er, M - 1)], t_r[RMAX];  // raw: scales are applied when the chunks are added up; FUSED: set below
-#pragma unroll
-    for (int j = 0; j < RMAX; ++j) t_r[j] = 0.f;
-    if constexpr (LR) {
-#pragma unroll
-        for (int j = 0; j < RMAX; ++j) t_r[j] = lorc.T[min(er, M - 1) * rk + min(j, rk - 1)];  // j >= rk: unused
-    }
+    float sx_r = (raw || FUSED) ? 1.0f : sx[min(er, M - 1)];  // raw: scales are applied when the chunks are added up; FUSED: set below
     float cs[NB];
-    uint32_t vv[NB][RMAX];  // binary16 bits
+    // LoRC on the float32 matrix cores, four ranks an instruction: wave w takes the ranks 4 w + [0, 4) (and 4 (w + 8) + [0, 4)),
+    // so that its operands are one or two values a lane: T stays in registers, V travels with the strip.  The shares meet in
+    // LDS beside the strip's partial tiles and are added to the scaled sum.  Ranks past r are zero on both sides.  Loads in
+    // place behind the reduction, which ranks above 8 had, were most of a call (16 x 8192 x 28672: rank 16 50.0 -> 28.4 us, rank
+    // 40 86.6 -> 28.2; 7 x 4992 x 24826, rank 40: 77.6 -> 17.5), eight values of T and V a thread for ranks up to 8 a few percent
+    // (1 x 8192 x 19200, rank 8: 19.0 -> 18.2; 4 x 2304 x 2304: 5.3 -> 4.65).
+    const int rk = lorc.r;
+    float t_f[LR ? LR_STEPS : 1];
+    uint32_t v_f[LR ? NB : 1][LR ? LR_STEPS : 1];  // binary16 bits
+    if constexpr (LR != 0) {
 #pragma unroll
-    for (int r = 0; r < NB; ++r)
-#pragma unroll
-        for (int j = 0; j < RMAX; ++j) vv[r][j] = 0u;
+        for (int i = 0; i < LR_STEPS; ++i) {
+            const int q = 4 * (wave + kWaves * i) + lb;
+            const float t = lorc.T[min(col, M - 1) * rk + min(q, rk - 1)];
+            t_f[i] = q < rk ? t : 0.f;
+        }
+    }
 
     auto issue = [&](int buf, int64_t strip_unclamped) {
         const int64_t strip = min(strip_unclamped, nstrips - 1);  // past the end: the last strip again, never used
+        if constexpr (LR != 0) {
+            const int64_t nf = min(strip * 16 + col, L.N - 1);
+#pragma unroll
+            for (int i = 0; i < LR_STEPS; ++i) v_f[buf][i] = lorc.V[(int64_t)min(4 * (wave + kWaves * i) + lb, rk - 1) * L.N + nf];
+        }
 #pragma unroll
         for (int u = 0; u < KPW; ++u) {
             const int kt = min(wave + kWaves * u, nkt - 1);  // clamped duplicates are multiplied by zero fragments
@@ -154,12 +167,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
         }
         const int64_t n = min(strip * 16 + ec, L.N - 1);
         cs[buf] = colscale[n];
-        if constexpr (LR) {
-#pragma unroll
-            for (int j = 0; j < RMAX; ++j) vv[buf][j] = lorc.V[(int64_t)min(j, rk - 1) * L.N + n];
-        }
     };
     auto finish = [&](int buf, int64_t strip, int par) {
+        if constexpr (LR != 0) {
+            v4f tv = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < LR_STEPS; ++i) {
+                const float v = 4 * (wave + kWaves * i) + lb < rk ? half_bits_to_f32((uint16_t)v_f[buf][i]) : 0.f;
+                tv = __builtin_amdgcn_mfma_f32_16x16x4f32(t_f[i], v, tv, 0, 0, 0);
+            }
+            if (wave < LR_SLOTS) *reinterpret_cast<v4f*>(&s_lr[par][wave][lane][0]) = tv;
+            // ahead of the strip's own instructions: among or behind them it makes the compiler read the fragments of all eight
+            // k-tiles at once and spill (16 x 8192 x 28672, rank 8: 44 us)
+            __builtin_amdgcn_sched_barrier(0);
+        }
         // independent accumulator chains (two; four in the exact mode, one pair per exponent band):
         // a matrix instruction that waits for the previous one's result costs its full latency
         v4f acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f}, acc3 = {0.f, 0.f, 0.f, 0.f};
@@ -200,14 +221,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) a += s_red[par][w][src][reg];
         float y = (sx_r * (raw ? 1.0f : cs[buf])) * a;
-        if constexpr (LR) {
+        if constexpr (LR != 0) {
+            float tv = 0.f;
 #pragma unroll
-            for (int j = 0; j < RMAX; ++j) y = fmaf(t_r[j], j < rk ? half_bits_to_f32((uint16_t)vv[buf][j]) : 0.f, y);
+            for (int w = 0; w < LR_SLOTS; ++w) tv += s_lr[par][w][src][reg];
+            y += tv;
         }
         if (row_live && n < L.N) {
-            if (!LR && rk > 0)  // ranks not held in registers: read in place
-                for (int j = 0; j < rk; ++j)
-                    y = fmaf(lorc.T[er * rk + j], half_bits_to_f32(lorc.V[(int64_t)j * L.N + n]), y);
             if (out_dtype == 0) reinterpret_cast<float*>(Y)[er * ldy + n] = y;
             else reinterpret_cast<uint16_t*>(Y)[er * ldy + n] = f32_to_bf16_bits(y);
         }
@@ -301,19 +321,20 @@ hipError_t launch_kpw(unsigned grid, bool exact, const uint8_t* Xq, const float*
                 const BlobLayout& L, Lorc lorc, void* Y, int64_t ldy, int out_dtype, int nchunks, int chunk_len,
                 float* partial, const FusedIn& fin, hipStream_t s)
 {
-    // LoRC operands of ranks up to 8 are held in registers
-    const bool lr = lorc.r > 0 && lorc.r <= 8;
+    const int lr = lorc.r == 0 ? 0 : lorc.r <= 8 ? 1 : 2;
     // the exact mode with 8 k-tiles per wave keeps the upper-band fragments in LDS (above the 64 KB
     // default limit of dynamic LDS, which is a per-function setting)
     const size_t smem = (exact && KPW >= 8) ? (size_t)NW * KPW * 2048 : 0;
     if (smem > 0) {
         static OnceStatus raised;
         if (hipError_t e = run_once(raised, [&] {
-                hipError_t e1 = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_decode<NW, KPW, NB, true, false, false, WB>),
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-                if (e1 != hipSuccess) return e1;
-                return hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_decode<NW, KPW, NB, true, true, false, WB>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                const void* kerns[] = {reinterpret_cast<const void*>(k_gemm_decode<NW, KPW, NB, true, 0, false, WB>),
+                                       reinterpret_cast<const void*>(k_gemm_decode<NW, KPW, NB, true, 1, false, WB>),
+                                       reinterpret_cast<const void*>(k_gemm_decode<NW, KPW, NB, true, 2, false, WB>)};
+                for (const void* k : kerns)
+                    if (hipError_t e1 = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); e1 != hipSuccess)
+                        return e1;
+                return hipSuccess;
             }); e != hipSuccess)
             return e;
     }
@@ -321,12 +342,19 @@ hipError_t launch_kpw(unsigned grid, bool exact, const uint8_t* Xq, const float*
     hipLaunchKernelGGL((k_gemm_decode<NW, KPW, NB, EX, LR, FU, WB>), dim3(grid), dim3(64 * NW), smem, s, Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, nchunks, chunk_len, partial, fin)
     if (fin.X != nullptr) {
         if constexpr (KPW <= 4 && WB == 4) {
-            if (exact) ZQ_LAUNCH(true, false, true); else ZQ_LAUNCH(false, false, true);
+            if (exact) ZQ_LAUNCH(true, 0, true); else ZQ_LAUNCH(false, 0, true);
         } else {
             return hipErrorInvalidValue;  // not reached: the caller checks gemm_decode_fused_supported
         }
-    } else if (exact) { if (lr) ZQ_LAUNCH(true, true, false); else ZQ_LAUNCH(true, false, false); }
-    else       { if (lr) ZQ_LAUNCH(false, true, false); else ZQ_LAUNCH(false, false, false); }
+    } else if (exact) {
+        if (lr == 0) ZQ_LAUNCH(true, 0, false);
+        else if (lr == 1) ZQ_LAUNCH(true, 1, false);
+        else ZQ_LAUNCH(true, 2, false);
+    } else {
+        if (lr == 0) ZQ_LAUNCH(false, 0, false);
+        else if (lr == 1) ZQ_LAUNCH(false, 1, false);
+        else ZQ_LAUNCH(false, 2, false);
+    }
 #undef ZQ_LAUNCH
     return hipGetLastError();
 }

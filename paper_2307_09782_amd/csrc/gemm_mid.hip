@@ -259,8 +259,9 @@ bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum)
         // E4M3 weights: K beyond the registers of the persistent kernel, which left it to the streaming one (11008 x 4096,
         // 16 tokens: 15.2 -> 13.7; 16384 x 12288, 1 token: 45.1 -> 40.5).  Up to 11 tokens and two strips per compute
         // unit: two of the streaming kernel's workgroups share a unit and are ahead (9216 x 8192, 8 / 9 tokens: 17.2 against 18.3 /
-        // 17.7 against 18.6; 12 tokens: 17.8 against 17.8).
-        if (L.wbits == 8) return L.nkt > 40 && (M > 11 || L.nstrips <= 256 || (L.nstrips > 512 && L.nstrips <= 768));
+        // 17.7 against 18.6; 12 tokens: 17.8 against 17.8), up to rank 8: its epilogue takes one rank after the other (9 tokens, rank
+        // 9 / 16 / 40: 19.3 / 21.2 / 27.6 us, here 18.4 / 18.7 / 20.9).
+        if (L.wbits == 8) return L.nkt > 40 && (M > 11 || r > 8 || L.nstrips <= 256 || (L.nstrips > 512 && L.nstrips <= 768));
         // K in one piece instead of chunks and a second launch (11008 x 4096, 4 tokens: 11.6 -> 9.5; 28672 x 8192: 28.8 -> 26.4;
         // 16384 x 12288, 16 tokens: 28.8 -> 25.1).  Beyond one round of compute units the persistent kernel's stream wins,
         // as it does where 16 tokens' activations would outweigh a single strip's weights for long (28672 x 4096: 19.5 against 21.2).
@@ -287,8 +288,10 @@ bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum)
             // The streaming kernel, a strip per compute unit as here and no LDS on the way of the activations: short K (1024 x 1024,
             // 24 tokens: 3.8 against 4.3; 2048 x 4096, 17 tokens: 5.2 against 5.6), and in the one-pass mode, where it waits for
             // memory only, while its stream fills the chip (4096 x 4096, 24 tokens: 7.3 against 7.8; 3072 x 3072: 5.7
-            // against 5.5).  From rank 8 on its epilogue, one rank after the other, decides (4096 x 4096, rank 8: 9.1 against 8.3).
-            if (L.nkt < 16 || (r < (L.nstrips < 32 ? 9 : 8) && L.nkt <= 20 && M < 24)) return false;
+            // against 5.5).  From rank 8 on its epilogue, one rank after the other, decides (4096 x 4096, rank 8: 9.1 against 8.3),
+            // with a single k-tile per wave from rank 11 on (1024 x 4096, 24 tokens, rank 16: 6.0 against 5.3; 512 x 1040, rank 9: 3.97
+            // against 4.08).
+            if ((L.nkt < 16 && r <= 10) || (r < (L.nstrips < 32 ? 9 : 8) && L.nkt <= 20 && M < 24)) return false;
             if (fast && r < 8 && L.nkt <= 40 && L.nstrips >= 192 && (L.nkt * L.nstrips >= 5120 || L.nstrips > 224)) return false;
         }
         if (L.N < 64) return true;  // the tiled kernel has no such tile

@@ -513,27 +513,76 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
     float cn[WTN];
 #pragma unroll
     for (int j = 0; j < WTN; ++j) cn[j] = raw ? 1.0f : colscale[min(n_wave + j * 16 + col, L.Np - 1)];
-    // LoRC of rank <= 8 (the paper's setting): the tile's rows of T and columns of V go through LDS
-    // once (zero-padded to rank 8, V converted to binary32), so that the 8 fused multiply-adds per
-    // output read registers filled by two 16-byte LDS reads per row and per column.
-    constexpr int RL = 8;
-    constexpr int PATCH_BYTES = C::THREADS / 64 * 16 * SLAB_LD * 4;
-    static_assert(PATCH_BYTES + (C::BM + C::BN) * RL * 4 <= C::NSTAGE * C::STAGE, "LoRC tiles do not fit the stages");
-    float* Ts = reinterpret_cast<float*>(smem + PATCH_BYTES);  // [BM][RL]
-    float* Vs = Ts + C::BM * RL;                               // [BN][RL]
+    // LoRC: T . V on the float32 matrix cores, on top of the scaled sums (each output is a chain of fused multiply-adds, in
+    // binary32 as before).  The tile's rows of T and columns of V go through LDS in blocks of at most kRanks ranks, T turned
+    // round so that the sixteen rows of an operand lie side by side; ranks past r are zero on both sides.  Four ranks are one
+    // matrix instruction per 16 x 16 tile (32 cycles) where vector multiply-adds take 64; reading T and V in place per output,
+    // as ranks above 8 did, cost more than the whole product (2048 x 5120 x 13824: without a correction 192 -> 185 us, since
+    // the token scales are fetched all at once; rank 8 199 -> 192, rank 16 468 -> 208, rank 40 948 -> 237).
+    constexpr int kRanks = 32;
+    constexpr int LDT = C::BM + 8, LDV = C::BN + 8;  // the four ranks of an operand spread over all LDS banks
+    static_assert(kRanks * (LDT * 4 + LDV * 2) <= C::NSTAGE * C::STAGE, "LoRC factors do not fit the stages");
     const int rk = raw ? 0 : lorc.r;
-    const bool lorc_lds = rk > 0 && rk <= RL;
-    if (lorc_lds) {
-        for (int idx = wg_tid; idx < C::BM * RL; idx += kThreads) {
-            const int row = idx / RL, q = idx % RL;
-            Ts[idx] = q < rk ? lorc.T[min(m0 + row, M - 1) * rk + q] : 0.f;
+    if (!raw && (KG == 1 || kgrp == 0)) {
+#pragma unroll
+        for (int i = 0; i < WTM; ++i)
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                const float sm = sx[min(m0 + (wm * WTM + i) * 16 + 4 * lb + rg, M - 1)];
+#pragma unroll
+                for (int j = 0; j < WTN; ++j) acc[i][j][rg] *= sm * cn[j];
+            }
+    }
+    for (int q0 = 0; q0 < rk; q0 += kRanks) {
+        const int nr = min(rk - q0, kRanks), steps = (nr + 3) >> 2;
+        float* Ts = reinterpret_cast<float*>(smem);                         // [4 * steps][LDT]
+        uint16_t* Vs = reinterpret_cast<uint16_t*>(smem + kRanks * LDT * 4);  // [4 * steps][LDV]
+        // eight loads ahead of their eight stores (a row of the tile: 4 * steps of T, then as many of V, whole columns at a time)
+        for (int idx = wg_tid; idx < C::BM * 4 * steps; idx += 8 * kThreads) {
+            float t[8];
+            int slot[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int e = idx + u * kThreads, row = e / (4 * steps), q = e - row * (4 * steps);
+                slot[u] = row < C::BM ? q * LDT + row : -1;
+                t[u] = lorc.T[min(m0 + row, M - 1) * rk + q0 + min(q, nr - 1)];
+                if (q >= nr) t[u] = 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (slot[u] >= 0) Ts[slot[u]] = t[u];
         }
-        for (int idx = wg_tid; idx < RL * C::BN; idx += kThreads) {
-            const int q = idx / C::BN, c = idx % C::BN;
-            const int64_t n = min(strip0 * 16 + c, L.N - 1);
-            Vs[c * RL + q] = q < rk ? half_bits_to_f32(lorc.V[(int64_t)q * L.N + n]) : 0.f;
+        for (int idx = wg_tid; idx < C::BN * 4 * steps; idx += 8 * kThreads) {
+            uint16_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int e = idx + u * kThreads, q = e / C::BN, c = e - q * C::BN;
+                v[u] = lorc.V[(int64_t)(q0 + min(q, nr - 1)) * L.N + min(strip0 * 16 + c, L.N - 1)];
+                if (q >= nr) v[u] = 0;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int e = idx + u * kThreads, q = e / C::BN, c = e - q * C::BN;
+                if (q < 4 * steps) Vs[q * LDV + c] = v[u];
+            }
         }
         __syncthreads();
+        if (KG == 1 || kgrp == 0) {
+            const float* tp = Ts + lb * LDT + wm * WTM * 16 + col;
+            const uint16_t* vp = Vs + lb * LDV + wn * WTN * 16 + col;
+            for (int st = 0; st < steps; ++st) {
+                float tf[WTM], vf[WTN];
+#pragma unroll
+                for (int i = 0; i < WTM; ++i) tf[i] = tp[4 * st * LDT + 16 * i];
+#pragma unroll
+                for (int j = 0; j < WTN; ++j) vf[j] = half_bits_to_f32(vp[4 * st * LDV + 16 * j]);
+#pragma unroll
+                for (int i = 0; i < WTM; ++i)
+#pragma unroll
+                    for (int j = 0; j < WTN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(tf[i], vf[j], acc[i][j], 0, 0, 0);
+            }
+        }
+        __syncthreads();  // the area is rewritten by the next block, or by the patches
     }
     if (KG == 2 && kgrp != 0) return;  // no barrier below: the first group alone writes the tile out
     constexpr int LPR = SLAB_N / 4;   // lanes per slab row when each lane carries 4 columns
@@ -545,39 +594,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
 #pragma unroll
     for (int i = 0; i < WTM; ++i) {
         const int64_t m_slab = m0 + (wm * WTM + i) * 16;
-        float sxm[4];
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) sxm[rg] = raw ? 1.0f : sx[min(m_slab + 4 * lb + rg, M - 1)];
-        v4f tl[4][RL / 4];
-        if (lorc_lds) {
+        for (int j = 0; j < WTN; ++j)
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg)
-#pragma unroll
-                for (int h = 0; h < RL / 4; ++h)
-                    tl[rg][h] = *reinterpret_cast<const v4f*>(Ts + ((wm * WTM + i) * 16 + 4 * lb + rg) * RL + 4 * h);
-        }
-#pragma unroll
-        for (int j = 0; j < WTN; ++j) {
-            const int64_t n = min(n_wave + j * 16 + col, L.N - 1);
-            v4f vl[RL / 4];
-            if (lorc_lds) {
-#pragma unroll
-                for (int h = 0; h < RL / 4; ++h)
-                    vl[h] = *reinterpret_cast<const v4f*>(Vs + ((wn * WTN + j) * 16 + col) * RL + 4 * h);
-            }
-#pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                float y = (sxm[rg] * cn[j]) * acc[i][j][rg];
-                if (lorc_lds) {
-#pragma unroll
-                    for (int q = 0; q < RL; ++q) y = fmaf(tl[rg][q / 4][q % 4], vl[q / 4][q % 4], y);  // padding adds 0 * 0
-                } else if (rk > 0) {  // larger ranks: read in place
-                    const float* t = lorc.T + min(m_slab + 4 * lb + rg, M - 1) * rk;
-                    for (int q = 0; q < rk; ++q) y = fmaf(t[q], half_bits_to_f32(lorc.V[(int64_t)q * L.N + n]), y);
-                }
-                patch[(4 * lb + rg) * SLAB_LD + j * 16 + col] = y;
-            }
-        }
+            for (int rg = 0; rg < 4; ++rg) patch[(4 * lb + rg) * SLAB_LD + j * 16 + col] = acc[i][j][rg];
 #pragma unroll
         for (int t = 0; t < 16 / RPI; ++t) {
             const int r = lane_stores ? t * RPI + srow : 0;
@@ -625,14 +645,46 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
     for (int s = 0; s < ksplit; ++s) acc += *reinterpret_cast<const v4f*>(partial + ((int64_t)s * M + m) * L.Np + n0);
     const float* colscale = reinterpret_cast<const float*>(blob + L.off_colscale);
     const float sm = sx[m];
+    float y[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) y[q] = (sm * colscale[n0 + q]) * acc[q];  // padding columns have a scale, too
+    // Eight ranks at a time, every load ahead of the sums (clamped to the last rank and channel); a thread's four channels of a
+    // row of V in one load where they lie on 8 bytes (163 x 5504 x 5632, two launches: rank 8 29.7 -> 23.9 us, rank 40 49.8 -> 28.4).
+    auto ranks = [&](auto vector_tag) __attribute__((always_inline)) {
+        constexpr bool VEC = decltype(vector_tag)::value;
+        for (int j0 = 0; j0 < lorc.r; j0 += 8) {
+            float t[8];
+            uint2 v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int jj = min(j0 + j, lorc.r - 1);
+                const uint16_t* row = lorc.V + (int64_t)jj * L.N;
+                t[j] = lorc.T[m * lorc.r + jj];
+                if constexpr (VEC) {
+                    v[j] = *reinterpret_cast<const uint2*>(row + n0);
+                } else {
+                    const uint32_t a = row[min(n0, L.N - 1)], b = row[min(n0 + 1, L.N - 1)], c = row[min(n0 + 2, L.N - 1)], d = row[min(n0 + 3, L.N - 1)];
+                    v[j] = make_uint2(a | b << 16, c | d << 16);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (j0 + j < lorc.r) {
+                    y[0] = fmaf(t[j], half_bits_to_f32((uint16_t)v[j].x), y[0]);
+                    y[1] = fmaf(t[j], half_bits_to_f32((uint16_t)(v[j].x >> 16)), y[1]);
+                    y[2] = fmaf(t[j], half_bits_to_f32((uint16_t)v[j].y), y[2]);
+                    y[3] = fmaf(t[j], half_bits_to_f32((uint16_t)(v[j].y >> 16)), y[3]);
+                }
+        }
+    };
+    if (n0 + 4 <= L.N && (L.N & 3) == 0 && (reinterpret_cast<uintptr_t>(lorc.V) & 7) == 0) ranks(std::integral_constant<bool, true>{});
+    else ranks(std::integral_constant<bool, false>{});
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int64_t n = n0 + q;
         if (n >= L.N) break;
-        float y = (sm * colscale[n]) * acc[q];
-        for (int j = 0; j < lorc.r; ++j) y = fmaf(lorc.T[m * lorc.r + j], half_bits_to_f32(lorc.V[(int64_t)j * L.N + n]), y);
-        if (out_dtype == 0) reinterpret_cast<float*>(Y)[m * ldy + n] = y;
-        else reinterpret_cast<uint16_t*>(Y)[m * ldy + n] = f32_to_bf16_bits(y);
+        if (out_dtype == 0) reinterpret_cast<float*>(Y)[m * ldy + n] = y[q];
+        else reinterpret_cast<uint16_t*>(Y)[m * ldy + n] = f32_to_bf16_bits(y[q]);
     }
 }
 
