@@ -21,47 +21,44 @@ typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
 __device__ inline float half_bits_to_float(uint32_t h) { return half_bits_to_f32((uint16_t)h); }
 
+// RP consecutive ranks of a row of U (binary16), and their products with x; a row past the end counts as zeros
+template <int RP>
+struct alignas(2 * RP < 16 ? 2 * RP : 16) Ranks {
+    uint32_t w[RP / 2];
+};
+template <int RP>
+__device__ inline void add_ranks(float (&acc)[RP], float x, const Ranks<RP>& u, bool live)
+{
+#pragma unroll
+    for (int q = 0; q < RP / 2; ++q) {
+        const uint32_t w = live ? u.w[q] : 0u;
+        acc[2 * q] = fmaf(x, half_bits_to_float(w & 0xFFFFu), acc[2 * q]);
+        acc[2 * q + 1] = fmaf(x, half_bits_to_float(w >> 16), acc[2 * q + 1]);
+    }
+}
+
 // acc[j] += sum_i x_i * U[k_i][j] for the 8 elements (x_i, k_i = kbase + 64 i) that a lane picked up
 // from its wave's 512-element slice: consecutive lanes own consecutive k, so a wave's load of U
 // rows is one contiguous run (r = 8: 1 KB per instruction) instead of 64 scattered 16-byte pieces.
+// U points to the first of this workgroup's `rb` <= RP ranks, rows lie r elements apart.
 template <int RP>
-__device__ inline void lorc_accumulate(float (&acc)[RP], const float (&x)[8], const uint16_t* U, int64_t kbase, int64_t K, int r)
+__device__ inline void lorc_accumulate(float (&acc)[RP], const float (&x)[8], const uint16_t* U, int64_t kbase, int64_t K, int r, int rb)
 {
     // K is a multiple of 128, not of 512: elements past the row's end are zero and meet a zeroed row of U
-    if ((r & 7) == 0) {
+    if ((r & (RP < 8 ? RP - 1 : 7)) == 0) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const bool live = kbase + 64 * i < K;
-            const uint4* urow = reinterpret_cast<const uint4*>(U + (live ? kbase + 64 * i : 0) * r);
-#pragma unroll
-            for (int jb = 0; jb < RP / 8; ++jb) {
-                if (jb * 8 < r) {
-                    uint4 u = urow[jb];
-                    uint32_t uw[4] = {live ? u.x : 0u, live ? u.y : 0u, live ? u.z : 0u, live ? u.w : 0u};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        acc[jb * 8 + 2 * q] = fmaf(x[i], half_bits_to_float(uw[q] & 0xFFFFu), acc[jb * 8 + 2 * q]);
-                        acc[jb * 8 + 2 * q + 1] = fmaf(x[i], half_bits_to_float(uw[q] >> 16), acc[jb * 8 + 2 * q + 1]);
-                    }
-                }
-            }
+            const Ranks<RP> u = *reinterpret_cast<const Ranks<RP>*>(U + (live ? kbase + 64 * i : 0) * r);
+            add_ranks<RP>(acc, x[i], u, live);
         }
     } else {
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll
             for (int j = 0; j < RP; ++j)
-                if (j < r && kbase + 64 * i < K) acc[j] = fmaf(x[i], half_bits_to_float(U[(kbase + 64 * i) * r + j]), acc[j]);
+                if (j < rb && kbase + 64 * i < K) acc[j] = fmaf(x[i], half_bits_to_float(U[(kbase + 64 * i) * r + j]), acc[j]);
     }
-}
-
-// NT threads per token: 256 when there are tokens enough to fill the chip, 1024 for a handful of
-// tokens (decode), where one row's latency chain is all there is.
-__device__ inline uint32_t f32_to_bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);  // round to nearest even (finite inputs)
-    return u >> 16;
 }
 
 // two binary32 values -> two bf16 in one dword (round to nearest even): the packed hardware conversion
@@ -210,6 +207,8 @@ __device__ inline double sum_squares(double acc, uint4 v)
 // (gain, bias), 3 ReLU, 4 gated SiLU (X is the gate, `other` the second operand).  With 1 and 2 a non-null
 // `other` is a residual added to X first; the sum, rounded to bf16, also goes to H.  Every thread reads an
 // element of `other` before it writes the same element of H, and nothing else touches it: H may be `other`.
+// NT threads per token: 256 when there are tokens enough to fill the chip, 1024 for a handful of
+// tokens (decode), where one row's latency chain is all there is.
 template <int RP, int NT, int NORM>
 __global__ __launch_bounds__(NT) void k_quantize_act(const uint16_t* __restrict__ X, int64_t K, int64_t ldx,
                                                          uint8_t* __restrict__ Xq, float* __restrict__ sx,
@@ -228,6 +227,12 @@ __global__ __launch_bounds__(NT) void k_quantize_act(const uint16_t* __restrict_
     const uint4* xrow = reinterpret_cast<const uint4*>(X + row * ldx);
     uint2* qrow = reinterpret_cast<uint2*>(Xq + row * K);
     const int nchunk = (int)(K / 8);
+    // More than 8 ranks and few tokens: a workgroup per 8 (or 4) of them, each of which forms the row for itself (one workgroup with all
+    // sums in its threads waits for up to eight loads of U in turn, and spills: 4 x 4096, RMS normalisation, rank 16 / 40: 11.7 / 43.5
+    // -> 8.6 / 8.7 us; 64 x 20224 plain, rank 40: 74 -> 29).  The first one writes what is not T.
+    const bool first_block = RP == 0 || blockIdx.y == 0;
+    const int rb = RP == 0 ? 0 : min(r - RP * (int)blockIdx.y, RP);
+    if constexpr (RP > 0) U += RP * blockIdx.y;
 
     uint4 v[kRegChunks];
 #pragma unroll
@@ -236,21 +241,21 @@ __global__ __launch_bounds__(NT) void k_quantize_act(const uint16_t* __restrict_
         v[c] = make_uint4(0, 0, 0, 0);
         if (idx < nchunk) v[c] = xrow[idx];
     }
-    // Rank 8 behind the RMS normalisation: the rows of U that meet the thread's first chunk are loaded here, not behind the
+    // Eight ranks behind the RMS normalisation: the rows of U that meet the thread's first chunk are loaded here, not behind the
     // normalisation whose result they are multiplied with (300 x 5120: 10.4 -> 8.7 us, 800 x 4096: 12.0 -> 11.1, 16 x 8192:
     // 9.1 -> 8.9; behind the other producers it cost 1 to 4 %).  A row past the end is read as row 0 and zeroed at its use.
     // In 1024 threads (few tokens, or rows beyond 8192 elements) only where it gains: a thread with several chunks of the row, and
     // of the residual, ahead of its sums waits for these loads as well (1 x 11008 with a residual: 10.1 us with them, 9.4 without;
     // 128 x 20480: 13.3, 12.4; 300 x 11008, no residual: 18.5, 17.7; the other way round at 300 x 20480 with one: 26.3, 28.9).
-    constexpr bool EARLY_U = RP == 8 && NORM == 1;
-    uint4 u0[EARLY_U ? 8 : 1];
+    constexpr bool EARLY_U = RP > 0 && RP <= 8 && NORM == 1;
+    Ranks<EARLY_U ? RP : 8> u0[EARLY_U ? 8 : 1];
     const int64_t k0 = (int64_t)(tid & ~63) * 8 + (tid & 63);
-    const bool early = EARLY_U && r == 8 &&
+    const bool early = EARLY_U && (r & (RP < 8 ? RP - 1 : 7)) == 0 &&
                        (NT != 1024 || (K > 4096 && K <= 8192) || (pr.other == nullptr ? K > 12288 : K > 16384 && gridDim.x > 256));
     if constexpr (EARLY_U) {
         if (early && (tid & ~63) < nchunk) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) u0[i] = reinterpret_cast<const uint4*>(U)[k0 + 64 * i < K ? k0 + 64 * i : 0];
+            for (int i = 0; i < 8; ++i) u0[i] = *reinterpret_cast<const Ranks<RP>*>(U + (k0 + 64 * i < K ? ((uint32_t)k0 + 64u * i) * (uint32_t)r : 0u));  // K <= 32768
         }
     }
     if constexpr (NORM != 0) {  // the whole row sits in registers (the launcher guarantees K <= 8 * kRegChunks * NT)
@@ -263,10 +268,10 @@ __global__ __launch_bounds__(NT) void k_quantize_act(const uint16_t* __restrict_
                 if (idx < nchunk) {
                     if constexpr (NORM == 4) {
                         v[c] = swiglu8(v[c], orow[idx]);
-                        if (pr.H != nullptr) hrow[idx] = v[c];
+                        if (pr.H != nullptr && first_block) hrow[idx] = v[c];
                     } else {
                         v[c] = add8(v[c], orow[idx]);
-                        hrow[idx] = v[c];
+                        if (first_block) hrow[idx] = v[c];
                     }
                 }
             }
@@ -349,17 +354,11 @@ __global__ __launch_bounds__(NT) void k_quantize_act(const uint16_t* __restrict_
                 if (first && early) {
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        const bool live = k0 + 64 * i < K;
-                        const uint32_t uw[4] = {live ? u0[i].x : 0u, live ? u0[i].y : 0u, live ? u0[i].z : 0u, live ? u0[i].w : 0u};
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            acc[2 * q] = fmaf(x[i], half_bits_to_float(uw[q] & 0xFFFFu), acc[2 * q]);
-                            acc[2 * q + 1] = fmaf(x[i], half_bits_to_float(uw[q] >> 16), acc[2 * q + 1]);
-                        }
+                        add_ranks<RP>(acc, x[i], u0[i], k0 + 64 * i < K);
                     }
                     return;
                 }
-            lorc_accumulate<RP>(acc, x, U, (int64_t)(idx - lane) * 8 + lane, K, r);
+            lorc_accumulate<RP>(acc, x, U, (int64_t)(idx - lane) * 8 + lane, K, r, rb);
         };
 #pragma unroll
         for (int c = 0; c < kRegChunks; ++c) {
@@ -385,15 +384,15 @@ __global__ __launch_bounds__(NT) void k_quantize_act(const uint16_t* __restrict_
         scale = amax / 448.0f;  // IEEE binary32 division
         inv = 448.0f / amax;    // IEEE binary32 division
     }
-    if (tid == 0) sx[row] = scale;
+    if (tid == 0 && first_block) sx[row] = scale;
 
 #pragma unroll
     for (int c = 0; c < kRegChunks; ++c) {
         int idx = tid + c * kThreads;
-        if (idx < nchunk) qrow[idx] = encode8(v[c], inv);
+        if (idx < nchunk && first_block) qrow[idx] = encode8(v[c], inv);
     }
     if constexpr (NORM == 0)
-        for (int idx = tid + kRegChunks * kThreads; idx < nchunk; idx += kThreads) qrow[idx] = encode8(xrow[idx], inv);
+        for (int idx = tid + kRegChunks * kThreads; idx < nchunk && first_block; idx += kThreads) qrow[idx] = encode8(xrow[idx], inv);
 
     if constexpr (RP > 0) {
 #pragma unroll
@@ -404,11 +403,11 @@ __global__ __launch_bounds__(NT) void k_quantize_act(const uint16_t* __restrict_
             if ((tid & 63) == 0) s_t[tid >> 6][j] = a;
         }
         __syncthreads();
-        if (tid < r) {  // fixed order: pairs of waves, then the pairs in sequence
+        if (tid < rb) {  // fixed order: pairs of waves, then the pairs in sequence
             float t = 0.0f;
 #pragma unroll
             for (int w = 0; w < kWaves; w += 2) t += s_t[w][tid] + s_t[w + 1][tid];
-            T[row * r + tid] = t;
+            T[row * r + RP * blockIdx.y + tid] = t;
         }
     }
 }
@@ -714,6 +713,212 @@ __global__ __launch_bounds__(1024) void k_quantize_rows_helped(const uint16_t* _
     if (lane < 8 && live) T[row * 8 + lane] = mine + s_part[w][lane];  // first half of the row plus second half: a fixed order
 }
 
+// ---------------------------------------------------------------------------
+// The left factor alone, T = y . U, for many tokens with more than 8 ranks: a launch of its own behind the quantizer without
+// one.  On the float32 matrix cores (v_mfma_f32_16x16x4_f32; in bfloat16, with U as the sum of two, the products are exact as
+// well but the unit drops bits of a run of eight: 4.4e-7 against 1e-7 relative error at 20224 elements).  A workgroup takes
+// 16 tokens and 16 * NB ranks, its eight waves split K.  A wave takes 64 elements at a time, a line of every row, PF such units ahead;
+// which element of its eight a lane feeds to an instruction is free as long as U's rows follow, so both operands are used as
+// they come, and U goes through the wave's own slice of LDS, which turns it round (a row of U is sixteen ranks, the operand
+// wants one of eight rows per lane).  The sums of 16 elements are added to the total with its rounding compensated, which keeps
+// the error at that of the other forms' trees (9e-8 at 4096 elements, 9e-8 against 1.25e-7 at 20224).  Bound by the matrix cores and
+// the scattered 16-byte pieces of X and U, about a microsecond per unit and wave.  With the quantizer, before -> now: 4000 x 4096
+// plain, rank 16 / 40: 50 -> 22.5 / 257 -> 37 us; 1000 x 11008 RMS normalisation, rank 40: 304 -> 64; 4000 x 2048, rank 64: 328 -> 39.
+// NORM as above, but a residual has been added already (X is then H).  Row statistics are formed again, in another order of
+// the same binary64 sums.
+// ---------------------------------------------------------------------------
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+template <int NORM, int NB>
+__global__ __launch_bounds__(512) void k_lorc_left(const uint16_t* __restrict__ X, int64_t M, int64_t K, int64_t ldx,
+                                                   const uint16_t* __restrict__ U, int r, float* __restrict__ T, Producer pr)
+{
+    constexpr int kSlice = 32 * 16 + 3 * 16;  // binary16 values of 32 rows x 16 ranks; 16 more behind every 8 rows spread the reads over all banks
+    constexpr int kWaveBytes = NB * kSlice * 2 > NB * 1024 ? NB * kSlice * 2 : NB * 1024;
+    __shared__ __attribute__((aligned(16))) uint8_t s_mem[8 * kWaveBytes];  // slices of U, then the waves' sums
+    __shared__ float s_stat[NORM == 1 || NORM == 2 ? 16 : 1][2];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t m0 = (int64_t)blockIdx.x * 16;
+    const int q0 = (int)blockIdx.y * (16 * NB);  // first rank of the workgroup
+
+    if constexpr (NORM == 1 || NORM == 2) {
+        const int nchunk = (int)(K / 8);
+        for (int rr = 0; rr < 2; ++rr) {
+            const uint4* x = reinterpret_cast<const uint4*>(X + min(m0 + 2 * wave + rr, M - 1) * ldx);
+            double ss = 0.0, s1 = 0.0;
+            for (int i0 = lane; i0 < nchunk; i0 += 256) {
+                uint4 v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = x[min(i0 + 64 * u, nchunk - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (i0 + 64 * u < nchunk) {
+                        ss = sum_squares(ss, v[u]);
+                        if constexpr (NORM == 2) s1 = sum_values(s1, v[u]);
+                    }
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                ss += __shfl_xor(ss, off);
+                if constexpr (NORM == 2) s1 += __shfl_xor(s1, off);
+            }
+            float mu, rstd;
+            row_statistics<NORM>(s1, ss, K, pr.eps, mu, rstd);
+            if (lane == 0) {
+                s_stat[2 * wave + rr][0] = mu;
+                s_stat[2 * wave + rr][1] = rstd;
+            }
+        }
+        __syncthreads();
+    }
+    const int row = lane & 15, lb = lane >> 4;
+    float mu = 0.0f, rstd = 0.0f;
+    if constexpr (NORM == 1 || NORM == 2) {
+        mu = s_stat[row][0];
+        rstd = s_stat[row][1];
+    }
+    // operand A: lane (row, lb) holds y[row][8 lb + [0, 8)] of a step of 32; two steps are a line of every row
+    const int64_t mrow = min(m0 + row, M - 1);  // a row past the end repeats the last one and is not stored
+    const uint16_t* xp = X + mrow * ldx + 8 * lb;
+    const uint16_t* op = NORM == 4 ? pr.other + mrow * pr.ld_other + 8 * lb : nullptr;
+    // U: lane l fetches ranks 8 (l % 2) + [0, 8) of row l / 2 of a step; ranks past the last are zeroed in the slice
+    const int uk = lane >> 1, un = q0 + 8 * (lane & 1);
+    const bool whole = (r & 7) == 0;  // eight ranks lie on 16 bytes
+    uint16_t* slice = reinterpret_cast<uint16_t*>(s_mem + wave * kWaveBytes);
+    uint16_t* const put = slice + uk * 16 + (uk >> 3) * 16 + 8 * (lane & 1);
+    const uint16_t* const get = slice + lb * (8 * 16 + 16) + row;
+
+    struct Fetched {
+        uint4 x[2], o[NORM == 4 ? 2 : 1], g[NORM == 1 || NORM == 2 ? 2 : 1], b[NORM == 2 ? 2 : 1], u[2][NB];
+    };
+    const int units = (int)(K / 64);
+    auto fetch = [&](Fetched& f, int unit) __attribute__((always_inline)) {
+        const int64_t k = (int64_t)min(unit, units - 1) * 64;  // past the end: the last again, unused
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            f.x[s] = *reinterpret_cast<const uint4*>(xp + k + 32 * s);
+            if constexpr (NORM == 4) f.o[s] = *reinterpret_cast<const uint4*>(op + k + 32 * s);
+            if constexpr (NORM == 1 || NORM == 2) f.g[s] = *reinterpret_cast<const uint4*>(pr.gain + k + 32 * s + 8 * lb);
+            if constexpr (NORM == 2) f.b[s] = *reinterpret_cast<const uint4*>(pr.bias + k + 32 * s + 8 * lb);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const int n = un + 16 * nb;
+                const uint16_t* p = U + (k + 32 * s + uk) * r;
+                if (whole) {
+                    f.u[s][nb] = *reinterpret_cast<const uint4*>(p + (n < r ? n : 0));
+                } else {
+                    uint32_t w[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) w[j] = p[min(n + j, r - 1)];
+                    f.u[s][nb] = make_uint4(w[0] | w[1] << 16, w[2] | w[3] << 16, w[4] | w[5] << 16, w[6] | w[7] << 16);
+                }
+            }
+        }
+    };
+    f32x4_t acc[NB], lost[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = lost[nb] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    bool live[NB];  // this lane's rank (its operand column) exists
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) live[nb] = q0 + 16 * nb + row < r;
+    auto multiply = [&](const Fetched& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            uint4 y = f.x[s];
+            if constexpr (NORM == 1) y = normalize8(y, f.g[s], rstd);
+            if constexpr (NORM == 2) y = normalize8_affine(y, f.g[s], f.b[s], mu, rstd);
+            if constexpr (NORM == 3) y = relu8(y);
+            if constexpr (NORM == 4) y = swiglu8(y, f.o[s]);
+            const uint32_t yw[4] = {y.x, y.y, y.z, y.w};
+            __builtin_amdgcn_wave_barrier();  // behind the reads of the step before
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<uint4*>(put + nb * kSlice) = f.u[s][nb];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            uint16_t h[NB][8];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) h[nb][i] = get[nb * kSlice + 16 * i];
+            f32x4_t part[NB][2];  // even and odd elements
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) part[nb][0] = part[nb][1] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float a = (i & 1) ? bf16_hi(yw[i >> 1]) : bf16_lo(yw[i >> 1]);
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    part[nb][i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, live[nb] ? half_bits_to_f32(h[nb][i]) : 0.0f, part[nb][i & 1], 0, 0, 0);
+            }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {  // compensated: what the total's rounding drops is added to the next sum
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4_t add = part[nb][h] - lost[nb], total = acc[nb] + add;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) lost[nb][i] = fabsf(total[i]) <= 0x1.fffffep127f ? (total[i] - acc[nb][i]) - add[i] : 0.0f;  // an infinity stays one
+                    acc[nb] = total;
+                }
+            }
+        }
+    };
+    constexpr int PF = NB == 1 ? 4 : NB == 2 ? 3 : 2;
+    {
+        Fetched f[PF];
+#pragma unroll
+        for (int i = 0; i < PF - 1; ++i) fetch(f[i], wave + 8 * i);
+        for (int u = wave; u < units;) {
+#pragma unroll
+            for (int i = 0; i < PF; ++i) {
+                fetch(f[(i + PF - 1) % PF], u + 8 * (PF - 1));
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(f[i]);
+                __builtin_amdgcn_sched_barrier(0);
+                u += 8;
+                if (u >= units) break;
+            }
+        }
+    }
+    __syncthreads();  // the waves' slices become their sums
+    float* part = reinterpret_cast<float*>(s_mem);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<f32x4_t*>(part + ((wave * NB + nb) * 64 + lane) * 4) = acc[nb];
+    __syncthreads();
+    // D[row][col] sits in lane 16 (row / 4) + col, register row % 4; the waves' sums in order
+    for (int o = tid; o < NB * 256; o += 512) {
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) t += part[w * NB * 256 + o];
+        const int nb = o >> 8, ln = (o >> 2) & 63;
+        const int64_t m = m0 + 4 * (ln >> 4) + (o & 3);
+        const int q = q0 + 16 * nb + (ln & 15);
+        if (m < M && q < r) T[m * r + q] = t;
+    }
+}
+
+template <int KIND>
+hipError_t launch_lorc_left(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, const uint16_t* U, int r, float* T,
+                            const Producer& pr, hipStream_t s)
+{
+    // sixteen ranks per workgroup while that leaves the chip idle, all of them where it would read the activations again for nothing
+    const unsigned gm = (unsigned)((M + 15) / 16), blocks = (unsigned)((r + 15) / 16);
+    const dim3 wg(512);
+    if (blocks == 1 || (int64_t)gm * blocks <= 2 * compute_units()) hipLaunchKernelGGL((k_lorc_left<KIND, 1>), dim3(gm, blocks), wg, 0, s, X, M, K, ldx, U, r, T, pr);
+    else if (blocks == 3) hipLaunchKernelGGL((k_lorc_left<KIND, 3>), dim3(gm, 1), wg, 0, s, X, M, K, ldx, U, r, T, pr);
+    else hipLaunchKernelGGL((k_lorc_left<KIND, 2>), dim3(gm, blocks / 2), wg, 0, s, X, M, K, ldx, U, r, T, pr);  // 2 or 4 blocks; four at once spill
+    return hipGetLastError();
+}
+
+// whether the bytes of two strided [M, K] bf16 matrices can meet
+bool overlap(const void* a, int64_t lda, const void* b, int64_t ldb, int64_t M, int64_t K)
+{
+    if (a == nullptr || b == nullptr) return false;
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    return a0 < b0 + 2 * (uintptr_t)((M - 1) * ldb + K) && b0 < a0 + 2 * (uintptr_t)((M - 1) * lda + K);
+}
+
 // the wave-per-token kernel with the rank-8 factor: eight tokens per workgroup, all of U in dynamic LDS
 template <int MAXC, int KIND>
 hipError_t launch_rows_lorc(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, uint8_t* Xq, float* sx, const uint16_t* U,
@@ -746,6 +951,35 @@ hipError_t launch_rows_lorc(const uint16_t* X, int64_t M, int64_t K, int64_t ldx
     return hipGetLastError();
 }
 
+// How the left factor of more than 8 ranks is formed (up to 8: by the workgroup or wave that quantizes the token).
+enum class LeftForm {
+    kBlocks,  // a workgroup per token and 8 ranks
+    kOne,     // a workgroup per token with up to 16 sums a thread
+    kApart    // k_lorc_left behind the quantizer
+};
+
+// In microseconds, graph-timed; b = blocks of 8 ranks.  Blocks cost about M b rows, kApart is flat up to 2000 tokens and then follows
+// the activations, so the line between them is one in M b^2: plain, 4096 elements, rank 40, 64 / 128 / 300 / 800 tokens: 13.6 / 12.0 / 20.8
+// / 44.4 in blocks, 13.2 / 13.1 / 13.4 / 14.4 apart; rank 24, 300 / 800: 11.0 / 21.9, 13.3 / 14.0.  Behind a normalisation kApart reads
+// the rows twice (rank 40, 128 / 300 / 800 tokens: 13.3 / 21.5 / 46.9, 19.6 / 20.1 / 21.8; 11008 elements: 38 / 76 / 184, 40 / 47 / 59), behind
+// the gated unit it evaluates it again (300 / 800: 22 / 46, 34 / 37; 11008: 72 / 178, 76 / 86).  Up to 16 ranks, one workgroup with all
+// sums passes the blocks between 300 and 800 tokens (4096, RMS normalisation: 12.4 and 16.3 against 9.6 and 17.3; 11008: 28.4 and 54.5
+// against 28.8 and 62.3) and is passed by kApart later (plain, 800 / 1500 tokens: 14.3 / 24.3, 13.9 / 15.8 apart; RMS 16.3 / 27.9, 22.0 / 24.3;
+// 20224, RMS, 1500: 104, 99; gated unit, 4000 x 4096: 52.7, 56.3).
+LeftForm left_form(int64_t M, int64_t K, int r, int kind, bool in_place)
+{
+    if (r <= 8) return LeftForm::kBlocks;
+    if (r <= 16) {
+        if (!in_place && M <= (K > 8192 && kind != 0 ? 256 : 512)) return LeftForm::kBlocks;
+        const bool apart = kind == 0 || kind == 3 ? M >= 800 : kind == 4 ? false : M >= 1400;
+        return apart ? LeftForm::kApart : LeftForm::kOne;
+    }
+    // with H over X or the second operand a row cannot be formed twice
+    if (in_place) return LeftForm::kApart;
+    const int64_t b = (r + 7) / 8, bound = kind == 0 || kind == 3 ? 3200 : kind == 4 ? (K > 8192 ? 6500 : 14000) : K > 8192 ? 3200 : 6000;
+    return M * b * b > bound ? LeftForm::kApart : LeftForm::kBlocks;
+}
+
 }  // namespace
 
 hipError_t launch_quantize_act(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, uint8_t* Xq, float* sx,
@@ -753,6 +987,22 @@ hipError_t launch_quantize_act(const uint16_t* X, int64_t M, int64_t K, int64_t 
 {
     if (M == 0) return hipSuccess;
     const int kind = pr.kind;
+    const bool in_place = overlap(pr.H, K, X, ldx, M, K) || overlap(pr.H, K, pr.other, pr.ld_other, M, K);
+    const LeftForm form = left_form(M, K, r, kind, in_place);
+    if (form == LeftForm::kApart) {
+        if (hipError_t e = launch_quantize_act(X, M, K, ldx, Xq, sx, nullptr, 0, nullptr, pr, s); e != hipSuccess) return e;
+        // behind the quantizer the sum with a residual, or the gated product, is read from H where there is one
+        const bool from_h = pr.H != nullptr;
+        const uint16_t* Y = from_h ? pr.H : X;
+        const int64_t ldy = from_h ? K : ldx;
+        switch (kind) {
+        case 1: return launch_lorc_left<1>(Y, M, K, ldy, U, r, T, pr, s);
+        case 2: return launch_lorc_left<2>(Y, M, K, ldy, U, r, T, pr, s);
+        case 3: return launch_lorc_left<3>(Y, M, K, ldy, U, r, T, pr, s);
+        case 4: if (!from_h) return launch_lorc_left<4>(Y, M, K, ldy, U, r, T, pr, s);
+        }
+        return launch_lorc_left<0>(Y, M, K, ldy, U, r, T, pr, s);
+    }
     // many tokens: one wave per token, without the LoRC factor or with the rank-8 one (U in LDS)
     if (M >= 1024 && K <= 8192 && (r == 0 || r == 8)) {
         const dim3 g4((unsigned)((M + 3) / 4));
@@ -785,7 +1035,13 @@ hipError_t launch_quantize_act(const uint16_t* X, int64_t M, int64_t K, int64_t 
 #undef ZQ_ROWS_N
         return hipGetLastError();
     }
-    const dim3 grid((unsigned)M);
+    const bool wide_sums = r > 8 && form == LeftForm::kOne;
+    // Four ranks per workgroup while that still gives every one a compute unit: half the loads of U and half the sums (16 x 8192, RMS
+    // normalisation, rank 8 / 16: 9.6 -> 8.3 / 9.7 -> 8.5 us; 64 x 4096, rank 16: 9.0 -> 8.2; twice the units lose, rank 40: 18.0 -> 23.3;
+    // so do ten workgroups over a long row of U, 16 x 20224, rank 40: 14.9 -> 16.4).  Two ranks gain 0.1 to 0.5 more, or lose.
+    const bool spread = r % 4 == 0 && !in_place && M * (r / 4) <= 256 && (K <= 8192 || r <= 16);
+    const int per = spread || r == 4 ? 4 : 8;
+    const dim3 grid((unsigned)M, (unsigned)(r > 0 && !wide_sums ? (r + per - 1) / per : 1));
     // 1024 threads per token for a handful of tokens, and for rows with a producer too long for 256 threads' registers
     const bool wide = (M <= 64 && K >= 2048) || (kind != 0 && K > 8 * kRegChunks * 256);
 #define ZQ_QUANT_N(RP, NT, KIND) \
@@ -806,10 +1062,9 @@ hipError_t launch_quantize_act(const uint16_t* X, int64_t M, int64_t K, int64_t 
         else ZQ_QUANT_K(RP, 256);       \
     } while (0)
     if (r == 0) ZQ_QUANT(0);
-    else if (r <= 8) ZQ_QUANT(8);
-    else if (r <= 16) ZQ_QUANT(16);
-    else if (r <= 32) ZQ_QUANT(32);
-    else ZQ_QUANT(64);
+    else if (wide_sums) ZQ_QUANT(16);
+    else if (per == 4) ZQ_QUANT(4);
+    else ZQ_QUANT(8);
 #undef ZQ_QUANT
 #undef ZQ_QUANT_K
 #undef ZQ_QUANT_N
