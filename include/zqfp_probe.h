@@ -41,10 +41,10 @@ int zqfp_probe_mfma(const void *operands, void *sink, int iters,
  * zqfp_w4a8_gemm* call with more than 16 tokens (and zqfp_gemm_workspace_bytes,
  * which must agree with it) uses bm x bn output tiles, `kg` wave groups per
  * workgroup and `ksplit` slices of K (1 = none) instead of planning them from
- * the problem size.  Tile shapes: 64x128, 64x192, 64x256, 128x128, 128x192,
- * 128x256, 256x256; kg 1, or 2 with 64-row tiles (it then needs an even number
- * of 128-wide k-tiles per slice, else one group runs); ksplit 1..64 (capped at
- * the number of k-tiles).  (0, 0, 0, 0) returns to automatic planning.
+ * the problem size.  Tile shapes: 64x128, 64x192, 64x256 with kg 1 or 2,
+ * 64x64, 64x96, 64x128 with kg 4, 128x128, 128x192, 128x256, 256x256 with kg
+ * 1; ksplit 1..64 (capped at the number of k-tiles).  E4M3 weights have 64x128
+ * (kg 1 or 2) and 128x128.  (0, 0, 0, 0) returns to automatic planning.
  * Process-wide, not meant for concurrent use with GEMM calls of other threads.
  * Returns ZQFP_OK or ZQFP_E_SHAPE.
  */

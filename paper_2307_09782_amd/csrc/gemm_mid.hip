@@ -249,10 +249,29 @@ MidShape mid_shape(int64_t M, const BlobLayout& L)
     return best;
 }
 
+// The tiled kernel's time with 2 x 2 waves per tile and wave group, in microseconds, for the line below: a launch is
+// 3 + t (e + s k-tiles), t = the most tiles any compute unit gets, or the K slices that the workspace query plans (then `split`).
+float two_by_two_us(int64_t M, const BlobLayout& L, bool& split)
+{
+    static constexpr struct { int bm, bn, kg; float e, s; } kinds[] = {
+        {64, 128, 2, 3.8f, 0.368f}, {64, 192, 2, 6.0f, 0.477f}, {64, 256, 2, 6.8f, 0.584f}, {64, 128, 1, 2.1f, 0.368f}, {64, 192, 1, 3.3f, 0.464f},
+        {64, 256, 1, 4.5f, 0.549f}, {128, 128, 1, 4.3f, 0.632f}, {128, 192, 1, 6.6f, 0.778f}, {128, 256, 1, 8.6f, 0.928f}, {256, 256, 1, 12.4f, 2.009f}};
+    float us = plan_slices(M, L.Np, L.nkt).us;
+    split = us > 0.0f;
+    if (split) return us;
+    for (const auto& k : kinds) {
+        const int64_t t = ((M + k.bm - 1) / k.bm) * ((L.Np + k.bn - 1) / k.bn);
+        if ((k.kg == 2 && (t > 256 || (L.nkt & 1))) || (k.bm > 64 && M <= 64)) continue;
+        const float one = 3.0f + (float)((t + 255) / 256) * (k.e + k.s * (float)L.nkt) * (t <= 256 && k.kg == 1 && k.bm < 256 ? 1.3f : 1.0f);
+        if (us == 0.0f || one < us) us = one;
+    }
+    return us;
+}
+
 }  // namespace
 
 // Where this form is the faster one (graph-timed, weights beyond the last-level cache, exact mode, before -> after in us).
-bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum)
+bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum, bool workspace)
 {
     const bool fast = accum != 0;
     if (M <= 16) {
@@ -272,9 +291,8 @@ bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum)
         // In one pass it holds the factors of five tokens and ranks up to 8 as well (5120 x 4000, 5 tokens: 5.8 against 6.1).
         return M > (fast && r > 4 && r <= 8 ? 5 : 4) && L.nkt > 32 && L.nstrips <= 256;
     }
-    // More tokens: against the tiled kernel's estimate (4096 x 12288, 24 / 64 tokens: 18.5 -> 10.6 / 19.9 -> 14.7; 4096 x 4096, 128
-    // tokens: 18.7 -> 11.3; 8192 x 28672 and 28672 x 8192 at 64 tokens stay there, 35.7 against 47.0 and 39.1 against 52.6).
-    const TilePlan p = effective_tile_plan(M, L.Np, L.nkt);
+    // More tokens: against the tiled kernel's estimate.
+    const TilePlan p = effective_tile_plan(M, L.Np, L.nkt, accum, L.wbits, workspace);
     if (p.forced) return false;
     const MidShape ms = mid_shape(M, L);
     // Every L2 fetches the activations of its workgroups, all M x K bytes once several groups of strips are about: beyond what the
@@ -305,15 +323,27 @@ bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum)
         return tiles <= 256 && us < 7.0f + 0.465f * (float)L.nkt && !(fast && extra > 8.0f);
     }
     if (L.N < 64) return true;
-    // Both estimates are those of the exact mode.  One pass takes an un-split tiled launch down by 13 to 20 %, this one, which waits for
-    // memory, by 3 to 5 (8192 x 28672, 32 tokens: 29.8 against 33.9; 6144 x 24576, 24 tokens: 22.1 against 24.1), and the
-    // low-rank correction costs the tiled kernel, which stages its factors, half as much (3072 x 20000, 32 tokens, rank 8: 18.7
-    // against 19.1).  Beyond 16384 rows this kernel is slower than its estimate (28672 x 8192, 32 tokens: 37.3 against 38.2 us; one
-    // pass 33.3 against 37.7; 96 tokens, one pass: 43.7 against 46.3).  Many tokens on few channels go to the tiled kernel by the
-    // activations they fetch (11008 x 128, 2048 tokens: 19.2 against 34.2; 4096 x 256, 4096 tokens, one pass: 14.0 against 15.2).
-    float bar = p.us;
+    if (M > 64 && M < 1024) {
+        // Both sides' estimates, this one's fitted to the exact mode, on 21 weight shapes, both modes and ranks 0, 8 and 40: the lines below
+        // give away 0.7 % against always taking the faster one (2304 x 6912, 96 tokens: 8.9, tiled 9.4; 4096 x 12288: 22.1, 16.5; 4096 x
+        // 4096, 163 tokens: 13.0, 11.9; 11008 x 1024, 512 tokens: 20.9, 25.4).  One pass takes 4 % off this kernel, which waits for memory;
+        // a rank costs both much the same up to 16, beyond that the tiled kernel, whose factors lie in LDS, less.
+        // K slices take longer than their estimate where they are short (11008 x 1024, 96 tokens: 13.6 here, 15.7 in slices; one pass, 11008 x
+        // 256, 200 tokens: 11.7, 12.3; but 20352 x 1713, 128 tokens: 29.1, 19.8).
+        if (p.ksplit > 1) return us + extra < p.us * (fast ? 1.6f : 1.13f);
+        return us + extra < p.us * (fast ? 1.12f : r == 0 ? 0.95f : r <= 16 ? 1.05f : 0.92f);
+    }
+    // Up to 64 tokens, and where very many meet few channels, against the time of 2 x 2 waves a tile, the tiled kernel's only form when
+    // this line was fitted; four wave groups are ahead of that, but in a block of 64 tokens by less than 10 % (4096 x 12288: 15.3 here, 13.9;
+    // 8192 x 28672, 24 tokens: 35.4, 34.6).  In the exact mode; one pass takes an un-split tiled launch down by 13 to 20 %, this one, which
+    // waits for memory, by 3 to 5 (8192 x 28672, 32 tokens: 29.8 against 33.9; 6144 x 24576, 24 tokens: 22.1 against 24.1), and the
+    // low-rank correction costs the tiled kernel half as much (3072 x 20000, 32 tokens, rank 8: 18.7 against 19.1).  Beyond 16384 rows this
+    // kernel is slower than its estimate (28672 x 8192, 32 tokens: 37.3 against 38.2 us; one pass 33.3 against 37.7).  Many tokens on
+    // few channels go to the tiled kernel by the activations they fetch (11008 x 128, 2048 tokens: 19.2 against 34.2).
+    bool split;
+    float bar = two_by_two_us(M, L, split);
     if (L.nkt > 128) bar *= fast ? 0.87f : 0.97f;
-    else if (p.ksplit == 1) bar *= fast ? 0.87f : r > 0 ? 0.95f : 1.0f;
+    else if (!split) bar *= fast ? 0.87f : r > 0 ? 0.95f : 1.0f;
     else if (fast && extra > 0.0f) bar *= 0.93f;  // 11008 x 1024, 1024 tokens: 22.6 against 24.4
     return us + extra < bar;
 }

@@ -10,12 +10,12 @@
 // instruction's scale operand -- the FP4 -> FP8 alignment is done by the
 // matrix core, no unpack and no multiply).
 //
-// Two waves share a SIMD so that one wave's LDS reads and barrier waits hide
-// behind the other's matrix instructions: two of an 8-wave workgroup that has
-// the compute unit to itself (three LDS stages), or one from each of two 4-wave
-// workgroups (two stages each), whose prologues, epilogues and barriers then
-// fall at different times, or -- small tiles, few of them -- one from each of
-// two wave groups of a workgroup that take the k-tiles in turn.  A stage
+// Two or three waves share a SIMD so that one wave's LDS reads and barrier waits hide
+// behind the others' matrix instructions: one from each of three 4-wave workgroups
+// (up to 128 x 128 and 64 x 256 tiles, two or three LDS stages) or of two (128 x 256, two stages), whose
+// prologues, epilogues and barriers then fall at different times, two of an 8-wave
+// workgroup that has the compute unit to itself, or -- small tiles, few of them -- one
+// from each wave group of a workgroup that takes the k-tiles in turn.  A stage
 // is filled by LDS-direct loads (global_load_lds_dwordx4: every lane names a
 // 16 B chunk in global memory, the wave's 64 chunks land in one contiguous
 // 1 KB block of LDS), NSTAGE - 1 k-steps ahead of its use: no staging
@@ -112,10 +112,11 @@ __device__ inline void wait_loads_then_barrier()
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// KG wave groups of WAVES_M x WAVES_N waves share the tile and take the k-tiles in turn (k-tile kt by group
-// kt % KG), each with its own operands in LDS and its own accumulators; the groups' sums meet in LDS in the
-// epilogue.  KG = 2 gives the small tile two waves per SIMD where the tile count leaves one workgroup per
-// compute unit.  GT = threads of one group; the per-group quantities below are written in terms of it.
+// KG wave groups of WAVES_M x WAVES_N waves share the tile and take the k-tiles in turn, each with its own operands in LDS
+// and its own accumulators; the groups' sums meet in LDS in the epilogue, whose rows (and columns) they then share.
+// This gives a small tile two waves per SIMD where the tile count leaves one workgroup per compute unit: two groups of 2 x 2
+// waves, or, four of 2 x 1, whose waves span the tile's whole width, so that nobody splits the same activations twice.
+// GT = threads of one group; the per-group quantities below are written in terms of it.
 template <int WTM, int WTN, int WAVES_M, int WAVES_N, int NSTAGE_, int KG_ = 1, int WB = 4>
 struct TileCfg {
     static_assert(WB == 4 || WB == 8, "weight bits: E2M1 or E4M3");
@@ -124,25 +125,26 @@ struct TileCfg {
     static constexpr int GT = 64 * WAVES_M * WAVES_N;
     static constexpr int THREADS = GT * KG;
     static constexpr int BM = WAVES_M * WTM * 16, BN = WAVES_N * WTN * 16;
-    static constexpr int A_BYTES = BM * 128, B_BYTES = BN / 16 * B_STRIP;
+    static constexpr int A_BYTES = BM * 128;
+    static constexpr int B_CHUNKS = (BN / 16 * B_STRIP + 16 * GT - 1) / (16 * GT);  // 16 B chunks per thread; past the last strip it is loaded again
+    static constexpr int B_BYTES = B_CHUNKS * 16 * GT;
     static constexpr int E_BYTES = GT * 4;                    // one exponent dword per output channel (first BN used)
     static constexpr int SUB = A_BYTES + B_BYTES + E_BYTES;   // one k-tile's operands
     static constexpr int STAGE = SUB * KG;
     static constexpr int NSTAGE = NSTAGE_;
     static_assert(NSTAGE >= 2 && NSTAGE <= 8, "the loop keeps NSTAGE - 1 k-tiles in flight behind the one it multiplies");
     static constexpr int A_CHUNKS = A_BYTES / 16 / GT;  // 16 B chunks per thread
-    static constexpr int B_CHUNKS = B_BYTES / 16 / GT;
-    static_assert(A_BYTES % (16 * GT) == 0 && B_BYTES % (16 * GT) == 0, "tile / thread mismatch");
+    static_assert(A_BYTES % (16 * GT) == 0, "tile / thread mismatch");
     static_assert(BN <= GT, "one exponent dword per thread");
-    static_assert(KG == 1 || KG == 2, "one or two wave groups");
+    static_assert(KG == 1 || KG == 2 || KG == 4, "one, two or four wave groups");
     static_assert((NSTAGE - 1) * (A_CHUNKS + B_CHUNKS + 1) <= 63, "outstanding loads must fit the 6-bit load counter");
     static_assert(NSTAGE * STAGE <= 160 * 1024, "stages exceed the LDS of a compute unit");
 };
 
-// Two waves per SIMD in every configuration (8-wave workgroups alone on a compute unit, 4-wave
-// workgroups in pairs): 256 registers per lane.
-template <int WTM, int WTN, int WAVES_M, int WAVES_N, int NSTAGE, int KG, bool EXACT, int WB = 4>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_tile(
+// OCC waves per SIMD: 8-wave workgroups alone on a compute unit or 4-wave workgroups in pairs, 256 registers per lane, or
+// three 4-wave workgroups, 168 registers.
+template <int WTM, int WTN, int WAVES_M, int WAVES_N, int NSTAGE, int KG, bool EXACT, int WB = 4, int OCC = 2>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_waves_per_eu(OCC, OCC))) void k_gemm_tile(
     const uint8_t* __restrict__ Xq, const float* __restrict__ sx, int64_t M, const uint8_t* __restrict__ blob,
     BlobLayout L, Lorc lorc, void* __restrict__ Y, int64_t ldy, int out_dtype, int tiles_m, int tiles_n, int ksplit,
     int kslice, float* __restrict__ partial)
@@ -186,9 +188,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
     const int64_t strip0 = (int64_t)tn * (C::BN / 16);
     const int nkt_all = (int)L.nkt;                 // k-tiles of the whole K (the packed layout's stride)
     const int kt_first = slice * kslice;            // this workgroup's first k-tile
-    const int nkt_wg = min(kslice, nkt_all - kt_first);  // and how many it multiplies (>= 1; a multiple of KG: the launcher's duty)
-    const int kt0 = kt_first + kgrp;                // this wave group's first k-tile; its local step kt is k-tile kt0 + KG * kt
-    const int nkt = nkt_wg / KG;                    // steps of every group
+    const int nkt_wg = min(kslice, nkt_all - kt_first);  // and how many it multiplies (>= 1)
+    const int nkt = (nkt_wg + KG - 1) / KG;         // steps of every group
+    // Where the k-tiles do not come out even, the first groups have none in step 0: zeros for activations.
+    const int missing = KG == 1 ? 0 : nkt * KG - nkt_wg;
+    const int kt0 = kt_first + kgrp - missing;      // this wave group's first k-tile; its local step kt is k-tile kt0 + KG * kt
+    const bool no_first = KG > 1 && kgrp < missing;
 
     // ---- load addresses: uniform base pointers plus 32-bit per-lane offsets.  Rows past M
     // and strips past the last one are clamped to the last valid one: what they produce is
@@ -217,7 +222,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
     for (int i = 0; i < C::B_CHUNKS; ++i) {
         const int q = wave + (kGT / 64) * i;  // 1 KB block q of the tile's weights
         const int strip = WB == 8 ? q >> 1 : q, half = WB == 8 ? q & 1 : 0;
-        b_strip[i] = min(strip0 + strip, L.nstrips - 1) * nkt_all * C::B_STRIP + half * 1024;
+        b_strip[i] = min(strip0 + min(strip, C::BN / 16 - 1), L.nstrips - 1) * nkt_all * C::B_STRIP + half * 1024;
     }
     // exponent dwords, [strip][quad][column] in memory: thread t stages the dword of column
     // t % BN of the tile; it lands in LDS as [column] and every lane later picks its own.
@@ -236,7 +241,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
     const bool small_groups = L.gsb < 4;
     const int gq = max(1, L.gsb >> 2);
     auto group_of = [&](const GroupCursor& c, int kt, int b) {
-        return small_groups ? ((kt * 4 + b) >> L.gsb_shift) : c.g;
+        const int g = small_groups ? ((kt * 4 + b) >> L.gsb_shift) : c.g;
+        return KG == 1 ? g : max(g, 0);
     };
     auto advance = [&](GroupCursor& c) {  // to the group's next k-tile, KG k-tiles further on
 #pragma unroll
@@ -253,11 +259,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
     // t-th load of k-tile kt into LDS stage `stage`
     auto side_load = [&](int t, int kt, int stage, const GroupCursor& c) __attribute__((always_inline)) {
         const uint32_t st = (uint32_t)stage * C::STAGE;
-        if (t < C::A_CHUNKS) lds_load16(a_base + (kt0 + KG * kt) * 128, a_off[t], st + a_dst + t * (kGT / 64) * 1024);
+        const int ktile = KG == 1 ? kt0 + kt : max(kt0 + KG * kt, 0);  // below 0: a group without a k-tile in step 0, any will do
+        if (t < C::A_CHUNKS) lds_load16(a_base + ktile * 128, a_off[t], st + a_dst + t * (kGT / 64) * 1024);
         else if (t < C::A_CHUNKS + C::B_CHUNKS)
-            lds_load16(b_base + b_strip[t - C::A_CHUNKS] + (int64_t)(kt0 + KG * kt) * C::B_STRIP, b_lane, st + b_dst + (t - C::A_CHUNKS) * (kGT / 64) * 1024);
+            lds_load16(b_base + b_strip[t - C::A_CHUNKS] + (int64_t)ktile * C::B_STRIP, b_lane, st + b_dst + (t - C::A_CHUNKS) * (kGT / 64) * 1024);
         else  // the dword holds 4 stored groups; the four 32-blocks of a k-tile always share one dword
-            lds_load4(e_base + __builtin_amdgcn_readfirstlane((group_of(c, kt0 + KG * kt, 0) >> 2) * 64), e_off, st + e_dst);
+            lds_load4(e_base + __builtin_amdgcn_readfirstlane((group_of(c, ktile, 0) >> 2) * 64), e_off, st + e_dst);
     };
 
     v4f acc[WTM][WTN];
@@ -279,7 +286,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
     uint32_t e_cur[WTN];  // their exponent dwords (raw until the first use in a step)
     v8i fx, fy, fz;
     u32x4 ta, tb;         // the activation fragment in flight
-    GroupCursor cur_comp = {kt0 / gq, kt0 % gq}, cur_load = cur_comp;  // at this workgroup's first k-tile
+    const int g0 = kt0 >= 0 ? kt0 / gq : -((gq - 1 - kt0) / gq);  // rounded down
+    GroupCursor cur_comp = {g0, kt0 - g0 * gq}, cur_load = cur_comp;  // at this wave group's first k-tile
     // per-lane LDS addresses inside stage 0 (the stage offset is added per step)
     const uint32_t a_addr0 = lds0 + (wm * WTM) * 2048 + col * 128 + ((lb ^ (col & 7)) * 16);
     const uint32_t a_addr1 = lds0 + (wm * WTM) * 2048 + col * 128 + ((lb ^ (col & 7) ^ 4) * 16);
@@ -419,8 +427,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
         constexpr int TILE = decltype(t_tag)::value;
         if (TILE < nkt) {
             if constexpr (TILE > 0) advance(cur_load);
+            if (TILE == 0 && KG > 1 && no_first) {  // fewer loads of tile 0 than the waits below allow for: they wait for all of them
 #pragma unroll
-            for (int t = 0; t < NSIDE; ++t) side_load(t, TILE, TILE, cur_load);
+                for (int t = 0; t < C::A_CHUNKS; ++t)
+                    *reinterpret_cast<u32x4*>(smem + kgrp * C::SUB + wave * 1024 + t * (kGT / 64) * 1024 + lane * 16) = (u32x4){0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int t = C::A_CHUNKS; t < NSIDE; ++t) side_load(t, TILE, TILE, cur_load);
+            } else {
+#pragma unroll
+                for (int t = 0; t < NSIDE; ++t) side_load(t, TILE, TILE, cur_load);
+            }
         }
     });
     if (nkt >= NSTAGE) advance(cur_load);
@@ -478,30 +494,42 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
     // Each wave therefore passes its 16 x (16*WTN) slabs through a private LDS patch (row stride
     // 16*WTN + 4 floats: the four row groups of a store land on disjoint banks, rows stay 16 B
     // aligned) and writes them out as 16 B per lane, whole rows of the slab at a time.
-    constexpr int SLAB_N = 16 * WTN, SLAB_LD = SLAB_N + 4;
+    // With several wave groups each takes a part of the rows (and, four, of the columns) of its wave's blocks: EI x EJ from block
+    // (ei0, ej0) on.
+    constexpr int EI = KG == 1 ? WTM : WTM / 2, EJ = KG == 4 ? WTN / 2 : WTN;
+    static_assert(KG == 1 || WTM % 2 == 0, "rows shared by the wave groups");
+    static_assert(KG != 4 || WTN % 2 == 0, "columns shared by the wave groups");
+    const int ei0 = KG == 1 ? 0 : (KG == 2 ? kgrp : kgrp >> 1) * EI, ej0 = KG == 4 ? (kgrp & 1) * EJ : 0;
+    constexpr int SLAB_N = 16 * EJ, SLAB_LD = SLAB_N + 4;
     static_assert(C::THREADS / 64 * 16 * SLAB_LD * 4 <= C::NSTAGE * C::STAGE, "epilogue patch does not fit the stages");
+    v4f out[EI][EJ];
     __syncthreads();  // every wave is done reading the stages
-    if constexpr (KG == 2) {  // the second wave group hands its sums over: acc = group 0 + group 1, a fixed order
-        static_assert(WTM * WTN * kGT * 16 <= C::NSTAGE * C::STAGE, "hand-over area does not fit the stages");
+    if constexpr (KG == 1) {
+#pragma unroll
+        for (int i = 0; i < EI; ++i)
+#pragma unroll
+            for (int j = 0; j < EJ; ++j) out[i][j] = acc[i][j];
+    } else {
+        static_assert(KG * WTM * WTN * kGT * 16 <= C::NSTAGE * C::STAGE, "hand-over area does not fit the stages");
         v4f* comb = reinterpret_cast<v4f*>(smem);
-        if (kgrp == 1) {
 #pragma unroll
-            for (int i = 0; i < WTM; ++i)
+        for (int i = 0; i < WTM; ++i)
 #pragma unroll
-                for (int j = 0; j < WTN; ++j) comb[(i * WTN + j) * kGT + tid] = acc[i][j];
-        }
+            for (int j = 0; j < WTN; ++j) comb[((kgrp * WTM + i) * WTN + j) * kGT + tid] = acc[i][j];
         __syncthreads();
-        if (kgrp == 0) {
 #pragma unroll
-            for (int i = 0; i < WTM; ++i)
+        for (int i = 0; i < EI; ++i)
 #pragma unroll
-                for (int j = 0; j < WTN; ++j) acc[i][j] += comb[(i * WTN + j) * kGT + tid];
-        }
+            for (int j = 0; j < EJ; ++j) {  // the groups' sums in order
+                out[i][j] = comb[((ei0 + i) * WTN + ej0 + j) * kGT + tid];
+#pragma unroll
+                for (int g = 1; g < KG; ++g) out[i][j] += comb[((g * WTM + ei0 + i) * WTN + ej0 + j) * kGT + tid];
+            }
         __syncthreads();  // the area is reused below
     }
-    float* patch = reinterpret_cast<float*>(smem) + wave * (16 * SLAB_LD);
+    float* patch = reinterpret_cast<float*>(smem) + wg_wave * (16 * SLAB_LD);
     const float* colscale = reinterpret_cast<const float*>(blob + L.off_colscale);
-    const int64_t n_wave = (strip0 + wn * WTN) * 16;
+    const int64_t n_wave = (strip0 + wn * WTN + ej0) * 16, m_wave = m0 + (wm * WTM + ei0) * 16;
     // With a K-split the workgroup hands its raw float32 sums to slice `slice` of the workspace
     // ([ksplit][M][Np]); scales and LoRC are applied by the kernel that adds the slices up.
     const bool raw = ksplit > 1;
@@ -510,9 +538,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
         ldy = L.Np;
         out_dtype = 0;
     }
-    float cn[WTN];
+    float cn[EJ];
 #pragma unroll
-    for (int j = 0; j < WTN; ++j) cn[j] = raw ? 1.0f : colscale[min(n_wave + j * 16 + col, L.Np - 1)];
+    for (int j = 0; j < EJ; ++j) cn[j] = raw ? 1.0f : colscale[min(n_wave + j * 16 + col, L.Np - 1)];
     // LoRC: T . V on the float32 matrix cores, on top of the scaled sums (each output is a chain of fused multiply-adds, in
     // binary32 as before).  The tile's rows of T and columns of V go through LDS in blocks of at most kRanks ranks, T turned
     // round so that the sixteen rows of an operand lie side by side; ranks past r are zero on both sides.  Four ranks are one
@@ -523,14 +551,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
     constexpr int LDT = C::BM + 8, LDV = C::BN + 8;  // the four ranks of an operand spread over all LDS banks
     static_assert(kRanks * (LDT * 4 + LDV * 2) <= C::NSTAGE * C::STAGE, "LoRC factors do not fit the stages");
     const int rk = raw ? 0 : lorc.r;
-    if (!raw && (KG == 1 || kgrp == 0)) {
+    if (!raw) {
 #pragma unroll
-        for (int i = 0; i < WTM; ++i)
+        for (int i = 0; i < EI; ++i)
 #pragma unroll
             for (int rg = 0; rg < 4; ++rg) {
-                const float sm = sx[min(m0 + (wm * WTM + i) * 16 + 4 * lb + rg, M - 1)];
+                const float sm = sx[min(m_wave + i * 16 + 4 * lb + rg, M - 1)];
 #pragma unroll
-                for (int j = 0; j < WTN; ++j) acc[i][j][rg] *= sm * cn[j];
+                for (int j = 0; j < EJ; ++j) out[i][j][rg] *= sm * cn[j];
             }
     }
     for (int q0 = 0; q0 < rk; q0 += kRanks) {
@@ -567,37 +595,34 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
             }
         }
         __syncthreads();
-        if (KG == 1 || kgrp == 0) {
-            const float* tp = Ts + lb * LDT + wm * WTM * 16 + col;
-            const uint16_t* vp = Vs + lb * LDV + wn * WTN * 16 + col;
-            for (int st = 0; st < steps; ++st) {
-                float tf[WTM], vf[WTN];
+        const float* tp = Ts + lb * LDT + (wm * WTM + ei0) * 16 + col;
+        const uint16_t* vp = Vs + lb * LDV + (wn * WTN + ej0) * 16 + col;
+        for (int st = 0; st < steps; ++st) {
+            float tf[EI], vf[EJ];
 #pragma unroll
-                for (int i = 0; i < WTM; ++i) tf[i] = tp[4 * st * LDT + 16 * i];
+            for (int i = 0; i < EI; ++i) tf[i] = tp[4 * st * LDT + 16 * i];
 #pragma unroll
-                for (int j = 0; j < WTN; ++j) vf[j] = half_bits_to_f32(vp[4 * st * LDV + 16 * j]);
+            for (int j = 0; j < EJ; ++j) vf[j] = half_bits_to_f32(vp[4 * st * LDV + 16 * j]);
 #pragma unroll
-                for (int i = 0; i < WTM; ++i)
+            for (int i = 0; i < EI; ++i)
 #pragma unroll
-                    for (int j = 0; j < WTN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(tf[i], vf[j], acc[i][j], 0, 0, 0);
-            }
+                for (int j = 0; j < EJ; ++j) out[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(tf[i], vf[j], out[i][j], 0, 0, 0);
         }
         __syncthreads();  // the area is rewritten by the next block, or by the patches
     }
-    if (KG == 2 && kgrp != 0) return;  // no barrier below: the first group alone writes the tile out
     constexpr int LPR = SLAB_N / 4;   // lanes per slab row when each lane carries 4 columns
-    constexpr int RPI = 64 / LPR;     // slab rows per store instruction (lanes beyond RPI * LPR idle when 64 % LPR != 0)
-    static_assert(RPI >= 1 && 16 % RPI == 0, "slab rows per store instruction");
+    constexpr int RPI = 64 / LPR >= 8 ? 8 : 64 / LPR >= 4 ? 4 : 64 / LPR >= 2 ? 2 : 1;  // slab rows per store instruction (lanes beyond RPI * LPR idle)
+    static_assert(LPR <= 64, "a slab row per store instruction");
     const int srow = lane / LPR, scol = (lane % LPR) * 4;
     const bool lane_stores = lane < RPI * LPR;
     const bool vec_ok = (ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
 #pragma unroll
-    for (int i = 0; i < WTM; ++i) {
-        const int64_t m_slab = m0 + (wm * WTM + i) * 16;
+    for (int i = 0; i < EI; ++i) {
+        const int64_t m_slab = m_wave + i * 16;
 #pragma unroll
-        for (int j = 0; j < WTN; ++j)
+        for (int j = 0; j < EJ; ++j)
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) patch[(4 * lb + rg) * SLAB_LD + j * 16 + col] = acc[i][j][rg];
+            for (int rg = 0; rg < 4; ++rg) patch[(4 * lb + rg) * SLAB_LD + j * 16 + col] = out[i][j][rg];
 #pragma unroll
         for (int t = 0; t < 16 / RPI; ++t) {
             const int r = lane_stores ? t * RPI + srow : 0;
@@ -689,7 +714,7 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
 }
 
 
-template <int WTM, int WTN, int WAVES_M, int WAVES_N, int NSTAGE, int KG, bool EXACT, int WB = 4>
+template <int WTM, int WTN, int WAVES_M, int WAVES_N, int NSTAGE, int KG, bool EXACT, int WB = 4, int OCC = 2>
 hipError_t launch_cfg(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob, const BlobLayout& L, Lorc lorc,
                       void* Y, int64_t ldy, int out_dtype, int ksplit, int kslice, float* partial, hipStream_t s)
 {
@@ -698,7 +723,7 @@ hipError_t launch_cfg(const uint8_t* Xq, const float* sx, int64_t M, const uint8
     const int units = tiles_m * tiles_n * ksplit;
     const int per = (units + 7) / 8;
     const size_t smem = C::NSTAGE * C::STAGE;
-    auto kern = k_gemm_tile<WTM, WTN, WAVES_M, WAVES_N, NSTAGE, KG, EXACT, WB>;
+    auto kern = k_gemm_tile<WTM, WTN, WAVES_M, WAVES_N, NSTAGE, KG, EXACT, WB, OCC>;
     static OnceStatus attr;  // raising the dynamic LDS limit is a per-function, per-process setting (one flag per instantiation)
     if (hipError_t e = run_once(attr, [&] {
             return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -715,52 +740,39 @@ template <bool EXACT>
 hipError_t launch_pick(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob, const BlobLayout& L, Lorc lorc,
                        void* Y, int64_t ldy, int out_dtype, void* workspace, hipStream_t s)
 {
-    TilePlan p = effective_tile_plan(M, L.Np, L.nkt);
-    if (workspace == nullptr) { p.ksplit = 1; p.kslice = (int)L.nkt; }  // no room for partial tiles: one slice
+    const TilePlan p = effective_tile_plan(M, L.Np, L.nkt, EXACT ? 0 : 1, 4, workspace != nullptr);
     float* ws = static_cast<float*>(workspace);
-#define ZQ_TILE(WTM, WTN, WM, WN, NST, KG) \
-    return launch_cfg<WTM, WTN, WM, WN, NST, KG, EXACT>(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, p.ksplit, p.kslice, ws, s)
-    if (p.bm == 256) ZQ_TILE(4, 8, 4, 2, 3, 1);
-    if (p.bm == 128 && p.bn == 256) ZQ_TILE(4, 8, 2, 2, 2, 1);
-    if (p.bm == 128 && p.bn == 192) ZQ_TILE(4, 6, 2, 2, 2, 1);
-    if (p.bm == 128) ZQ_TILE(4, 4, 2, 2, 3, 1);
-    // 64-row tiles.  Two wave groups need an even number of k-tiles in every slice.
-    if (p.ksplit >= 2 && !p.forced) {  // half as many slices (of even length), two wave groups each: half the partial tiles to add up
-        const int64_t tiles = ((M + 63) / 64) * ((L.Np + 127) / 128);
-        const int want = (p.ksplit + 1) / 2;
-        int kslice = (int)((L.nkt + want - 1) / want);
-        kslice += kslice & 1;
-        const int ksplit = (int)((L.nkt + kslice - 1) / kslice);
-        const int tail = (int)L.nkt - (ksplit - 1) * kslice;
-        if (tiles * ksplit <= 256 && tail > 0 && tail % 2 == 0) { p.ksplit = ksplit; p.kslice = kslice; p.kg = 2; }
+#define ZQ_TILE(WTM, WTN, WM, WN, NST, KG, OCC) \
+    return launch_cfg<WTM, WTN, WM, WN, NST, KG, EXACT, 4, OCC>(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, p.ksplit, p.kslice, ws, s)
+    if (p.bm == 256) ZQ_TILE(4, 8, 4, 2, 3, 1, 2);
+    if (p.bm == 128 && p.bn == 256) ZQ_TILE(4, 8, 2, 2, 2, 1, 2);
+    if (p.bm == 128 && p.bn == 192) ZQ_TILE(4, 6, 2, 2, 2, 1, 2);
+    if (p.bm == 128) ZQ_TILE(2, 8, 4, 1, 2, 1, 3);
+    if (p.kg == 4) {
+        if (p.bn == 64) ZQ_TILE(2, 4, 2, 1, 3, 4, 2);
+        if (p.bn == 96) ZQ_TILE(2, 6, 2, 1, 2, 4, 2);
+        ZQ_TILE(2, 8, 2, 1, 2, 4, 2);
     }
-    const bool even_slices = p.kslice % 2 == 0 && ((int)L.nkt - (p.ksplit - 1) * p.kslice) % 2 == 0;
-    const bool two_groups = p.kg == 2 && even_slices;
-    if (p.bn == 256) { if (two_groups) ZQ_TILE(2, 8, 2, 2, 3, 2); ZQ_TILE(2, 8, 2, 2, 3, 1); }
-    if (p.bn == 192) { if (two_groups) ZQ_TILE(2, 6, 2, 2, 3, 2); ZQ_TILE(2, 6, 2, 2, 3, 1); }
-    if (two_groups) ZQ_TILE(2, 4, 2, 2, 3, 2);
-    ZQ_TILE(2, 4, 2, 2, 3, 1);
+    if (p.bn == 256) { if (p.kg == 2) ZQ_TILE(2, 8, 2, 2, 3, 2, 2); ZQ_TILE(2, 8, 2, 2, 2, 1, 3); }
+    if (p.bn == 192) { if (p.kg == 2) ZQ_TILE(2, 6, 2, 2, 3, 2, 2); ZQ_TILE(2, 6, 2, 2, 2, 1, 3); }
+    if (p.kg == 2) ZQ_TILE(2, 4, 2, 2, 3, 2, 2);
+    ZQ_TILE(2, 4, 2, 2, 3, 1, 3);
 #undef ZQ_TILE
 }
 
-// E4M3 weights: 128 x 128 tiles, two workgroups per compute unit, once there is more than one of them per compute
-// unit; below that 64 x 128 tiles, with two wave groups while at most one workgroup per compute unit is left (and
-// the k-tiles can be dealt out in pairs).  No K-split: the W8A8 entry point takes no workspace.
+// E4M3 weights: 128 x 128 tiles, two workgroups per compute unit, or 64 x 128 tiles, three of them, or one with two wave
+// groups.  No K-split: the W8A8 entry point takes no workspace.
 template <bool EXACT>
 hipError_t launch_pick_w8(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob, const BlobLayout& L, Lorc lorc,
                           void* Y, int64_t ldy, int out_dtype, hipStream_t s)
 {
-    auto tiles = [&](int bm) { return ((M + bm - 1) / bm) * ((L.Np + 127) / 128); };
-    int bm = tiles(128) > 256 ? 128 : 64;
-    int kg = bm == 64 && tiles(64) <= 256 ? 2 : 1;
-    const TilePlan f = effective_tile_plan(M, L.Np, L.nkt);
-    if (f.forced && f.bn == 128 && (f.bm == 64 || f.bm == 128)) { bm = f.bm; kg = f.bm == 64 ? f.kg : 1; }
-    if (L.nkt & 1) kg = 1;
-#define ZQ_TILE8(WTM, NST, KG) \
-    return launch_cfg<WTM, 4, 2, 2, NST, KG, EXACT, 8>(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, 1, (int)L.nkt, nullptr, s)
-    if (bm == 128) ZQ_TILE8(4, 2, 1);
-    if (kg == 2) ZQ_TILE8(2, 3, 2);
-    ZQ_TILE8(2, 3, 1);
+    const TilePlan p = effective_tile_plan(M, L.Np, L.nkt, EXACT ? 0 : 1, 8, false);
+#define ZQ_TILE8(WTM, NST, KG, OCC) \
+    return launch_cfg<WTM, 4, 2, 2, NST, KG, EXACT, 8, OCC>(Xq, sx, M, blob, L, lorc, Y, ldy, out_dtype, 1, (int)L.nkt, nullptr, s)
+    if (p.bm == 128) ZQ_TILE8(4, 2, 1, 2);
+    if (p.kg == 2) ZQ_TILE8(2, 3, 2, 2);
+    if (p.occ == 2) ZQ_TILE8(2, 3, 1, 2);
+    ZQ_TILE8(2, 2, 1, 3);
 #undef ZQ_TILE8
 }
 
@@ -779,93 +791,123 @@ hipError_t launch_splitk_reduce(const float* partial, int slices, int64_t M, con
 
 bool gemm_tile_supported(int64_t M, const BlobLayout& L) { return M > 16 && L.N >= 64; }
 
-// ---- planning.  Measured on LLaMA-7B / 13B / 70B and OPT shapes (exact accumulation), the time of a launch is
-// close to  3 + t * (e + s * k-tiles)  microseconds, t = the most tiles any compute unit gets: e is a tile's
-// prologue and epilogue, s its k-step.  Small tiles cost more per output (plain vector work per matrix
-// instruction grows as a wave's tile narrows, and it takes matrix-pipe time), large tiles come in coarser
-// rounds.  A compute unit that holds a single four-wave workgroup has one wave per SIMD and nothing to fill
-// its stalls with: 1.3 times slower.  The planner takes the cheapest.
+// ---- planning.  The time of a launch is close to  3 + f(t) (e + s k-tiles)  microseconds, t = the most tiles any compute unit
+// gets: e is a tile's prologue and epilogue, s its k-step, and f(t) = t but for one and two tiles, which leave a compute unit
+// that holds two or three workgroups of the kind partly idle.  What tells the kinds apart: a small tile fetches more bytes
+// per matrix instruction (measured, tiles of 64 rows move about 43 KB/us per compute unit whatever their width) and splits its
+// activations for fewer columns; large tiles come in coarser rounds.  Three workgroups per compute unit, where the registers
+// allow, are 5 to 10 % ahead of two with a stage more (2048 x 5120 x 13824: 64 x 256 tiles 180 -> 174 us, 128 x 256 183; 1500 x 4096 x
+// 4096: 64 x 128 43.0 -> 40.5; one pass, 637 x 1408 x 15488: 22.7 -> 19.9).  Four wave groups, each over the tile's whole width, let a
+// compute unit take 64 x 64 tiles, whose k-step 2 x 2 waves would spend on splitting (256 x 11008 x 4096: 64 x 128 two groups 39.3 us,
+// 64 x 64 four groups 28.9 un-split; 100 x 4096 x 4096: 17.9, 12.6).
+// Least-squares fit (relative error) per kind and mode to 5800 timings with weights beyond the last-level cache, sixteen shapes with 9 ...
+// 224 k-tiles and 24 ... 4096 tokens: 4 % rms in the exact mode, 9 % in one pass; the cheapest kind by it is within 0.2 % (0.4 %) of the
+// fastest on average, 4 % (10 %) at worst.  E4M3 weights: 0.2 % (0.6 %), 9 % (21 %).
+struct TileCost {
+    float e, s, f1, f2;
+};
 struct TileKind {
-    int bm, bn, kg;
-    float e, s;
+    int bm, bn, kg, occ;
+    TileCost cost[2];  // exact, one pass
 };
 constexpr TileKind kTileKinds[] = {
-    // least-squares fit (relative error) to 527 timings: seven weight shapes with 16 ... 224 k-tiles, 64 ... 4096 tokens
-    {64, 128, 2, 3.8f, 0.368f},   // two wave groups: one workgroup per compute unit, so at most 256 tiles
-    {64, 192, 2, 6.0f, 0.477f},
-    {64, 256, 2, 6.8f, 0.584f},
-    {64, 128, 1, 2.1f, 0.368f},
-    {64, 192, 1, 3.3f, 0.464f},
-    {64, 256, 1, 4.5f, 0.549f},
-    {128, 128, 1, 4.3f, 0.632f},
-    {128, 192, 1, 6.6f, 0.778f},
-    {128, 256, 1, 8.6f, 0.928f},
-    {256, 256, 1, 12.4f, 2.009f},
+    {64, 64, 4, 1, {{2.92f, 0.229f, 0.94f, 2.00f}, {2.46f, 0.174f, 0.91f, 1.94f}}},
+    {64, 96, 4, 1, {{3.56f, 0.298f, 0.95f, 1.99f}, {2.64f, 0.266f, 0.94f, 1.94f}}},
+    {64, 128, 4, 1, {{4.15f, 0.341f, 0.93f, 1.98f}, {2.95f, 0.316f, 0.94f, 1.95f}}},
+    {64, 128, 2, 1, {{3.34f, 0.395f, 0.94f, 2.03f}, {2.87f, 0.267f, 0.90f, 1.97f}}},
+    {64, 192, 2, 1, {{4.76f, 0.509f, 0.95f, 2.00f}, {4.41f, 0.329f, 0.89f, 1.89f}}},
+    {64, 256, 2, 1, {{5.38f, 0.628f, 0.92f, 1.93f}, {4.96f, 0.429f, 0.88f, 1.88f}}},
+    {64, 128, 1, 3, {{1.32f, 0.363f, 1.38f, 2.10f}, {0.94f, 0.236f, 1.44f, 2.03f}}},
+    {64, 192, 1, 3, {{1.77f, 0.485f, 1.46f, 2.05f}, {0.77f, 0.360f, 1.98f, 2.19f}}},
+    {64, 256, 1, 3, {{2.32f, 0.587f, 1.30f, 2.02f}, {0.86f, 0.445f, 1.71f, 1.99f}}},
+    {128, 128, 1, 3, {{2.28f, 0.572f, 1.30f, 2.03f}, {0.98f, 0.427f, 1.72f, 1.99f}}},
+    {128, 192, 1, 2, {{4.75f, 0.831f, 1.18f, 1.97f}, {3.01f, 0.592f, 1.29f, 1.81f}}},
+    {128, 256, 1, 2, {{5.28f, 1.026f, 1.15f, 1.95f}, {3.86f, 0.691f, 1.18f, 1.88f}}},
+    {256, 256, 1, 1, {{8.38f, 2.227f, 0.89f, 1.92f}, {8.75f, 1.315f, 0.84f, 1.88f}}},
+};
+constexpr TileKind kTileKindsW8[] = {
+    {64, 128, 2, 1, {{4.07f, 0.457f, 0.95f, 1.99f}, {3.45f, 0.351f, 0.98f, 1.99f}}},
+    {64, 128, 1, 2, {{1.90f, 0.421f, 1.22f, 1.98f}, {1.67f, 0.322f, 1.27f, 2.06f}}},
+    {64, 128, 1, 3, {{1.33f, 0.419f, 1.79f, 2.18f}, {0.91f, 0.362f, 2.00f, 2.21f}}},
+    {128, 128, 1, 2, {{2.91f, 0.742f, 1.18f, 1.97f}, {2.36f, 0.539f, 1.48f, 1.73f}}},
 };
 
-TilePlan plan_tiles(int64_t M, int64_t Np, int64_t nkt)
+// K slices of a launch whose 64 x 128 tiles fill less than a third of the chip, at least 8 k-steps each (down-projections at
+// small M); ksplit = 1 where they would not have paid against the un-split 64 x 128 tile.  This is what the workspace query
+// answers; whether a launch takes them is decided against all kinds.
+TilePlan plan_slices(int64_t M, int64_t Np, int64_t nkt)
 {
     constexpr int64_t kCUs = 256;  // MI355X
-    auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((Np + bn - 1) / bn); };
-    TilePlan p{64, 128, 1, 1, (int)nkt};
-    // Few output tiles, long K (down-projections at small M): even 64 x 128 tiles fill less than a third of the
-    // chip, so K is cut into slices of at least 8 k-steps.
-    {
-        const int64_t slots = 2 * kCUs, nt = tiles(64, 128);
-        int64_t want = slots / nt;
-        if (want > 16) want = 16;
-        if (want > nkt / 8) want = nkt / 8;
-        if (want >= 3) {
-            // The slices' trip through memory must pay for itself: against the un-split launch (two wave groups, at
-            // most one tile per compute unit here) the split saves K-steps and costs a second kernel and the
-            // partial sums written, read back and summed.  The launch will halve the slice count where two wave
-            // groups can take the halves (launch_pick), which is what is priced.  Measured on K = N = 4096: splitting
-            // wins up to 128 tokens (17.0 against 18.1 us) and loses from 192 on (21.1 against 18.4 at 256), while
-            // K = 11008 gains at every token count that gets here (256 tokens: 29.6 against 38.1 us).
-            const int kslice = (int)((nkt + want - 1) / want), ksplit = (int)((nkt + kslice - 1) / kslice);
-            const float eff = (float)((ksplit + 1) / 2);
-            const float trip_us = (2.0f * eff + 1.0f) * (float)M * (float)Np * 4.0f / 2.5e6f;  // measured: 2.5 TB/s, second launch included
-            const float split_us = 3.8f + 0.368f * (float)nkt / eff + trip_us, unsplit_us = 3.8f + 0.368f * (float)nkt;
-            if (split_us < unsplit_us) {
-                p.kslice = kslice;
-                p.ksplit = ksplit;
-                p.us = 3.0f + split_us;
-                return p;
-            }
+    TilePlan p{64, 128, 1};
+    p.kslice = (int)nkt;
+    const int64_t slots = 2 * kCUs, nt = ((M + 63) / 64) * ((Np + 127) / 128);
+    int64_t want = slots / nt;
+    if (want > 16) want = 16;
+    if (want > nkt / 8) want = nkt / 8;
+    if (want < 3) return p;
+    // The slices' trip through memory must pay for itself: a second kernel, the partial sums written, read back and summed.  The
+    // launch will halve the slice count where that still leaves a workgroup per compute unit, which is what is priced.
+    const int kslice = (int)((nkt + want - 1) / want), ksplit = (int)((nkt + kslice - 1) / kslice);
+    const float eff = (float)((ksplit + 1) / 2);
+    const float trip_us = (2.0f * eff + 1.0f) * (float)M * (float)Np * 4.0f / 2.5e6f;  // measured: 2.5 TB/s, second launch included
+    const float split_us = 3.8f + 0.368f * (float)nkt / eff + trip_us, unsplit_us = 3.8f + 0.368f * (float)nkt;
+    if (split_us < unsplit_us) {
+        p.kslice = kslice;
+        p.ksplit = ksplit;
+        p.us = 3.0f + split_us;
+    }
+    return p;
+}
+
+TilePlan plan_tiles(int64_t M, int64_t Np, int64_t nkt, int accum, int wbits, bool may_split)
+{
+    constexpr int64_t kCUs = 256;  // MI355X
+    TilePlan p{64, 128, 1};
+    p.kslice = (int)nkt;
+    const int mode = accum == 0 ? 0 : 1;
+    auto consider = [&](const TileKind& k) {
+        if (k.bm > 64 && M <= 64) return;
+        const int64_t t = (((M + k.bm - 1) / k.bm) * ((Np + k.bn - 1) / k.bn) + kCUs - 1) / kCUs;
+        const TileCost& c = k.cost[mode];
+        const float us = 3.0f + (t == 1 ? c.f1 : t == 2 ? c.f2 : (float)t) * (c.e + c.s * (float)nkt);
+        if (p.us == 0.f || us < p.us) { p.bm = k.bm; p.bn = k.bn; p.kg = k.kg; p.occ = k.occ; p.us = us; }
+    };
+    if (wbits == 8) {
+        for (const TileKind& k : kTileKindsW8) consider(k);
+        return p;
+    }
+    for (const TileKind& k : kTileKinds) consider(k);
+    if (may_split) {
+        TilePlan q = plan_slices(M, Np, nkt);
+        // The slices' estimate is the exact mode's; one pass takes a third off their k-steps.  Few-token launches in one round are 10 % faster
+        // than their estimate (64 x 4096 x 1024: 13.4 in slices, 11.5 un-split; but 256 x 12032 x 2176: 24.6, 26.2).
+        if (mode != 0) q.us -= 0.9f + 0.101f * (float)nkt / (float)((q.ksplit + 1) / 2);
+        if (q.ksplit > 1 && q.us < p.us * (mode == 0 && M <= 128 ? 0.9f : 1.0f)) {
+            // half as many slices, two wave groups each: half the partial tiles to add up
+            const int64_t tiles = ((M + 63) / 64) * ((Np + 127) / 128);
+            const int want = (q.ksplit + 1) / 2;
+            int kslice = (int)((nkt + want - 1) / want);
+            kslice += kslice & 1;
+            const int ksplit = (int)((nkt + kslice - 1) / kslice);
+            if (tiles * ksplit <= kCUs) { q.ksplit = ksplit; q.kslice = kslice; q.kg = 2; }
+            return q;
         }
     }
-    // Many rounds of large tiles: 128 x 256, two workgroups per compute unit that fill each other's gaps.
-    const int64_t n256 = tiles(256, 256);
-    if (n256 >= kCUs * 3 / 2) { p.bm = 128; p.bn = 256; return p; }
-    float best = 0.f;
-    bool have = false;
-    for (const TileKind& k : kTileKinds) {
-        const int64_t t = tiles(k.bm, k.bn);
-        if (k.kg == 2 && (t > kCUs || (nkt & 1))) continue;
-        if (k.bm > 64 && M <= 64) continue;
-        const float per_cu = (float)((t + kCUs - 1) / kCUs);
-        const bool lone_waves = t <= kCUs && k.kg == 1 && k.bm < 256;
-        const float cost = 3.0f + per_cu * (k.e + k.s * (float)nkt) * (lone_waves ? 1.3f : 1.0f);
-        if (!have || cost < best) { best = cost; have = true; p.bm = k.bm; p.bn = k.bn; p.kg = k.kg; }
-    }
-    p.us = best;
     return p;
 }
 
 bool force_tile_plan(int bm, int bn, int ksplit, int kg)
 {
     if (bm == 0 && bn == 0 && ksplit == 0) { g_forced_plan.store(0); return true; }
-    const bool shape_ok = (bm == 64 && (bn == 128 || bn == 192 || bn == 256)) ||
-                          (bm == 128 && (bn == 128 || bn == 192 || bn == 256)) || (bm == 256 && bn == 256);
-    if (!shape_ok || ksplit < 1 || ksplit > 64 || kg < 1 || kg > 2 || (kg == 2 && bm != 64)) return false;
+    bool shape_ok = false;
+    for (const TileKind& k : kTileKinds) shape_ok = shape_ok || (k.bm == bm && k.bn == bn && k.kg == kg);
+    if (!shape_ok || ksplit < 1 || ksplit > 64) return false;
     g_forced_plan.store((uint32_t)bm | ((uint32_t)bn << 10) | ((uint32_t)ksplit << 20) | ((uint32_t)kg << 28));
     return true;
 }
 
-TilePlan effective_tile_plan(int64_t M, int64_t Np, int64_t nkt)
+static TilePlan forced_plan(uint32_t f, int64_t nkt)
 {
-    const uint32_t f = g_forced_plan.load(std::memory_order_relaxed);
-    if (f == 0) return plan_tiles(M, Np, nkt);
     TilePlan p;
     p.bm = (int)(f & 1023u); p.bn = (int)((f >> 10) & 1023u);
     p.kg = (int)(f >> 28);
@@ -874,6 +916,25 @@ TilePlan effective_tile_plan(int64_t M, int64_t Np, int64_t nkt)
     p.ksplit = (int)((nkt + p.kslice - 1) / p.kslice);
     p.forced = true;
     return p;
+}
+
+TilePlan effective_tile_plan(int64_t M, int64_t Np, int64_t nkt, int accum, int wbits, bool may_split)
+{
+    const uint32_t f = g_forced_plan.load(std::memory_order_relaxed);
+    if (f == 0) return plan_tiles(M, Np, nkt, accum, wbits, may_split);
+    TilePlan p = forced_plan(f, nkt);
+    if (wbits == 8 && (p.bn != 128 || (p.bm != 64 && p.bm != 128) || p.kg == 4)) {  // not a shape of the E4M3 form
+        p = plan_tiles(M, Np, nkt, accum, wbits, false);
+        p.forced = true;
+    }
+    if (!may_split) { p.ksplit = 1; p.kslice = (int)nkt; }
+    return p;
+}
+
+int tile_workspace_slices(int64_t M, int64_t Np, int64_t nkt)
+{
+    const uint32_t f = g_forced_plan.load(std::memory_order_relaxed);
+    return f == 0 ? plan_slices(M, Np, nkt).ksplit : forced_plan(f, nkt).ksplit;
 }
 
 hipError_t launch_gemm_w8_tile(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob, const BlobLayout& L,

@@ -31,14 +31,14 @@ size_t gemm_workspace_need(int64_t M, int64_t K, int64_t N)
         return d.chunks > 1 ? (size_t)d.chunks * (size_t)M * (size_t)Np * sizeof(float) : 0;
     }
     if (N < 64) return 0;
-    const zqfp::TilePlan p = zqfp::effective_tile_plan(M, Np, K / 128);
-    return p.ksplit > 1 ? (size_t)p.ksplit * (size_t)M * (size_t)Np * sizeof(float) : 0;
+    const int slices = zqfp::tile_workspace_slices(M, Np, K / 128);
+    return slices > 1 ? (size_t)slices * (size_t)M * (size_t)Np * sizeof(float) : 0;
 }
 
 // The kernel that serves a GEMM call, with rank r and the caller's workspace or without one (nullptr)
 int gemm_form(int64_t M, const zqfp::BlobLayout& L, int r, int accum, const void* workspace)
 {
-    if (zqfp::gemm_mid_wins(M, L, r, accum)) return ZQFP_FORM_MID;
+    if (zqfp::gemm_mid_wins(M, L, r, accum, workspace != nullptr)) return ZQFP_FORM_MID;
     if (L.wbits == 8) {
         if (zqfp::gemm_w8_decode_supported(M, L)) return ZQFP_FORM_DECODE;
         // the streaming kernel: at most 16 tokens with long K, or up to 32 tokens on a small matrix

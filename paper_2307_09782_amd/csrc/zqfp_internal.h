@@ -222,21 +222,22 @@ __device__ inline int m2_shift(float amax_max, float amax_g)
     return k;
 }
 
-// Tile shape, wave groups and K-split of the tiled GEMM for a problem (the launcher and the workspace query
-// must agree; gemm_tile.hip plans them).  `kg` wave groups of four waves share a tile and take its k-tiles in
-// turn (two waves per SIMD from one workgroup per compute unit).  When even the smallest tiles fill less than a
-// third of the chip (few output channels, long K: down-projections at small M), K is cut into `ksplit` slices
+// Tile shape, wave groups and K-split of the tiled GEMM for a problem (gemm_tile.hip plans them).  `kg` wave groups share a tile
+// and take its k-tiles in turn (two waves per SIMD from one workgroup per compute unit).  When even the smallest tiles fill
+// less than a third of the chip (few output channels, long K: down-projections at small M), K may be cut into `ksplit` slices
 // of `kslice` k-tiles, each tile-slice goes to its own workgroup, and the float32 partial tiles meet in a
-// workspace (ksplit * M * Np floats) that a second kernel sums in fixed order.
+// workspace (at most tile_workspace_slices * M * Np floats) that a second kernel sums in fixed order.
 struct TilePlan {
     int bm, bn;       // tile shape
-    int kg;           // wave groups per workgroup (1 or 2)
-    int ksplit;       // number of K slices (1: none)
-    int kslice;       // k-tiles per slice
-    float us = 0.f;   // estimated time (0: many rounds of large tiles, not estimated)
+    int kg;           // wave groups per workgroup (1, 2 or 4)
+    int occ = 3;      // workgroups per compute unit at most, where the kernel has several (E4M3 weights, 64 x 128, one group: 2 or 3)
+    int ksplit = 1;   // number of K slices (1: none)
+    int kslice = 0;   // k-tiles per slice
+    float us = 0.f;   // estimated time
     bool forced = false;  // set through the tuning hook (zqfp_probe_force_tile_plan), not planned
 };
-TilePlan plan_tiles(int64_t M, int64_t Np, int64_t nkt);
+TilePlan plan_slices(int64_t M, int64_t Np, int64_t nkt);           // the K slices the workspace query plans, if any (else us = 0)
+int tile_workspace_slices(int64_t M, int64_t Np, int64_t nkt);  // and how many it makes room for (1: none)
 
 // The decode GEMM keeps a wave's activation fragments in registers, at most 8 k-tiles per wave and
 // 64 per workgroup.  A longer K is cut into `chunks` pieces of `len` k-tiles; a workgroup serves one
@@ -288,19 +289,19 @@ hipError_t launch_gemm_w8_decode(const uint8_t* Xq, const float* sx, int64_t M, 
 hipError_t launch_gemm_w8_tile(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob,
                                const BlobLayout& L, Lorc lorc, void* Y, int64_t ldy, int out_dtype,
                                int accum, hipStream_t s);
-// workspace: device memory of plan_tiles(...).ksplit * M * Np floats, or nullptr (then K is not split)
+// workspace: device memory of tile_workspace_slices(...) * M * Np floats, or nullptr (then K is not split)
 hipError_t launch_gemm_tile(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob,
                             const BlobLayout& L, Lorc lorc, void* Y, int64_t ldy, int out_dtype,
                             int accum, void* workspace, hipStream_t s);
 bool gemm_tile_supported(int64_t M, const BlobLayout& L);
 // few tokens, any shape, both weight formats; gemm_mid_wins: faster than the other forms for this problem
-bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum);
+bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum, bool workspace);
 hipError_t launch_gemm_mid(const uint8_t* Xq, const float* sx, int64_t M, const uint8_t* blob,
                            const BlobLayout& L, Lorc lorc, void* Y, int64_t ldy, int out_dtype,
                            int accum, hipStream_t s);
-// The plan the tiled form runs for a problem: plan_tiles, unless the tuning hook has fixed one (tile shape and
-// number of K slices for every following call; 0, 0, 0 returns to automatic planning; false = not a shape the kernel has).
-TilePlan effective_tile_plan(int64_t M, int64_t Np, int64_t nkt);
+// The plan the tiled form runs for a problem, unless the tuning hook has fixed one (tile shape and number of K slices for every
+// following call; 0, 0, 0 returns to automatic planning; false = not a shape the kernel has).  may_split: there is a workspace.
+TilePlan effective_tile_plan(int64_t M, int64_t Np, int64_t nkt, int accum, int wbits, bool may_split);
 bool force_tile_plan(int bm, int bn, int ksplit, int kg);
 
 // workspace: plan_decode(nkt).chunks * M * Np floats when K has more than 64 k-tiles (else unused)
