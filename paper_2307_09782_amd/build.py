@@ -15,6 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libzqfp.so")
+BINDING = os.path.join(HERE, "_binding.so")  # the Python binding's extension module: host code only, no part of the library
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -62,15 +63,29 @@ def _check_no_scratch(remarks):
                     raise RuntimeError(f"{name}: '{text}' -- this kernel must not spill")
 
 
+def _binding_command():
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    includes = [*include_paths("cuda"), sysconfig.get_paths()["include"]]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(x for i in includes for x in ("-isystem", i)),
+            os.path.join(CSRC, "binding.cpp"), "-o", BINDING, "-L" + libs, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build_lib(verbose=False, jobs=8):
-    """Compile every csrc/*.hip and link libzqfp.so (always recompiles)."""
+    """Compile every csrc/*.hip and link libzqfp.so, compile the binding's extension module (always recompiles)."""
     os.makedirs(OBJDIR, exist_ok=True)
     srcs = sources()
     objs = [os.path.join(OBJDIR, os.path.basename(s)[:-4] + ".o") for s in srcs]
     cmds = [[HIPCC, *FLAGS, "-Rpass-analysis=kernel-resource-usage",
              *(["-save-temps=obj"] if os.path.basename(s) in HAND_WAIT_SOURCES else []), "-c", s, "-o", o] for s, o in zip(srcs, objs)]
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        binding = ex.submit(_run, _binding_command())
         outs = list(ex.map(_run, cmds))
+        outs.append(binding.result())
     for o in outs:
         _check_no_scratch(o)
     for src, kernel in HAND_WAIT_SOURCES.items():

@@ -2,12 +2,16 @@
 
 Argument marshalling only: every function takes torch tensors that live on
 the GPU, checks dtypes / contiguity, allocates the outputs with torch and
-passes raw device pointers plus the current HIP stream to the library.  No
+passes raw device pointers plus the current HIP stream to the library.  The
+layer calls do this in a small extension module (``csrc/binding.cpp``) when
+everything is as documented, and here otherwise.  No
 step of the path is computed here and there is no fallback: if the library
 is missing or a call fails, an exception is raised.
 """
 import ctypes
 import functools
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -24,8 +28,15 @@ FORM_DECODE, FORM_MID, FORM_TILE, FORM_STREAM = 1, 2, 3, 4  # probe_gemm_form
 _ERR = {-1: "ZQFP_E_NULL", -2: "ZQFP_E_SHAPE", -3: "ZQFP_E_ALIGN", -4: "ZQFP_E_MODE", -5: "ZQFP_E_HIP",
         -6: "ZQFP_E_WORKSPACE", -7: "ZQFP_E_BLOB"}
 BLOB_HEADER_BYTES = 256
+BINDING_PATH = os.path.join(_HERE, "_binding.so")
 
 _lib = None
+_native = None  # the extension module, once the library is loaded
+
+# the entry points that the extension module calls, in its order
+_NATIVE_CALLS = ("quantize_act_fp8", "rmsnorm_quantize_act_fp8", "layernorm_quantize_act_fp8", "add_rmsnorm_quantize_act_fp8",
+                 "add_layernorm_quantize_act_fp8", "relu_quantize_act_fp8", "swiglu_quantize_act_fp8", "packed_weight_bytes",
+                 "packed_weight_fp8_bytes", "gemm_workspace_bytes", "w4a8_gemm", "w4a8_gemm_lorc", "w8a8_gemm", "w4a8_linear")
 
 
 class ZqfpError(RuntimeError):
@@ -35,13 +46,13 @@ class ZqfpError(RuntimeError):
 
 
 def lib():
-    """Load libzqfp.so (raises if it has not been built)."""
-    global _lib
+    """Load libzqfp.so and the extension module (raises if they have not been built)."""
+    global _lib, _native
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise FileNotFoundError(
-                f"{LIB_PATH} not found: build it with `python -m paper_2307_09782_amd.build` "
-                "(there is no fallback path)")
+        for path in (LIB_PATH, BINDING_PATH):
+            if not os.path.exists(path):
+                raise FileNotFoundError(f"{path} not found: build it with `python -m paper_2307_09782_amd.build` "
+                                        "(there is no fallback path)")
         L = ctypes.CDLL(LIB_PATH)
         c, p, i64 = ctypes, ctypes.c_void_p, ctypes.c_int64
         L.zqfp_version.restype = c.c_int
@@ -106,8 +117,17 @@ def lib():
         L.zqfp_probe_gemm_form.argtypes = [i64, i64, i64, c.c_int, c.c_int, c.c_int, c.c_int, c.c_int]
         L.zqfp_probe_mfma.restype = c.c_int
         L.zqfp_probe_mfma.argtypes = [p, p, c.c_int, c.c_int, p]
-        _lib = L
+        loader = importlib.machinery.ExtensionFileLoader("_binding", BINDING_PATH)
+        native = importlib.util.module_from_spec(importlib.util.spec_from_loader("_binding", loader))
+        loader.exec_module(native)
+        native.use(tuple(c.cast(getattr(L, "zqfp_" + name), p).value for name in _NATIVE_CALLS))
+        _native, _lib = native, L
     return _lib
+
+
+def _load_native():
+    lib()
+    return _native
 
 
 def _check(rc):
@@ -140,6 +160,9 @@ def _rows(t, dtype):
 
 def quantize_act_fp8(X, U=None):
     """X [M,K] bf16 (U [K,r] fp16) -> Xq [M,K] uint8 E4M3 codes, sx [M] f32 (, T [M,r] f32)."""
+    done = (_native or _load_native()).quantize(0, X, None, None, None, None, U)
+    if done is not None:
+        return done
     _dev(X, torch.bfloat16, 2)
     M, K = X.shape
     Xq = torch.empty((M, K), dtype=torch.uint8, device=X.device)
@@ -156,6 +179,9 @@ def quantize_act_fp8(X, U=None):
 
 def rmsnorm_quantize_act_fp8(X, gain, eps, U=None):
     """RMS normalisation (gain [K] bf16, eps > 0) fused in front of quantize_act_fp8; same outputs."""
+    done = (_native or _load_native()).quantize(1, X, None, gain, None, eps, U)
+    if done is not None:
+        return done
     _dev(X, torch.bfloat16, 2), _dev(gain, torch.bfloat16, 1)
     M, K = X.shape
     if gain.shape[0] != K:
@@ -174,6 +200,9 @@ def rmsnorm_quantize_act_fp8(X, gain, eps, U=None):
 
 def layernorm_quantize_act_fp8(X, gain, bias, eps, U=None):
     """Layer normalisation (gain, bias [K] bf16, eps > 0) fused in front of quantize_act_fp8; same outputs."""
+    done = (_native or _load_native()).quantize(2, X, None, gain, bias, eps, U)
+    if done is not None:
+        return done
     _dev(X, torch.bfloat16, 2), _dev(gain, torch.bfloat16, 1), _dev(bias, torch.bfloat16, 1)
     M, K = X.shape
     if gain.shape[0] != K or bias.shape[0] != K:
@@ -205,6 +234,10 @@ def _quant_outputs(X, U):
 def add_norm_quantize_act_fp8(X, R, gain, eps, bias=None, U=None, H=None):
     """h = bf16(X + R), then RMS (bias None) or layer normalisation and the quantizer.  Returns (H, Xq, sx[, T]);
     pass H=R to update the residual stream in place."""
+    if H is None and R is not None:
+        done = (_native or _load_native()).quantize(1 if bias is None else 2, X, R, gain, bias, eps, U)
+        if done is not None:
+            return done
     _rows(X, torch.bfloat16), _rows(R, torch.bfloat16), _dev(gain, torch.bfloat16, 1)
     M, K = X.shape
     if tuple(R.shape) != (M, K) or gain.shape[0] != K or (bias is not None and bias.shape[0] != K):
@@ -227,6 +260,9 @@ def add_norm_quantize_act_fp8(X, R, gain, eps, bias=None, U=None, H=None):
 
 def relu_quantize_act_fp8(X, U=None):
     """ReLU fused in front of quantize_act_fp8; same outputs."""
+    done = (_native or _load_native()).quantize(3, X, None, None, None, None, U)
+    if done is not None:
+        return done
     _rows(X, torch.bfloat16)
     M, K = X.shape
     Xq, sx, T, r = _quant_outputs(X, U)
@@ -237,6 +273,10 @@ def relu_quantize_act_fp8(X, U=None):
 def swiglu_quantize_act_fp8(G, Up, U=None, H=None):
     """bf16(silu(G) * Up) fused in front of quantize_act_fp8; same outputs.  H (dense [M, K] bf16, optional)
     receives the unquantized product."""
+    if H is None and Up is not None:
+        done = (_native or _load_native()).quantize(4, G, Up, None, None, None, U)
+        if done is not None:
+            return done
     _rows(G, torch.bfloat16), _rows(Up, torch.bfloat16)
     M, K = G.shape
     if tuple(Up.shape) != (M, K):
@@ -393,6 +433,10 @@ def w4a8_gemm_lorc_static(Xq, sx, packed, N, G, out, T=None, V=None, accum=ACCUM
 def w4a8_gemm(Xq, sx, packed, N, G, out_dtype=torch.float32, accum=ACCUM_EXACT, out=None, workspace=None):
     """Y [M,N] = (sx c) * (Xq . Wq).  workspace: None = allocated here when the shape needs one, a uint8 tensor of
     at least gemm_workspace_bytes(M, K, N) bytes, or False = none (K is then not split)."""
+    if out is None and workspace is None:
+        done = (_native or _load_native()).gemm(4, Xq, sx, packed, N, G, None, None, out_dtype, accum)
+        if done is not None:
+            return done
     return _gemm_call(Xq, sx, packed, N, G, None, None, out_dtype, accum, out, workspace)
 
 
@@ -400,6 +444,10 @@ def w4a8_gemm_lorc(Xq, sx, packed, N, G, T, V, out_dtype=torch.float32, accum=AC
     """Y [M,N] = (sx c) * (Xq . Wq) + T . V."""
     if T is None or V is None:
         raise ZqfpError(-1, "T and V are required")
+    if out is None and workspace is None:
+        done = (_native or _load_native()).gemm(4, Xq, sx, packed, N, G, T, V, out_dtype, accum)
+        if done is not None:
+            return done
     return _gemm_call(Xq, sx, packed, N, G, T, V, out_dtype, accum, out, workspace)
 
 
@@ -411,6 +459,10 @@ def linear_is_fused(M, K, r=0):
 def w4a8_linear(X, packed, N, G, U=None, V=None, out_dtype=torch.float32, accum=ACCUM_EXACT, out=None, want_codes=False):
     """Y = Q8(X) . Q4(W) (+ (X.U).V) from bfloat16 X in one call (one kernel for at most 16 tokens, K <= 4096 and no
     LoRC).  Returns Y, or (Y, Xq, sx) with want_codes."""
+    if out is None and not want_codes:
+        done = (_native or _load_native()).linear(X, packed, N, G, U, V, out_dtype, accum)
+        if done is not None:
+            return done
     _rows(X, torch.bfloat16), _dev(packed, torch.uint8, 1)
     M, K = X.shape
     r = 0
@@ -460,6 +512,10 @@ def unpack_codes_fp8(packed, K, N, G):
 
 def w8a8_gemm(Xq, sx, packed, N, G, T=None, V=None, out_dtype=torch.float32, accum=ACCUM_EXACT, out=None):
     """Y [M,N] = (sx c) * (Xq . Wq8) (+ T . V): E4M3 weights."""
+    if out is None:
+        done = (_native or _load_native()).gemm(8, Xq, sx, packed, N, G, T, V, out_dtype, accum)
+        if done is not None:
+            return done
     _dev(Xq, torch.uint8, 2), _dev(sx, torch.float32, 1), _dev(packed, torch.uint8, 1)
     M, K = Xq.shape
     if packed.numel() != _blob_bytes_fp8(K, N, G) or packed.numel() == 0 or sx.shape[0] != M:

@@ -1,0 +1,92 @@
+"""The extension module behind the layer calls against the Python code that it stands in for: the same results for every call that it
+takes, and None, so that the Python code does the call or refuses it, for everything else."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2307_09782_amd import zqfp
+
+pytestmark = pytest.mark.gpu
+
+
+class Nothing:
+    """In the module's place: leaves every call to the Python code."""
+    quantize = gemm = linear = staticmethod(lambda *a: None)
+
+
+def _both(call, monkeypatch):
+    zqfp.lib()
+    native = zqfp._native
+    got = call()
+    with monkeypatch.context() as m:
+        m.setattr(zqfp, "_native", Nothing)
+        want = call()
+    assert zqfp._native is native
+    got, want = (x if isinstance(x, tuple) else (x,) for x in (got, want))
+    assert len(got) == len(want)
+    for a, b in zip(got, want):
+        assert a.dtype == b.dtype and a.shape == b.shape and a.stride() == b.stride() and a.device == b.device and not a.requires_grad
+        assert torch.equal(a, b)
+
+
+def _state(M=20, K=512, N=272, r=8):
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    f = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    return dict(X=f(M, K).bfloat16(), R=f(M, K).bfloat16(), g=f(K).bfloat16(), b=f(K).bfloat16(), U=(f(K, r) * .01).half(), V=(f(r, N) * .01).half(),
+                W=(f(K, N) * .02).bfloat16(), N=N)
+
+
+@pytest.mark.parametrize("M", [1, 20, 200])
+@pytest.mark.parametrize("rank", [0, 8])
+def test_same_results(M, rank, monkeypatch):
+    s = _state(M)
+    X, R, g, b, U = s["X"], s["R"], s["g"], s["b"], s["U"] if rank else None
+    for call in (lambda: zqfp.quantize_act_fp8(X, U), lambda: zqfp.rmsnorm_quantize_act_fp8(X, g, 1e-5, U), lambda: zqfp.rmsnorm_quantize_act_fp8(X, g, 1, U),
+                 lambda: zqfp.layernorm_quantize_act_fp8(X, g, b, 1e-5, U), lambda: zqfp.relu_quantize_act_fp8(X, U), lambda: zqfp.swiglu_quantize_act_fp8(X, R, U),
+                 lambda: zqfp.add_norm_quantize_act_fp8(X, R, g, 1e-5, None, U), lambda: zqfp.add_norm_quantize_act_fp8(X, R, g, 1e-5, b, U),
+                 lambda: zqfp.relu_quantize_act_fp8(torch.cat([X, R], 1)[:, :X.shape[1]], U)):
+        _both(call, monkeypatch)
+    T = zqfp.quantize_act_fp8(X, s["U"])[2] if rank else None
+    V = s["V"] if rank else None
+    Xq, sx = zqfp.quantize_act_fp8(X)
+    p4, p8 = zqfp.pack_weight_fp4(s["W"], 128, 1), zqfp.pack_weight_fp8(s["W"], 128, 1)
+    for out in (torch.float32, torch.bfloat16):
+        for accum in (0, 1):
+            _both(lambda: zqfp.w8a8_gemm(Xq, sx, p8, s["N"], 128, T, V, out_dtype=out, accum=accum), monkeypatch)
+            _both(lambda: zqfp.w4a8_linear(X, p4, s["N"], 128, U, V, out_dtype=out, accum=accum), monkeypatch)
+            if rank:
+                _both(lambda: zqfp.w4a8_gemm_lorc(Xq, sx, p4, s["N"], 128, T, V, out_dtype=out, accum=accum), monkeypatch)
+            else:
+                _both(lambda: zqfp.w4a8_gemm(Xq, sx, p4, s["N"], 128, out_dtype=out, accum=accum), monkeypatch)
+
+
+def test_what_was_refused_is_refused():
+    s = _state()
+    X, packed = s["X"], zqfp.pack_weight_fp4(s["W"], 128, 1)
+    Xq, sx = zqfp.quantize_act_fp8(X)
+    for call, error in ((lambda: zqfp.quantize_act_fp8(X.float()), TypeError), (lambda: zqfp.quantize_act_fp8(X.t()), TypeError),
+                        (lambda: zqfp.quantize_act_fp8(X.cpu()), TypeError), (lambda: zqfp.quantize_act_fp8(X[:, :500].contiguous()), zqfp.ZqfpError),
+                        (lambda: zqfp.rmsnorm_quantize_act_fp8(X, s["g"], 0.0), zqfp.ZqfpError), (lambda: zqfp.rmsnorm_quantize_act_fp8(X, s["g"][:-1], 1e-5), zqfp.ZqfpError),
+                        (lambda: zqfp.swiglu_quantize_act_fp8(X, s["R"][:-1]), zqfp.ZqfpError), (lambda: zqfp.add_norm_quantize_act_fp8(X, s["R"][:-1], s["g"], 1e-5), zqfp.ZqfpError),
+                        (lambda: zqfp.w4a8_gemm(Xq, sx, packed, 256, 128), zqfp.ZqfpError), (lambda: zqfp.w4a8_gemm(Xq, sx, packed, 272.0, 128), TypeError), (lambda: zqfp.w4a8_gemm(Xq, sx, packed, 272, 128.0), ctypes.ArgumentError),
+                        (lambda: zqfp.w4a8_gemm(Xq, sx[:-1].contiguous(), packed, 272, 128), zqfp.ZqfpError), (lambda: zqfp.w4a8_gemm(Xq, sx, packed, 272, 128, accum=7), zqfp.ZqfpError),
+                        (lambda: zqfp.w4a8_gemm(Xq, sx, packed, 272, 128, out_dtype=torch.float16), zqfp.ZqfpError),
+                        (lambda: zqfp.w4a8_gemm_lorc(Xq, sx, packed, 272, 128, sx[:, None].contiguous(), s["V"]), zqfp.ZqfpError),
+                        (lambda: zqfp.w4a8_gemm(None, sx, packed, 272, 128), TypeError), (lambda: zqfp.w4a8_linear(X, packed[:-256], 272, 128), zqfp.ZqfpError)):
+        with pytest.raises(error):
+            call()
+
+
+def test_on_a_side_stream_and_under_a_function_mode():
+    s = _state(200)
+    want = zqfp.quantize_act_fp8(s["X"], s["U"])
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        got = zqfp.quantize_act_fp8(s["X"], s["U"])
+    stream.synchronize()
+    with torch.device("cuda"):  # a torch function mode: the Python code, whose allocations it may see
+        also = zqfp.quantize_act_fp8(s["X"], s["U"])
+    for a, b, c in zip(want, got, also):
+        assert torch.equal(a, b) and torch.equal(a, c)
