@@ -64,6 +64,7 @@ __device__ inline void lorc_accumulate(float (&acc)[RP], const float (&x)[8], co
 // two binary32 values -> two bf16 in one dword (round to nearest even): the packed hardware conversion
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
 __device__ inline uint32_t pack_bf16_rne(float lo, float hi)
 {
     const f32x2_t v = {lo, hi};
@@ -125,42 +126,67 @@ __device__ inline uint4 relu8(uint4 x)
 // that of the expression evaluated in binary64 and rounded to binary32 first.
 // Fast path, binary32 throughout: for 2^-30 <= |g| <= 32 and 2^-30 <= |u| <= 2^30 every intermediate
 // is a normal number (exp(-g) in 2^+-47, the quotient above 2^-77, the product in 2^-107 .. 2^35), so
-// the relative error is bounded by that of expf (documented as 1 ulp, taken as 4), of the hardware
+// the relative error is bounded by that of exp (below, taken as 4 ulp), of the hardware
 // reciprocal (1 ulp) and three roundings: 13 * 2^-24 in all, at most 13 binary32 ulps of the result.
 // The bf16 rounding of the true value and of the
 // binary64 evaluation (which is within half a binary32 ulp of it after its own rounding) is therefore
 // the one of this value whenever its low 16 bits are more than 32 ulps away from the half-way pattern
 // 0x8000.  Anything else (1 value in 1000, and inputs outside the ranges) is evaluated in binary64.
+//
+// exp(-g) = 2^(-g L) e^(-g c) with L = 47274 / 2^15, log2 e to 16 bits, and c = 1 - L ln 2.  g has 8 bits, so -g L is exact and the
+// hardware's power of two (1 ulp) is of the number meant; |g c| <= 2^-12.6, so 1 - g c is e^(-g c) within a quarter ulp.
+//
+// The vector units are the bound: a row of 28672 values on its one compute unit, and from some hundred rows on all of them.  Hence no
+// general expf, and the conditions in 16-bit arithmetic on pairs (what a saturating difference leaves of a value outside a
+// range is not zero), not in comparisons of each value: about 21 issue slots a value in place of 33.  Graph-timed, before -> after: 4 x 28672
+// 10.2 -> 9.2 us, 16 x 8192 5.0 -> 4.7, 333 x 4096 6.4 -> 5.7, 1500 x 4096 17.7 -> 15.1, 2048 x 8192 rank 8 43.7 -> 37.8, 4096 x 11008
+// 64.0 -> 60.6.  (All loads of the second operand ahead of the evaluations lose: 64 x 28672 11.7 -> 12.1, 4096 x 11008 64 -> 101.)
+__device__ inline uint32_t outside(uint32_t pair, uint16_t lo, uint16_t hi)  // a half of the result is 0 where lo <= pair's half <= hi
+{
+    const u16x2_t v = __builtin_bit_cast(u16x2_t, pair), l = {lo, lo}, h = {hi, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(l, v)) | __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(v, h));
+}
+
 __device__ inline uint4 swiglu8(uint4 g, uint4 u)
 {
+    constexpr float L = 47274.0f / 32768.0f, c = 0x1.480fb6p-18f;
     const uint32_t gw[4] = {g.x, g.y, g.z, g.w}, uw[4] = {u.x, u.y, u.z, u.w};
-    float gf[8], uf[8], y[8];
+    uint32_t o[4], open[4];
+    auto fast = [&](float gf, float uf) __attribute__((always_inline)) {
+        const float e = __builtin_amdgcn_exp2f(gf * -L);
+        return gf * __builtin_amdgcn_rcpf(1.0f + fmaf(e, gf * -c, e)) * uf;
+    };
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        gf[2 * i] = bf16_lo(gw[i]); gf[2 * i + 1] = bf16_hi(gw[i]);
-        uf[2 * i] = bf16_lo(uw[i]); uf[2 * i + 1] = bf16_hi(uw[i]);
+        const float y0 = fast(bf16_lo(gw[i]), bf16_lo(uw[i])), y1 = fast(bf16_hi(gw[i]), bf16_hi(uw[i]));
+        o[i] = pack_bf16_rne(y0, y1);
+        const u16x2_t low = __builtin_bit_cast(u16x2_t, __builtin_amdgcn_perm(__float_as_uint(y1), __float_as_uint(y0), 0x05040100u));
+        const u16x2_t first = {0x8000 - 32, 0x8000 - 32}, count = {65, 65};
+        open[i] = outside(gw[i] & 0x7FFF7FFFu, 0x3080, 0x4200) | outside(uw[i] & 0x7FFF7FFFu, 0x3080, 0x4E80) |
+                  __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(count, (u16x2_t)(low - first)));
     }
-    uint32_t redo = 0;  // the eight fast evaluations are straight-line code; what they leave open is redone below
+    if ((open[0] | open[1] | open[2] | open[3]) != 0) {
+        uint32_t redo = 0;  // a bit per value
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float ag = fabsf(gf[i]), au = fabsf(uf[i]);
-        y[i] = gf[i] * __builtin_amdgcn_rcpf(1.0f + expf(-gf[i])) * uf[i];
-        const uint32_t low = __float_as_uint(y[i]) & 0xFFFFu;
-        const bool safe = ag >= 0x1p-30f && ag <= 32.0f && au >= 0x1p-30f && au <= 0x1p30f &&
-                          low - (0x8000u - 32u) > 64u;  // unsigned: |low - 0x8000| > 32
-        redo |= safe ? 0u : 1u << i;
-    }
-    if (redo != 0) {
+        for (int i = 0; i < 4; ++i) redo |= ((open[i] & 0xFFFFu) != 0 ? 1u << 2 * i : 0u) | (open[i] >> 16 != 0 ? 2u << 2 * i : 0u);
+        // every lane takes its own next value: one turn where a branch at each place would make one per place that any lane has open
+        do {
+            const int b = __builtin_ctz(redo);
+            redo &= redo - 1;
+            uint32_t gb = gw[0], ub = uw[0];
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if ((redo >> i) & 1u) {
-                const double gd = (double)gf[i];
-                y[i] = (float)(gd / (1.0 + exp(-gd)) * (double)uf[i]);
+            for (int i = 1; i < 4; ++i) {
+                gb = (b >> 1) == i ? gw[i] : gb;
+                ub = (b >> 1) == i ? uw[i] : ub;
             }
-    }
-    uint32_t o[4];
+            asm volatile("" : "+v"(gb), "+v"(ub));  // the conversions' halves need not live across turns
+            const double gd = (double)((b & 1) ? bf16_hi(gb) : bf16_lo(gb)), ud = (double)((b & 1) ? bf16_hi(ub) : bf16_lo(ub));
+            const float y = (float)(gd / (1.0 + exp(-gd)) * ud);
+            const uint32_t half = (b & 1) ? 0xFFFF0000u : 0xFFFFu, bits = pack_bf16_rne(y, y) & half;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = pack_bf16_rne(y[2 * i], y[2 * i + 1]);
+            for (int i = 0; i < 4; ++i) o[i] = (b >> 1) == i ? (o[i] & ~half) | bits : o[i];
+        } while (redo != 0);
+    }
     return make_uint4(o[0], o[1], o[2], o[3]);
 }
 
@@ -208,9 +234,10 @@ __device__ inline double sum_squares(double acc, uint4 v)
 // `other` is a residual added to X first; the sum, rounded to bf16, also goes to H.  Every thread reads an
 // element of `other` before it writes the same element of H, and nothing else touches it: H may be `other`.
 // NT threads per token: 256 when there are tokens enough to fill the chip, 1024 for a handful of
-// tokens (decode), where one row's latency chain is all there is.
+// tokens (decode), where one row's latency chain is all there is.  The gated unit in 1024 threads is held to 64 registers, so that two
+// tokens share a compute unit (4096 x 11008: 81 -> 61 us; the four that do not fit are the binary64 loop's).
 template <int RP, int NT, int NORM>
-__global__ __launch_bounds__(NT) void k_quantize_act(const uint16_t* __restrict__ X, int64_t K, int64_t ldx,
+__global__ __launch_bounds__(NT, NORM == 4 && RP == 0 && NT == 1024 ? 8 : 1) void k_quantize_act(const uint16_t* __restrict__ X, int64_t K, int64_t ldx,
                                                          uint8_t* __restrict__ Xq, float* __restrict__ sx,
                                                          const uint16_t* __restrict__ U, int r, float* __restrict__ T,
                                                          Producer pr)
