@@ -71,9 +71,18 @@ bool output_type(PyObject* o, at::ScalarType& type, int& code)
     code = type == at::kFloat ? ZQFP_OUT_F32 : ZQFP_OUT_BF16;
     return type == at::kFloat || type == at::kBFloat16;
 }
-Tensor make(at::IntArrayRef shape, at::ScalarType type, const Tensor& like) { return at::empty(shape, at::TensorOptions().dtype(type).device(like.device())); }
-void* stream_of(const Tensor& t) { return c10::hip::getCurrentHIPStream(t.get_device()).stream(); }
+Tensor make(at::IntArrayRef shape, at::ScalarType type, at::Device device) { return at::empty(shape, at::TensorOptions().dtype(type).device(device)); }
+void* stream_of(at::Device device) { return c10::hip::getCurrentHIPStream(device.index()).stream(); }
 void* ptr(const Tensor& t) { return t.data_ptr(); }
+
+// Without the interpreter lock: allocations may wait for the device, and a launch for room in its queue or for code to be loaded, while
+// other threads of the interpreter go on (and may be what the queue waits for).  Whatever is read from the arguments is read before.
+struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked&) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
 
 template <class F>
 PyObject* guarded(F&& f)
@@ -132,25 +141,30 @@ PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n)
             if (U == nullptr || U->size(0) != K || U->size(1) < 1 || U->size(1) > 64) return nullptr;
             r = (int)U->size(1);
         }
-        Tensor H, T;
-        if (norm && other) H = make({M, K}, at::kBFloat16, *X);
-        const Tensor Xq = make({M, K}, at::kByte, *X), sx = make({M}, at::kFloat, *X);
-        if (r) T = make({M, r}, at::kFloat, *X);
         const float eps = norm ? (float)PyFloat_AS_DOUBLE(a[5]) : 0.0f;
-        uint8_t* q = static_cast<uint8_t*>(ptr(Xq));
-        float *s = static_cast<float*>(ptr(sx)), *t = r ? static_cast<float*>(ptr(T)) : nullptr;
-        const void* u = r ? ptr(*U) : nullptr;
-        const void* x = ptr(*X);
-        const int64_t ldx = X->stride(0);
-        void* st = stream_of(*X);
+        auto address = [](const Tensor* t) -> const void* { return t != nullptr ? ptr(*t) : nullptr; };
+        const void *x = ptr(*X), *o = address(R), *gain = address(g), *bias = address(b), *u = address(U);
+        const int64_t ldx = X->stride(0), ldo = R != nullptr ? R->stride(0) : 0;
+        const at::Device device = X->device();
+        Tensor H, Xq, sx, T;
         int rc = ZQFP_E_SHAPE;
-        if (kind == 0) rc = lib.quantize(x, M, K, ldx, q, s, u, r, t, st);
-        else if (kind == 3) rc = lib.relu(x, M, K, ldx, q, s, u, r, t, st);
-        else if (kind == 4) rc = lib.swiglu(x, ptr(*R), R->stride(0), nullptr, M, K, ldx, q, s, u, r, t, st);
-        else if (kind == 1 && !other) rc = lib.rmsnorm(x, ptr(*g), eps, M, K, ldx, q, s, u, r, t, st);
-        else if (kind == 2 && !other) rc = lib.layernorm(x, ptr(*g), ptr(*b), eps, M, K, ldx, q, s, u, r, t, st);
-        else if (kind == 1) rc = lib.add_rmsnorm(x, ptr(*R), R->stride(0), ptr(H), ptr(*g), eps, M, K, ldx, q, s, u, r, t, st);
-        else if (kind == 2) rc = lib.add_layernorm(x, ptr(*R), R->stride(0), ptr(H), ptr(*g), ptr(*b), eps, M, K, ldx, q, s, u, r, t, st);
+        {
+            Unlocked unlocked;
+            if (norm && other) H = make({M, K}, at::kBFloat16, device);
+            Xq = make({M, K}, at::kByte, device);
+            sx = make({M}, at::kFloat, device);
+            if (r) T = make({M, r}, at::kFloat, device);
+            uint8_t* q = static_cast<uint8_t*>(ptr(Xq));
+            float *s = static_cast<float*>(ptr(sx)), *t = r ? static_cast<float*>(ptr(T)) : nullptr;
+            void* st = stream_of(device);
+            if (kind == 0) rc = lib.quantize(x, M, K, ldx, q, s, u, r, t, st);
+            else if (kind == 3) rc = lib.relu(x, M, K, ldx, q, s, u, r, t, st);
+            else if (kind == 4) rc = lib.swiglu(x, o, ldo, nullptr, M, K, ldx, q, s, u, r, t, st);
+            else if (kind == 1 && !other) rc = lib.rmsnorm(x, gain, eps, M, K, ldx, q, s, u, r, t, st);
+            else if (kind == 2 && !other) rc = lib.layernorm(x, gain, bias, eps, M, K, ldx, q, s, u, r, t, st);
+            else if (kind == 1) rc = lib.add_rmsnorm(x, o, ldo, ptr(H), gain, eps, M, K, ldx, q, s, u, r, t, st);
+            else if (kind == 2) rc = lib.add_layernorm(x, o, ldo, ptr(H), gain, bias, eps, M, K, ldx, q, s, u, r, t, st);
+        }
         if (rc != ZQFP_OK) return nullptr;
         if (H.defined()) return r ? tuple_of(H, Xq, sx, T) : tuple_of(H, Xq, sx);
         return r ? tuple_of(Xq, sx, T) : tuple_of(Xq, sx);
@@ -177,22 +191,27 @@ PyObject* gemm(PyObject*, PyObject* const* a, Py_ssize_t n)
         }
         const size_t need = wbits == 8 ? lib.blob_bytes_fp8(K, N, (int)G) : lib.blob_bytes(K, N, (int)G);
         if (need == 0 || (size_t)packed->numel() != need || sx->size(0) != M) return nullptr;
-        const Tensor Y = make({M, N}, type, *Xq);
         const uint8_t* q = static_cast<const uint8_t*>(ptr(*Xq));
         const float *s = static_cast<const float*>(ptr(*sx)), *t = r ? static_cast<const float*>(ptr(*T)) : nullptr;
-        const void* v = r ? ptr(*V) : nullptr;
-        void *st = stream_of(*Xq), *y = ptr(Y);
-        const int64_t ldy = Y.stride(0);
+        const void *p = ptr(*packed), *v = r ? ptr(*V) : nullptr;
+        const at::Device device = Xq->device();
+        Tensor Y;
         int rc;
-        if (wbits == 8) {
-            rc = lib.gemm_w8(q, s, M, K, ptr(*packed), N, (int)G, t, v, r, y, ldy, code, (int)accum, st);
-        } else {
-            const size_t bytes = lib.workspace_bytes(M, K, N);
-            Tensor ws;
-            if (bytes) ws = make({(int64_t)bytes}, at::kByte, *Xq);
-            void* w = bytes ? ptr(ws) : nullptr;
-            rc = r ? lib.gemm_lorc(q, s, M, K, ptr(*packed), N, (int)G, t, v, r, y, ldy, code, (int)accum, w, bytes, st)
-                   : lib.gemm(q, s, M, K, ptr(*packed), N, (int)G, y, ldy, code, (int)accum, w, bytes, st);
+        {
+            Unlocked unlocked;
+            Y = make({M, N}, type, device);
+            void *st = stream_of(device), *y = ptr(Y);
+            const int64_t ldy = Y.stride(0);
+            if (wbits == 8) {
+                rc = lib.gemm_w8(q, s, M, K, p, N, (int)G, t, v, r, y, ldy, code, (int)accum, st);
+            } else {
+                const size_t bytes = lib.workspace_bytes(M, K, N);
+                Tensor ws;
+                if (bytes) ws = make({(int64_t)bytes}, at::kByte, device);
+                void* w = bytes ? ptr(ws) : nullptr;
+                rc = r ? lib.gemm_lorc(q, s, M, K, p, N, (int)G, t, v, r, y, ldy, code, (int)accum, w, bytes, st)
+                       : lib.gemm(q, s, M, K, p, N, (int)G, y, ldy, code, (int)accum, w, bytes, st);
+            }
         }
         return rc == ZQFP_OK ? THPVariable_Wrap(Y) : nullptr;
     });
@@ -218,20 +237,27 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n)
         }
         const size_t need = lib.blob_bytes(K, N, (int)G);
         if (need == 0 || (size_t)packed->numel() != need) return nullptr;
-        const Tensor Y = make({M, N}, type, *X);
-        Tensor Xq, sx, T, ws;
-        size_t bytes = 0;
-        if (!(M >= 1 && M <= 16 && K <= 4096 && r == 0)) {  // not the one-kernel form
-            Xq = make({M, K}, at::kByte, *X);
-            sx = make({M}, at::kFloat, *X);
-            bytes = lib.workspace_bytes(M, K, N);
-            if (bytes) ws = make({(int64_t)bytes}, at::kByte, *X);
+        const void *x = ptr(*X), *w = ptr(*packed), *u = r ? ptr(*U) : nullptr, *v = r ? ptr(*V) : nullptr;
+        const int64_t ldx = X->stride(0);
+        const at::Device device = X->device();
+        Tensor Y;
+        int rc;
+        {
+            Unlocked unlocked;
+            Y = make({M, N}, type, device);
+            Tensor Xq, sx, T, ws;
+            size_t bytes = 0;
+            if (!(M >= 1 && M <= 16 && K <= 4096 && r == 0)) {  // not the one-kernel form
+                Xq = make({M, K}, at::kByte, device);
+                sx = make({M}, at::kFloat, device);
+                bytes = lib.workspace_bytes(M, K, N);
+                if (bytes) ws = make({(int64_t)bytes}, at::kByte, device);
+            }
+            if (r) T = make({M, r}, at::kFloat, device);
+            auto p = [](const Tensor& t) { return t.defined() ? ptr(t) : nullptr; };
+            rc = lib.linear(x, ldx, M, K, w, N, (int)G, u, v, r, static_cast<uint8_t*>(p(Xq)), static_cast<float*>(p(sx)), static_cast<float*>(p(T)), ptr(Y),
+                            Y.stride(0), code, (int)accum, p(ws), bytes, stream_of(device));
         }
-        if (r) T = make({M, r}, at::kFloat, *X);
-        auto p = [](const Tensor& t) { return t.defined() ? ptr(t) : nullptr; };
-        const int rc = lib.linear(ptr(*X), X->stride(0), M, K, ptr(*packed), N, (int)G, r ? ptr(*U) : nullptr, r ? ptr(*V) : nullptr, r,
-                                  static_cast<uint8_t*>(p(Xq)), static_cast<float*>(p(sx)), static_cast<float*>(p(T)), ptr(Y), Y.stride(0), code,
-                                  (int)accum, p(ws), bytes, stream_of(*X));
         return rc == ZQFP_OK ? THPVariable_Wrap(Y) : nullptr;
     });
 }

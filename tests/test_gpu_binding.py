@@ -90,3 +90,37 @@ def test_on_a_side_stream_and_under_a_function_mode():
         also = zqfp.quantize_act_fp8(s["X"], s["U"])
     for a, b, c in zip(want, got, also):
         assert torch.equal(a, b) and torch.equal(a, c)
+
+
+# in the order in which the module takes them; the others are host arithmetic
+_QUERIES = ("packed_weight_bytes", "packed_weight_fp8_bytes", "gemm_workspace_bytes")
+
+
+def test_the_interpreter_lock_is_not_held_inside_the_library():
+    """In the place of every entry point that launches something stands the interpreter's own question whether this thread holds its
+    lock: 0, which is the library's success, where it does not, and 1, an error that makes the module decline the call, where it does."""
+    s = _state()
+    X, R, g, b, U, V, N = (s[k] for k in ("X", "R", "g", "b", "U", "V", "N"))
+    Xq, sx, T = zqfp.quantize_act_fp8(X, U)
+    p4, p8 = zqfp.pack_weight_fp4(s["W"], 128, 1), zqfp.pack_weight_fp8(s["W"], 128, 1)
+    native, address = zqfp._native, lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    real = {name: address(getattr(zqfp.lib(), "zqfp_" + name)) for name in zqfp._NATIVE_CALLS}
+    assert ctypes.pythonapi.PyGILState_Check() == 1
+    held = address(ctypes.pythonapi.PyGILState_Check)
+    native.use(tuple(real[name] if name in _QUERIES else held for name in zqfp._NATIVE_CALLS))
+    try:
+        done = [native.quantize(0, X, None, None, None, None, U), native.quantize(1, X, None, g, None, 1e-5, U), native.quantize(2, X, None, g, b, 1e-5, U),
+                native.quantize(1, X, R, g, None, 1e-5, None), native.quantize(2, X, R, g, b, 1e-5, None), native.quantize(3, X, None, None, None, None, U),
+                native.quantize(4, X, R, None, None, None, U), native.gemm(4, Xq, sx, p4, N, 128, None, None, torch.float32, 0),
+                native.gemm(4, Xq, sx, p4, N, 128, T, V, torch.float32, 0), native.gemm(8, Xq, sx, p8, N, 128, None, None, torch.float32, 0),
+                native.linear(X, p4, N, 128, U, V, torch.float32, 0)]
+    finally:
+        native.use(tuple(real[name] for name in zqfp._NATIVE_CALLS))
+    assert [i for i, d in enumerate(done) if d is None] == []
+
+
+def test_an_allocation_that_fails_is_reported():
+    """Both paths meet it; the module's lock is back when its exception leaves."""
+    with pytest.raises(torch.OutOfMemoryError):
+        zqfp.relu_quantize_act_fp8(torch.zeros(1, 128, dtype=torch.bfloat16, device="cuda").expand(1 << 40, 128))
+    assert zqfp.relu_quantize_act_fp8(torch.zeros(1, 128, dtype=torch.bfloat16, device="cuda"))[0].shape == (1, 128)
