@@ -15,7 +15,6 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libzqfp.so")
-BINDING = os.path.join(HERE, "_binding.so")  # the Python binding's extension module: host code only, no part of the library
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -63,6 +62,15 @@ def _check_no_scratch(remarks):
                     raise RuntimeError(f"{name}: '{text}' -- this kernel must not spill")
 
 
+def binding_path():
+    """The Python binding's extension module (host code only, no part of the library).  It uses the interpreter's and torch's binary
+    interfaces, so its name says which ones it was built for: another interpreter or torch does not find it."""
+    import sysconfig
+
+    import torch
+    return os.path.join(HERE, f"_binding-torch-{torch.__version__}{sysconfig.get_config_var('EXT_SUFFIX')}")
+
+
 def _binding_command():
     import sysconfig
 
@@ -72,7 +80,7 @@ def _binding_command():
     libs = os.path.join(os.path.dirname(torch.__file__), "lib")
     return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(x for i in includes for x in ("-isystem", i)),
-            os.path.join(CSRC, "binding.cpp"), "-o", BINDING, "-L" + libs, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+            os.path.join(CSRC, "binding.cpp"), "-o", binding_path(), "-L" + libs, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
 
 
 def build_lib(verbose=False, jobs=8):

@@ -16,6 +16,8 @@ import os
 
 import torch
 
+from .build import binding_path
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # ZQFP_LIB_PATH names another build of the same library (e.g. one whose host code is compiled with sanitizers)
 LIB_PATH = os.environ.get("ZQFP_LIB_PATH") or os.path.join(_HERE, "libzqfp.so")
@@ -28,7 +30,7 @@ FORM_DECODE, FORM_MID, FORM_TILE, FORM_STREAM = 1, 2, 3, 4  # probe_gemm_form
 _ERR = {-1: "ZQFP_E_NULL", -2: "ZQFP_E_SHAPE", -3: "ZQFP_E_ALIGN", -4: "ZQFP_E_MODE", -5: "ZQFP_E_HIP",
         -6: "ZQFP_E_WORKSPACE", -7: "ZQFP_E_BLOB"}
 BLOB_HEADER_BYTES = 256
-BINDING_PATH = os.path.join(_HERE, "_binding.so")
+BINDING_PATH = binding_path()
 
 _lib = None
 _native = None  # the extension module, once the library is loaded

@@ -230,3 +230,12 @@ def test_gemm_form_query_refuses_what_the_gemm_refuses(lib):
     with pytest.raises(zqfp.ZqfpError) as e:
         zqfp.probe_gemm_form(1, 4096, 4096, accum=2)
     assert e.value.code == -4
+
+
+def test_extension_module_is_named_after_what_it_was_built_for():
+    """It speaks the interpreter's and torch's binary interfaces; one built for others must not be loaded."""
+    import sysconfig
+
+    import torch
+    name = os.path.basename(zqfp.BINDING_PATH)
+    assert torch.__version__ in name and name.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
