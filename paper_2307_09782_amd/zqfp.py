@@ -4,7 +4,7 @@ Argument marshalling only: every function takes torch tensors that live on
 the GPU, checks dtypes / contiguity, allocates the outputs with torch and
 passes raw device pointers plus the current HIP stream to the library.  The
 layer calls do this in a small extension module (``csrc/binding.cpp``) when
-everything is as documented, and here otherwise.  No
+it has been built and everything is as documented, and here otherwise.  No
 step of the path is computed here and there is no fallback: if the library
 is missing or a call fails, an exception is raised.
 """
@@ -33,12 +33,17 @@ BLOB_HEADER_BYTES = 256
 BINDING_PATH = binding_path()
 
 _lib = None
-_native = None  # the extension module, once the library is loaded
+_native = None  # the extension module (or what stands in for it), once the library is loaded
 
 # the entry points that the extension module calls, in its order
 _NATIVE_CALLS = ("quantize_act_fp8", "rmsnorm_quantize_act_fp8", "layernorm_quantize_act_fp8", "add_rmsnorm_quantize_act_fp8",
                  "add_layernorm_quantize_act_fp8", "relu_quantize_act_fp8", "swiglu_quantize_act_fp8", "packed_weight_bytes",
                  "packed_weight_fp8_bytes", "gemm_workspace_bytes", "w4a8_gemm", "w4a8_gemm_lorc", "w8a8_gemm", "w4a8_linear")
+
+
+class _NoExtension:
+    """Where the extension module has not been built: leaves every call to the code here, at 3 to 6 us of host time more."""
+    quantize = gemm = linear = staticmethod(lambda *args: None)
 
 
 class ZqfpError(RuntimeError):
@@ -48,13 +53,13 @@ class ZqfpError(RuntimeError):
 
 
 def lib():
-    """Load libzqfp.so and the extension module (raises if they have not been built)."""
+    """Load libzqfp.so (raises if it has not been built), and the extension module where there is one."""
     global _lib, _native
     if _lib is None:
-        for path in (LIB_PATH, BINDING_PATH):
-            if not os.path.exists(path):
-                raise FileNotFoundError(f"{path} not found: build it with `python -m paper_2307_09782_amd.build` "
-                                        "(there is no fallback path)")
+        if not os.path.exists(LIB_PATH):
+            raise FileNotFoundError(
+                f"{LIB_PATH} not found: build it with `python -m paper_2307_09782_amd.build` "
+                "(there is no fallback path)")
         L = ctypes.CDLL(LIB_PATH)
         c, p, i64 = ctypes, ctypes.c_void_p, ctypes.c_int64
         L.zqfp_version.restype = c.c_int
@@ -119,10 +124,12 @@ def lib():
         L.zqfp_probe_gemm_form.argtypes = [i64, i64, i64, c.c_int, c.c_int, c.c_int, c.c_int, c.c_int]
         L.zqfp_probe_mfma.restype = c.c_int
         L.zqfp_probe_mfma.argtypes = [p, p, c.c_int, c.c_int, p]
-        loader = importlib.machinery.ExtensionFileLoader("_binding", BINDING_PATH)
-        native = importlib.util.module_from_spec(importlib.util.spec_from_loader("_binding", loader))
-        loader.exec_module(native)
-        native.use(tuple(c.cast(getattr(L, "zqfp_" + name), p).value for name in _NATIVE_CALLS))
+        native = _NoExtension
+        if os.path.exists(BINDING_PATH):
+            loader = importlib.machinery.ExtensionFileLoader("_binding", BINDING_PATH)
+            native = importlib.util.module_from_spec(importlib.util.spec_from_loader("_binding", loader))
+            loader.exec_module(native)
+            native.use(tuple(c.cast(getattr(L, "zqfp_" + name), p).value for name in _NATIVE_CALLS))
         _native, _lib = native, L
     return _lib
 

@@ -239,3 +239,13 @@ def test_extension_module_is_named_after_what_it_was_built_for():
     import torch
     name = os.path.basename(zqfp.BINDING_PATH)
     assert torch.__version__ in name and name.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def test_library_loads_without_the_extension_module(lib, monkeypatch, tmp_path):
+    """Every call has its Python code; only the library itself is needed."""
+    monkeypatch.setattr(zqfp, "_lib", None)
+    monkeypatch.setattr(zqfp, "_native", None)
+    monkeypatch.setattr(zqfp, "BINDING_PATH", str(tmp_path / "absent.so"))
+    assert zqfp.lib().zqfp_version() >= 100
+    for call, count in ((zqfp._native.quantize, 7), (zqfp._native.gemm, 10), (zqfp._native.linear, 8)):
+        assert call(*[None] * count) is None
