@@ -1,8 +1,9 @@
-"""Build libzqfp.so (HIP kernels + C ABI) for gfx950 with hipcc.
+"""Build libzqfp.so (HIP kernels + C ABI) for gfx950 with hipcc, and the Python
+binding's extension module with g++.
 
 Run as ``python -m paper_2307_09782_amd.build``; ``__graft_entry__.build()``
-calls :func:`build_lib`.  The library is placed next to this file so that it
-travels with the source tree; objects go to ``_build/`` (not committed).
+calls :func:`build_all`.  Both are placed next to this file so that they
+travel with the source tree; objects go to ``_build/`` (not committed).
 """
 import glob
 import os
@@ -84,16 +85,14 @@ def _binding_command():
 
 
 def build_lib(verbose=False, jobs=8):
-    """Compile every csrc/*.hip and link libzqfp.so, compile the binding's extension module (always recompiles)."""
+    """Compile every csrc/*.hip and link libzqfp.so (always recompiles).  Needs hipcc and nothing else."""
     os.makedirs(OBJDIR, exist_ok=True)
     srcs = sources()
     objs = [os.path.join(OBJDIR, os.path.basename(s)[:-4] + ".o") for s in srcs]
     cmds = [[HIPCC, *FLAGS, "-Rpass-analysis=kernel-resource-usage",
              *(["-save-temps=obj"] if os.path.basename(s) in HAND_WAIT_SOURCES else []), "-c", s, "-o", o] for s, o in zip(srcs, objs)]
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        binding = ex.submit(_run, _binding_command())
         outs = list(ex.map(_run, cmds))
-        outs.append(binding.result())
     for o in outs:
         _check_no_scratch(o)
     for src, kernel in HAND_WAIT_SOURCES.items():
@@ -107,6 +106,22 @@ def build_lib(verbose=False, jobs=8):
         if text:
             print(text)
     return LIB
+
+
+def build_binding(verbose=False):
+    """Compile the extension module (always recompiles).  Needs g++, torch's headers and Python's."""
+    out = _run(_binding_command())
+    if verbose and out.strip():
+        print(out)
+    return binding_path()
+
+
+def build_all(verbose=False):
+    """The library and, beside it, the extension module.  Where the module cannot be built the library has been, and the error is raised."""
+    with ThreadPoolExecutor(max_workers=1) as ex:
+        binding = ex.submit(build_binding, verbose)
+        lib = build_lib(verbose)
+        return lib, binding.result()
 
 
 def sanitizer_runtime():
@@ -137,4 +152,4 @@ def build_host_sanitized(out):
 
 
 if __name__ == "__main__":
-    print(build_lib(verbose=True))
+    print(*build_all(verbose=True), sep="\n")

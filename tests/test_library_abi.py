@@ -249,3 +249,17 @@ def test_library_loads_without_the_extension_module(lib, monkeypatch, tmp_path):
     assert zqfp.lib().zqfp_version() >= 100
     for call, count in ((zqfp._native.quantize, 7), (zqfp._native.gemm, 10), (zqfp._native.linear, 8)):
         assert call(*[None] * count) is None
+
+
+def test_library_is_built_by_hipcc_alone(monkeypatch, tmp_path):
+    """The C library needs no C++ compiler of its own, no torch and no Python headers; those are the extension module's."""
+    from paper_2307_09782_amd import build
+    commands = []
+    monkeypatch.setattr(build, "_run", lambda cmd: commands.append(cmd) or "")
+    monkeypatch.setattr(build, "OBJDIR", str(tmp_path))
+    monkeypatch.setattr(build.check_lds_waits, "check_text", lambda *a: None)
+    for src in build.HAND_WAIT_SOURCES:
+        (tmp_path / (src[:-4] + "-hip-amdgcn-amd-amdhsa-gfx950.s")).write_text("")
+    build.build_lib()
+    assert len(commands) == len(build.sources()) + 1
+    assert {cmd[0] for cmd in commands} == {build.HIPCC}
