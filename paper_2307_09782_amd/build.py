@@ -35,7 +35,10 @@ def sources():
 # compile without scratch memory.  The compiler's resource remarks are checked after every build.
 # The register-fed GEMM has no hand-issued reads, but a spill inside its loop costs a quarter of its time.
 NO_SCRATCH_KERNELS = ("k_gemm_tile", "k_gemm_mid")
-# The same kernels' device assembly is kept by the compile and checked for another thing the compiler may do to
+# Waves per SIMD that a kernel's registers must leave room for, by its mangled name: one less is a round of workgroups more.
+MIN_WAVES = {"k_quantize_actILi16ELi256ELi0E": 5, "k_quantize_actILi16ELi256ELi1E": 5, "k_quantize_actILi16ELi256ELi3E": 5,
+             "k_quantize_actILi16ELi256ELi4E": 7, "k_quantize_actILi8ELi256ELi0E": 5}
+# The hand-waiting kernels' device assembly is kept by the compile and checked for another thing the compiler may do to
 # such reads: copy their destination register before the wait (see check_lds_waits).
 HAND_WAIT_SOURCES = {"gemm_tile.hip": "k_gemm_tile"}
 
@@ -61,6 +64,22 @@ def _check_no_scratch(remarks):
             for key in ("ScratchSize [bytes/lane]:", "VGPRs Spill:"):
                 if text.startswith(key) and int(text[len(key):].split("[")[0]) != 0:
                     raise RuntimeError(f"{name}: '{text}' -- this kernel must not spill")
+
+
+def _check_waves(remarks):
+    """Raise if a kernel named in MIN_WAVES leaves room for fewer waves, or buys that room by spilling."""
+    name = None
+    for line in remarks.splitlines():
+        if "remark:" not in line:
+            continue
+        text = line.split("remark:", 1)[1].strip()
+        if text.startswith("Function Name:"):
+            name = text.split(":", 1)[1].split("[")[0].strip()
+            want = max((n for k, n in MIN_WAVES.items() if k in name), default=0)
+        elif name and want:
+            for key, bad in (("Occupancy [waves/SIMD]:", lambda n: n < want), ("ScratchSize [bytes/lane]:", bool), ("VGPRs Spill:", bool)):
+                if text.startswith(key) and bad(int(text[len(key):].split("[")[0])):
+                    raise RuntimeError(f"{name}: '{text}' -- this kernel must leave room for {want} waves per SIMD without spilling")
 
 
 def binding_path():
@@ -95,6 +114,7 @@ def build_lib(verbose=False, jobs=8):
         outs = list(ex.map(_run, cmds))
     for o in outs:
         _check_no_scratch(o)
+        _check_waves(o)
     for src, kernel in HAND_WAIT_SOURCES.items():
         listing = os.path.join(OBJDIR, src[:-4] + "-hip-amdgcn-amd-amdhsa-gfx950.s")
         with open(listing) as f:

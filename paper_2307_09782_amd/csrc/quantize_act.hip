@@ -236,8 +236,18 @@ __device__ inline double sum_squares(double acc, uint4 v)
 // NT threads per token: 256 when there are tokens enough to fill the chip, 1024 for a handful of
 // tokens (decode), where one row's latency chain is all there is.  The gated unit in 1024 threads is held to 64 registers, so that two
 // tokens share a compute unit (4096 x 11008: 81 -> 61 us; the four that do not fit are the binary64 loop's).
+// With sums for a left factor and 256 threads a token is four waves, one a SIMD, so the waves a SIMD holds are the rounds of
+// 256 tokens a launch takes at once: the instances that fit into one round more by a few registers are held to it, none of them spills
+// (five in 96 registers, the gated unit seven in 72; left alone four and five.  1166 x 384, RMS normalisation, rank 15: 26.1 -> 17.4 us;
+// 1268 x 640 with a residual, rank 9: 24.7 -> 17.0; gated, 1489 x 4736, rank 14: 96.2 -> 76.2).
+constexpr int waves_per_simd(int rp, int nt, int norm)
+{
+    if (nt == 1024) return norm == 4 && rp == 0 ? 8 : 1;
+    if (norm == 4) return rp == 16 ? 7 : 1;
+    return (rp == 16 && norm != 2) || (rp == 8 && norm == 0) ? 5 : 1;
+}
 template <int RP, int NT, int NORM>
-__global__ __launch_bounds__(NT, NORM == 4 && RP == 0 && NT == 1024 ? 8 : 1) void k_quantize_act(const uint16_t* __restrict__ X, int64_t K, int64_t ldx,
+__global__ __launch_bounds__(NT, waves_per_simd(RP, NT, NORM)) void k_quantize_act(const uint16_t* __restrict__ X, int64_t K, int64_t ldx,
                                                          uint8_t* __restrict__ Xq, float* __restrict__ sx,
                                                          const uint16_t* __restrict__ U, int r, float* __restrict__ T,
                                                          Producer pr)

@@ -162,6 +162,20 @@ def test_build_rejects_spills_in_the_register_fed_gemm():
         build._check_no_scratch(spilled)
 
 
+def test_build_rejects_quantizers_that_leave_room_for_fewer_waves():
+    """The remarks of the sums-of-sixteen quantizer as they are, and with what a few registers more would make of them."""
+    from paper_2307_09782_amd import build
+    ok = ("x.hip:1:1: remark: Function Name: _ZN4zqfp12_GLOBAL__N_114k_quantize_actILi16ELi256ELi1EEEvPKtll [-Rpass-analysis=kernel-resource-usage]\n"
+          "x.hip:1:1: remark:     ScratchSize [bytes/lane]: 0 [-Rpass-analysis=kernel-resource-usage]\n"
+          "x.hip:1:1: remark:     Occupancy [waves/SIMD]: 5 [-Rpass-analysis=kernel-resource-usage]\n"
+          "x.hip:1:1: remark: Function Name: _ZN4zqfp12_GLOBAL__N_114k_quantize_actILi16ELi1024ELi1EEEvPKtll [-Rpass-analysis=kernel-resource-usage]\n"
+          "x.hip:1:1: remark:     Occupancy [waves/SIMD]: 4 [-Rpass-analysis=kernel-resource-usage]\n")
+    build._check_waves(ok)
+    for bad in (ok.replace("SIMD]: 5", "SIMD]: 4"), ok.replace("lane]: 0", "lane]: 8")):
+        with pytest.raises(RuntimeError):
+            build._check_waves(bad)
+
+
 def test_workspace_query_is_pure_host_logic():
     """zqfp_gemm_workspace_bytes plans on the host (no GPU needed): zero for every benchmark
     configuration, [slices][M][Np] floats where K is split."""
