@@ -71,6 +71,18 @@ int zqfp_probe_force_decode_waves(int nw);
 int zqfp_probe_gemm_form(int64_t M, int64_t K, int64_t N, int G, int wbits,
                          int r, int accum, int have_workspace);
 
+/*
+ * zqfp_probe_left_form -- how a quantizer call forms the left factor T of a
+ * rank-r correction.  kind: 0 zqfp_quantize_act_fp8, 1 RMS normalisation, 2
+ * layer normalisation (with or without a residual), 3 ReLU, 4 gated unit;
+ * in_place: H lies over X or over the second operand.  Host only: nothing is
+ * enqueued.  Returns ZQFP_LEFT_* or ZQFP_E_SHAPE.
+ */
+#define ZQFP_LEFT_BLOCKS 1 /* a workgroup per token and 4 or 8 ranks (or, rank 8, a wave per token) */
+#define ZQFP_LEFT_ONE 2    /* a workgroup per token with all sums */
+#define ZQFP_LEFT_APART 3  /* a launch of its own behind the quantizer */
+int zqfp_probe_left_form(int64_t M, int64_t K, int r, int kind, int in_place);
+
 #ifdef __cplusplus
 }
 #endif

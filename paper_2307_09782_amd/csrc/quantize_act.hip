@@ -988,27 +988,33 @@ hipError_t launch_rows_lorc(const uint16_t* X, int64_t M, int64_t K, int64_t ldx
     return hipGetLastError();
 }
 
-// How the left factor of more than 8 ranks is formed (up to 8: by the workgroup or wave that quantizes the token).
-enum class LeftForm {
-    kBlocks,  // a workgroup per token and 8 ranks
-    kOne,     // a workgroup per token with up to 16 sums a thread
-    kApart    // k_lorc_left behind the quantizer
-};
+}  // namespace
 
 // In microseconds, graph-timed; b = blocks of 8 ranks.  Blocks cost about M b rows, kApart is flat up to 2000 tokens and then follows
 // the activations, so the line between them is one in M b^2: plain, 4096 elements, rank 40, 64 / 128 / 300 / 800 tokens: 13.6 / 12.0 / 20.8
 // / 44.4 in blocks, 13.2 / 13.1 / 13.4 / 14.4 apart; rank 24, 300 / 800: 11.0 / 21.9, 13.3 / 14.0.  Behind a normalisation kApart reads
 // the rows twice (rank 40, 128 / 300 / 800 tokens: 13.3 / 21.5 / 46.9, 19.6 / 20.1 / 21.8; 11008 elements: 38 / 76 / 184, 40 / 47 / 59), behind
-// the gated unit it evaluates it again (300 / 800: 22 / 46, 34 / 37; 11008: 72 / 178, 76 / 86).  Up to 16 ranks, one workgroup with all
-// sums passes the blocks between 300 and 800 tokens (4096, RMS normalisation: 12.4 and 16.3 against 9.6 and 17.3; 11008: 28.4 and 54.5
-// against 28.8 and 62.3) and is passed by kApart later (plain, 800 / 1500 tokens: 14.3 / 24.3, 13.9 / 15.8 apart; RMS 16.3 / 27.9, 22.0 / 24.3;
-// 20224, RMS, 1500: 104, 99; gated unit, 4000 x 4096: 52.7, 56.3).
+// the gated unit it evaluates it again (300 / 800: 22 / 46, 34 / 37; 11008: 72 / 178, 76 / 86).
+//
+// Up to 16 ranks there is one workgroup with all sums as well, which reads the row once.  The lines are set where neither side is slower than
+// that one by more than 4 % (7000 timings: the seven producers and sums, 13 row lengths, 24 token counts, ranks 9, 12, 15 and 16).  Blocks win
+// while both launches take as many rounds of workgroups: a row beyond 8192 elements behind a producer takes 1024 threads, one to a
+// compute unit, so up to 128 tokens (layer normalisation with a residual, 14336 elements, rank 16: 128 tokens 13.9 in blocks, 15.9; 256 tokens 25.0, 17.7); else up to 512 (RMS normalisation, 512 x 4096, rank 16: 10.9, 11.8),
+// the plain quantizer with ranks one at a time, whose six waves a SIMD take 768 tokens at once, up to those.  kApart pays off the sooner
+// the longer the sums take: sixteen ranks come in one vector load, fewer one by one (plain, 1024 x 8192, rank 16: 18.7, 27.9 apart;
+// rank 12: 58.5, 39.9).  Behind a normalisation its second reading of the rows counts (layer normalisation, 1400 x 8192, rank 16: 28.1, 52.6
+// apart; 4096 x 2048: 34.8, 22.7), behind the gated unit its second evaluation (4000 x 4096: 52.7, 56.3).
 LeftForm left_form(int64_t M, int64_t K, int r, int kind, bool in_place)
 {
     if (r <= 8) return LeftForm::kBlocks;
     if (r <= 16) {
-        if (!in_place && M <= (K > 8192 && kind != 0 ? 256 : 512)) return LeftForm::kBlocks;
-        const bool apart = kind == 0 || kind == 3 ? M >= 800 : kind == 4 ? false : M >= 1400;
+        const bool plain = kind == 0, whole = r == 16;
+        const int64_t blocks = !plain && K > 8192 ? 128 : plain && !whole && K <= 8192 ? 768 : 512;
+        if (!in_place && M <= blocks) return LeftForm::kBlocks;
+        bool apart;
+        if (plain || kind == 3) apart = whole ? M >= 1300 : plain || M >= 800;
+        else if (kind == 4) apart = false;
+        else apart = !whole ? M >= 1400 : K > 8192 ? M >= 1800 : M >= 1400 && M >= K;
         return apart ? LeftForm::kApart : LeftForm::kOne;
     }
     // with H over X or the second operand a row cannot be formed twice
@@ -1016,8 +1022,6 @@ LeftForm left_form(int64_t M, int64_t K, int r, int kind, bool in_place)
     const int64_t b = (r + 7) / 8, bound = kind == 0 || kind == 3 ? 3200 : kind == 4 ? (K > 8192 ? 6500 : 14000) : K > 8192 ? 3200 : 6000;
     return M * b * b > bound ? LeftForm::kApart : LeftForm::kBlocks;
 }
-
-}  // namespace
 
 hipError_t launch_quantize_act(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, uint8_t* Xq, float* sx,
                                const uint16_t* U, int r, float* T, const Producer& pr, hipStream_t s)

@@ -431,6 +431,12 @@ int zqfp_probe_gemm_form(int64_t M, int64_t K, int64_t N, int G, int wbits, int 
     return gemm_form(M, L, r, accum, have_workspace ? &L : nullptr);
 }
 
+int zqfp_probe_left_form(int64_t M, int64_t K, int r, int kind, int in_place)
+{
+    if (M <= 0 || K <= 0 || K % 128 != 0 || r < 1 || r > 64 || kind < 0 || kind > 4 || (kind != 0 && K > 32768)) return ZQFP_E_SHAPE;
+    return (int)zqfp::left_form(M, K, r, kind, in_place != 0);
+}
+
 int zqfp_probe_force_decode_waves(int nw)
 {
     if (nw != 8 && nw != 16) return ZQFP_E_SHAPE;

@@ -270,6 +270,13 @@ struct Producer {
     uint16_t* H;            // [M, K] bf16 dense: X + other rounded to bf16 (kinds 1, 2 with a residual)
     float eps;              // kinds 1, 2
 };
+// How the left factor of more than 8 ranks is formed (up to 8: by the workgroup or wave that quantizes the token).
+enum class LeftForm {
+    kBlocks = 1,  // a workgroup per token and 4 or 8 ranks
+    kOne,         // a workgroup per token with up to 16 sums a thread
+    kApart        // k_lorc_left behind the quantizer
+};
+LeftForm left_form(int64_t M, int64_t K, int r, int kind, bool in_place);  // in_place: H over X or the second operand
 hipError_t launch_quantize_act(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, uint8_t* Xq,
                                float* sx, const uint16_t* U, int r, float* T, const Producer& pr, hipStream_t s);
 hipError_t launch_pack_weight(const uint16_t* W, int64_t ldw, const BlobLayout& L, int mode,

@@ -26,6 +26,7 @@ SCALE_M1, SCALE_M2 = 1, 2
 OUT_F32, OUT_BF16 = 0, 1
 ACCUM_EXACT, ACCUM_FAST = 0, 1
 FORM_DECODE, FORM_MID, FORM_TILE, FORM_STREAM = 1, 2, 3, 4  # probe_gemm_form
+LEFT_BLOCKS, LEFT_ONE, LEFT_APART = 1, 2, 3  # probe_left_form
 
 _ERR = {-1: "ZQFP_E_NULL", -2: "ZQFP_E_SHAPE", -3: "ZQFP_E_ALIGN", -4: "ZQFP_E_MODE", -5: "ZQFP_E_HIP",
         -6: "ZQFP_E_WORKSPACE", -7: "ZQFP_E_BLOB"}
@@ -122,6 +123,8 @@ def lib():
         L.zqfp_probe_force_decode_waves.argtypes = [c.c_int]
         L.zqfp_probe_gemm_form.restype = c.c_int
         L.zqfp_probe_gemm_form.argtypes = [i64, i64, i64, c.c_int, c.c_int, c.c_int, c.c_int, c.c_int]
+        L.zqfp_probe_left_form.restype = c.c_int
+        L.zqfp_probe_left_form.argtypes = [i64, i64, c.c_int, c.c_int, c.c_int]
         L.zqfp_probe_mfma.restype = c.c_int
         L.zqfp_probe_mfma.argtypes = [p, p, c.c_int, c.c_int, p]
         native = _NoExtension
@@ -612,6 +615,15 @@ def probe_force_decode_waves(nw=8):
 def probe_gemm_form(M, K, N, G=128, wbits=4, r=0, accum=ACCUM_EXACT, have_workspace=True):
     """Which kernel (FORM_*) serves a GEMM call of this size, rank and accumulation mode; nothing is enqueued."""
     form = lib().zqfp_probe_gemm_form(M, K, N, G, wbits, r, accum, int(have_workspace))
+    if form < 0:
+        raise ZqfpError(form)
+    return form
+
+
+def probe_left_form(M, K, r, kind=0, in_place=False):
+    """How (LEFT_*) a quantizer call forms the left factor of a rank-r correction (kind: 0 plain, 1 RMS, 2 layer norm, 3 ReLU,
+    4 gated); nothing is enqueued."""
+    form = lib().zqfp_probe_left_form(M, K, r, kind, int(in_place))
     if form < 0:
         raise ZqfpError(form)
     return form

@@ -277,3 +277,31 @@ def test_library_is_built_by_hipcc_alone(monkeypatch, tmp_path):
     build.build_lib()
     assert len(commands) == len(build.sources()) + 1
     assert {cmd[0] for cmd in commands} == {build.HIPCC}
+
+
+B_, O, A = zqfp.LEFT_BLOCKS, zqfp.LEFT_ONE, zqfp.LEFT_APART
+
+
+@pytest.mark.parametrize("kind,M,K,r,form", [
+    # rows beyond 8192 elements behind a producer: the second block of ranks is a second round of workgroups from 129 tokens on
+    (2, 128, 13440, 16, B_), (2, 223, 13440, 16, O), (2, 168, 12288, 16, O), (1, 187, 9728, 15, O), (3, 220, 8832, 12, O), (4, 256, 11008, 9, O),
+    (1, 512, 4096, 16, B_), (1, 513, 4096, 16, O), (0, 512, 11008, 16, B_),
+    # the plain quantizer with ranks one at a time: 768 tokens in one round, apart behind that and for long rows
+    (0, 640, 128, 9, B_), (0, 768, 2048, 12, B_), (0, 769, 2048, 12, A), (0, 513, 20224, 9, A), (0, 720, 11008, 15, A),
+    # sixteen ranks in one load: apart pays off later, behind a normalisation the later the longer the row
+    (3, 1024, 8192, 16, O), (0, 1024, 8192, 16, O), (0, 800, 14336, 16, O), (0, 1300, 8192, 16, A), (3, 800, 8192, 15, A), (2, 1400, 8192, 16, O), (2, 1600, 2048, 16, O),
+    (1, 2048, 2048, 16, A), (2, 1400, 9088, 16, O), (2, 1800, 9088, 16, A), (1, 1400, 8192, 15, A), (4, 4096, 4096, 16, O)])
+def test_how_the_left_factor_is_formed(lib, kind, M, K, r, form):
+    """Host logic; each of these is where one form measured faster than another by 4 % or more, or a neighbour across such a line."""
+    assert zqfp.probe_left_form(M, K, r, kind) == form
+
+
+def test_left_form_with_a_row_that_cannot_be_formed_twice(lib):
+    """H over an operand: more than one workgroup per token would read what another has written."""
+    for kind in (1, 2, 4):
+        for M in (1, 16, 300, 5000):
+            for r in range(9, 65):
+                assert zqfp.probe_left_form(M, 4096, r, kind, in_place=True) != zqfp.LEFT_BLOCKS
+    for args in ((0, 4096, 8), (1, 4100, 8), (1, 4096, 0), (1, 4096, 65), (1, 4096, 8, 5), (1, 32896, 8, 1)):
+        with pytest.raises(zqfp.ZqfpError):
+            zqfp.probe_left_form(*args)
