@@ -41,11 +41,13 @@ __device__ inline void add_ranks(float (&acc)[RP], float x, const Ranks<RP>& u, 
 // from its wave's 512-element slice: consecutive lanes own consecutive k, so a wave's load of U
 // rows is one contiguous run (r = 8: 1 KB per instruction) instead of 64 scattered 16-byte pieces.
 // U points to the first of this workgroup's `rb` <= RP ranks, rows lie r elements apart.
-template <int RP>
+// How a row of U is read: as r allows, whole blocks in vector loads, or one rank after the other.
+enum class Rows { kAny, kWhole, kSingle };
+template <int RP, Rows ROWS>
 __device__ inline void lorc_accumulate(float (&acc)[RP], const float (&x)[8], const uint16_t* U, int64_t kbase, int64_t K, int r, int rb)
 {
     // K is a multiple of 128, not of 512: elements past the row's end are zero and meet a zeroed row of U
-    if ((r & (RP < 8 ? RP - 1 : 7)) == 0) {
+    if (ROWS == Rows::kWhole || (ROWS == Rows::kAny && (r & (RP < 8 ? RP - 1 : 7)) == 0)) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const bool live = kbase + 64 * i < K;
@@ -236,17 +238,17 @@ __device__ inline double sum_squares(double acc, uint4 v)
 // NT threads per token: 256 when there are tokens enough to fill the chip, 1024 for a handful of
 // tokens (decode), where one row's latency chain is all there is.  The gated unit in 1024 threads is held to 64 registers, so that two
 // tokens share a compute unit (4096 x 11008: 81 -> 61 us; the four that do not fit are the binary64 loop's).
-// With sums for a left factor and 256 threads a token is four waves, one a SIMD, so the waves a SIMD holds are the rounds of
-// 256 tokens a launch takes at once: the instances that fit into one round more by a few registers are held to it, none of them spills
+// With sixteen sums for a left factor and 256 threads a token is four waves, one a SIMD, so the waves a SIMD holds are the rounds of
+// 256 tokens a launch takes at once: the instances that miss one by a few registers are held to it, none of them spills
 // (five in 96 registers, the gated unit seven in 72; left alone four and five.  1166 x 384, RMS normalisation, rank 15: 26.1 -> 17.4 us;
 // 1268 x 640 with a residual, rank 9: 24.7 -> 17.0; gated, 1489 x 4736, rank 14: 96.2 -> 76.2).
 constexpr int waves_per_simd(int rp, int nt, int norm)
 {
     if (nt == 1024) return norm == 4 && rp == 0 ? 8 : 1;
     if (norm == 4) return rp == 16 ? 7 : 1;
-    return (rp == 16 && norm != 2) || (rp == 8 && norm == 0) ? 5 : 1;
+    return rp == 16 && norm != 2 ? 5 : 1;
 }
-template <int RP, int NT, int NORM>
+template <int RP, int NT, int NORM, Rows ROWS = Rows::kAny>
 __global__ __launch_bounds__(NT, waves_per_simd(RP, NT, NORM)) void k_quantize_act(const uint16_t* __restrict__ X, int64_t K, int64_t ldx,
                                                          uint8_t* __restrict__ Xq, float* __restrict__ sx,
                                                          const uint16_t* __restrict__ U, int r, float* __restrict__ T,
@@ -395,7 +397,7 @@ __global__ __launch_bounds__(NT, waves_per_simd(RP, NT, NORM)) void k_quantize_a
                     }
                     return;
                 }
-            lorc_accumulate<RP>(acc, x, U, (int64_t)(idx - lane) * 8 + lane, K, r, rb);
+            lorc_accumulate<RP, ROWS>(acc, x, U, (int64_t)(idx - lane) * 8 + lane, K, r, rb);
         };
 #pragma unroll
         for (int c = 0; c < kRegChunks; ++c) {
@@ -948,6 +950,22 @@ hipError_t launch_lorc_left(const uint16_t* X, int64_t M, int64_t K, int64_t ldx
     return hipGetLastError();
 }
 
+// The plain quantizer's blocks of eight ranks have an instance for each way to read U: with both in one, its registers leave room for
+// four waves per SIMD (97 of them) in place of five and seven, which a launch of 1025 to 1280 tokens pays with a second round
+// (1100 x 4096, rank 6: 26.6 -> 19.8 us; 1100 x 28672, rank 8: 50.0 -> 43.5).  Held to five waves in one instance, the loads of U no longer run
+// ahead of their sums (2048 x 28672, rank 8: 102, 69.7 now).
+template <int RP, int NT>
+void launch_plain(dim3 grid, hipStream_t s, const uint16_t* X, int64_t K, int64_t ldx, uint8_t* Xq, float* sx, const uint16_t* U, int r, float* T,
+                  const Producer& pr)
+{
+    if constexpr (RP == 8 && NT == 256) {
+        if (r % 8 == 0) hipLaunchKernelGGL((k_quantize_act<RP, NT, 0, Rows::kWhole>), grid, dim3(NT), 0, s, X, K, ldx, Xq, sx, U, r, T, pr);
+        else hipLaunchKernelGGL((k_quantize_act<RP, NT, 0, Rows::kSingle>), grid, dim3(NT), 0, s, X, K, ldx, Xq, sx, U, r, T, pr);
+    } else {
+        hipLaunchKernelGGL((k_quantize_act<RP, NT, 0>), grid, dim3(NT), 0, s, X, K, ldx, Xq, sx, U, r, T, pr);
+    }
+}
+
 // whether the bytes of two strided [M, K] bf16 matrices can meet
 bool overlap(const void* a, int64_t lda, const void* b, int64_t ldb, int64_t M, int64_t K)
 {
@@ -1000,7 +1018,7 @@ hipError_t launch_rows_lorc(const uint16_t* X, int64_t M, int64_t K, int64_t ldx
 // that one by more than 4 % (7000 timings: the seven producers and sums, 13 row lengths, 24 token counts, ranks 9, 12, 15 and 16).  Blocks win
 // while both launches take as many rounds of workgroups: a row beyond 8192 elements behind a producer takes 1024 threads, one to a
 // compute unit, so up to 128 tokens (layer normalisation with a residual, 14336 elements, rank 16: 128 tokens 13.9 in blocks, 15.9; 256 tokens 25.0, 17.7); else up to 512 (RMS normalisation, 512 x 4096, rank 16: 10.9, 11.8),
-// the plain quantizer with ranks one at a time, whose six waves a SIMD take 768 tokens at once, up to those.  kApart pays off the sooner
+// the plain quantizer with ranks one at a time, whose seven waves a SIMD take 896 tokens at once, up to 768.  kApart pays off the sooner
 // the longer the sums take: sixteen ranks come in one vector load, fewer one by one (plain, 1024 x 8192, rank 16: 18.7, 27.9 apart;
 // rank 12: 58.5, 39.9).  Behind a normalisation its second reading of the rows counts (layer normalisation, 1400 x 8192, rank 16: 28.1, 52.6
 // apart; 4096 x 2048: 34.8, 22.7), behind the gated unit its second evaluation (4000 x 4096: 52.7, 56.3).
@@ -1094,7 +1112,7 @@ hipError_t launch_quantize_act(const uint16_t* X, int64_t M, int64_t K, int64_t 
         case 2: ZQ_QUANT_N(RP, NT, 2); break;     \
         case 3: ZQ_QUANT_N(RP, NT, 3); break;     \
         case 4: ZQ_QUANT_N(RP, NT, 4); break;     \
-        default: ZQ_QUANT_N(RP, NT, 0); break;    \
+        default: launch_plain<RP, NT>(grid, s, X, K, ldx, Xq, sx, U, r, T, pr); break; \
         }                                         \
     } while (0)
 #define ZQ_QUANT(RP)                    \
