@@ -47,8 +47,24 @@ int zqfp_probe_mfma(const void *operands, void *sink, int iters,
  * (kg 1 or 2) and 128x128.  (0, 0, 0, 0) returns to automatic planning.
  * Process-wide, not meant for concurrent use with GEMM calls of other threads.
  * Returns ZQFP_OK or ZQFP_E_SHAPE.
+ *
+ * zqfp_probe_force_tile_kind -- the same where a shape has several kernels:
+ * 64x128 with kg 1 for E4M3 weights, three LDS stages and at most two workgroups
+ * per compute unit (occ 2) or two stages and three workgroups (occ 3, also what
+ * occ 0 and the call above take).  Any other shape takes occ 0 only.
  */
 int zqfp_probe_force_tile_plan(int bm, int bn, int ksplit, int kg);
+int zqfp_probe_force_tile_kind(int bm, int bn, int ksplit, int kg, int occ);
+
+/*
+ * zqfp_probe_tile_plan -- what the tiled kernel would take for a problem of this
+ * size if it served it (zqfp_probe_gemm_form says whether it does): plan[0..5]
+ * (host) = tile rows, tile columns, wave groups, workgroups per compute unit
+ * (where a shape has several kernels), K slices, k-tiles per slice.  Host only.
+ * Returns ZQFP_OK, ZQFP_E_SHAPE, ZQFP_E_MODE or ZQFP_E_NULL.
+ */
+int zqfp_probe_tile_plan(int64_t M, int64_t K, int64_t N, int wbits, int accum,
+                         int have_workspace, int *plan);
 
 /*
  * zqfp_probe_force_decode_waves -- tuning hook: 8 (default) or 16 waves per

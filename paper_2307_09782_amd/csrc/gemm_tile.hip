@@ -776,7 +776,7 @@ hipError_t launch_pick_w8(const uint8_t* Xq, const float* sx, int64_t M, const u
 #undef ZQ_TILE8
 }
 
-std::atomic<uint32_t> g_forced_plan{0};  // bm | bn << 10 | ksplit << 20 | kg << 28; 0 = automatic
+std::atomic<uint64_t> g_forced_plan{0};  // bm | bn << 10 | ksplit << 20 | kg << 28 | occ << 32; 0 = automatic
 
 }  // namespace
 
@@ -896,21 +896,23 @@ TilePlan plan_tiles(int64_t M, int64_t Np, int64_t nkt, int accum, int wbits, bo
     return p;
 }
 
-bool force_tile_plan(int bm, int bn, int ksplit, int kg)
+bool force_tile_plan(int bm, int bn, int ksplit, int kg, int occ)
 {
     if (bm == 0 && bn == 0 && ksplit == 0) { g_forced_plan.store(0); return true; }
     bool shape_ok = false;
     for (const TileKind& k : kTileKinds) shape_ok = shape_ok || (k.bm == bm && k.bn == bn && k.kg == kg);
-    if (!shape_ok || ksplit < 1 || ksplit > 64) return false;
-    g_forced_plan.store((uint32_t)bm | ((uint32_t)bn << 10) | ((uint32_t)ksplit << 20) | ((uint32_t)kg << 28));
+    const bool several = bm == 64 && bn == 128 && kg == 1;
+    if (!shape_ok || ksplit < 1 || ksplit > 64 || (occ != 0 && !(several && (occ == 2 || occ == 3)))) return false;
+    g_forced_plan.store((uint64_t)bm | (uint64_t)bn << 10 | (uint64_t)ksplit << 20 | (uint64_t)kg << 28 | (uint64_t)(occ == 0 ? 3 : occ) << 32);
     return true;
 }
 
-static TilePlan forced_plan(uint32_t f, int64_t nkt)
+static TilePlan forced_plan(uint64_t f, int64_t nkt)
 {
     TilePlan p;
     p.bm = (int)(f & 1023u); p.bn = (int)((f >> 10) & 1023u);
-    p.kg = (int)(f >> 28);
+    p.kg = (int)((f >> 28) & 15u);
+    p.occ = (int)(f >> 32);
     const int want = (int)std::min<int64_t>((int64_t)((f >> 20) & 255u), nkt);
     p.kslice = (int)((nkt + want - 1) / want);
     p.ksplit = (int)((nkt + p.kslice - 1) / p.kslice);
@@ -920,7 +922,7 @@ static TilePlan forced_plan(uint32_t f, int64_t nkt)
 
 TilePlan effective_tile_plan(int64_t M, int64_t Np, int64_t nkt, int accum, int wbits, bool may_split)
 {
-    const uint32_t f = g_forced_plan.load(std::memory_order_relaxed);
+    const uint64_t f = g_forced_plan.load(std::memory_order_relaxed);
     if (f == 0) return plan_tiles(M, Np, nkt, accum, wbits, may_split);
     TilePlan p = forced_plan(f, nkt);
     if (wbits == 8 && (p.bn != 128 || (p.bm != 64 && p.bm != 128) || p.kg == 4)) {  // not a shape of the E4M3 form
@@ -933,7 +935,7 @@ TilePlan effective_tile_plan(int64_t M, int64_t Np, int64_t nkt, int accum, int 
 
 int tile_workspace_slices(int64_t M, int64_t Np, int64_t nkt)
 {
-    const uint32_t f = g_forced_plan.load(std::memory_order_relaxed);
+    const uint64_t f = g_forced_plan.load(std::memory_order_relaxed);
     return f == 0 ? plan_slices(M, Np, nkt).ksplit : forced_plan(f, nkt).ksplit;
 }
 

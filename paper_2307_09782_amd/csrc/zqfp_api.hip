@@ -420,7 +420,23 @@ int zqfp_probe_stream_read(const void* src, int64_t bytes, void* sink, int workg
 
 int zqfp_probe_force_tile_plan(int bm, int bn, int ksplit, int kg)
 {
-    return zqfp::force_tile_plan(bm, bn, ksplit, kg) ? ZQFP_OK : ZQFP_E_SHAPE;
+    return zqfp::force_tile_plan(bm, bn, ksplit, kg, 0) ? ZQFP_OK : ZQFP_E_SHAPE;
+}
+
+int zqfp_probe_force_tile_kind(int bm, int bn, int ksplit, int kg, int occ)
+{
+    return zqfp::force_tile_plan(bm, bn, ksplit, kg, occ) ? ZQFP_OK : ZQFP_E_SHAPE;
+}
+
+int zqfp_probe_tile_plan(int64_t M, int64_t K, int64_t N, int wbits, int accum, int have_workspace, int* plan)
+{
+    if (!plan) return ZQFP_E_NULL;
+    if (M <= 0 || K <= 0 || K % 128 != 0 || N <= 0 || (wbits != 4 && wbits != 8)) return ZQFP_E_SHAPE;
+    if (accum != ZQFP_ACCUM_EXACT && accum != ZQFP_ACCUM_FAST) return ZQFP_E_MODE;
+    const zqfp::TilePlan p = zqfp::effective_tile_plan(M, (N + 15) / 16 * 16, K / 128, accum, wbits, wbits == 4 && have_workspace != 0);
+    const int out[6] = {p.bm, p.bn, p.kg, p.occ, p.ksplit, p.kslice};
+    std::memcpy(plan, out, sizeof out);
+    return ZQFP_OK;
 }
 
 int zqfp_probe_gemm_form(int64_t M, int64_t K, int64_t N, int G, int wbits, int r, int accum, int have_workspace)

@@ -309,7 +309,7 @@ hipError_t launch_gemm_mid(const uint8_t* Xq, const float* sx, int64_t M, const 
 // The plan the tiled form runs for a problem, unless the tuning hook has fixed one (tile shape and number of K slices for every
 // following call; 0, 0, 0 returns to automatic planning; false = not a shape the kernel has).  may_split: there is a workspace.
 TilePlan effective_tile_plan(int64_t M, int64_t Np, int64_t nkt, int accum, int wbits, bool may_split);
-bool force_tile_plan(int bm, int bn, int ksplit, int kg);
+bool force_tile_plan(int bm, int bn, int ksplit, int kg, int occ);
 
 // workspace: plan_decode(nkt).chunks * M * Np floats when K has more than 64 k-tiles (else unused)
 // X != nullptr: the fused form (gemm_decode_fused_supported): bfloat16 activations, quantized in the kernel's

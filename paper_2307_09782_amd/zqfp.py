@@ -119,6 +119,10 @@ def lib():
         L.zqfp_probe_stream_read.argtypes = [p, i64, p, c.c_int, p]
         L.zqfp_probe_force_tile_plan.restype = c.c_int
         L.zqfp_probe_force_tile_plan.argtypes = [c.c_int, c.c_int, c.c_int, c.c_int]
+        L.zqfp_probe_force_tile_kind.restype = c.c_int
+        L.zqfp_probe_force_tile_kind.argtypes = [c.c_int, c.c_int, c.c_int, c.c_int, c.c_int]
+        L.zqfp_probe_tile_plan.restype = c.c_int
+        L.zqfp_probe_tile_plan.argtypes = [i64, i64, i64, c.c_int, c.c_int, c.c_int, c.POINTER(c.c_int)]
         L.zqfp_probe_force_decode_waves.restype = c.c_int
         L.zqfp_probe_force_decode_waves.argtypes = [c.c_int]
         L.zqfp_probe_gemm_form.restype = c.c_int
@@ -601,10 +605,18 @@ def probe_mfma(operands, sink, iters, workgroups):
     return 2.0 * 16 * 16 * 128 * 32 * 8 * iters * workgroups
 
 
-def probe_force_tile_plan(bm=0, bn=0, ksplit=0, kg=1):
-    """Tuning hook: fix tile shape, wave groups and number of K slices of the tiled GEMM for the calls that follow
-    (0, 0, 0 = plan automatically again)."""
-    _check(lib().zqfp_probe_force_tile_plan(bm, bn, ksplit, kg if bm else 0))
+def probe_force_tile_plan(bm=0, bn=0, ksplit=0, kg=1, occ=0):
+    """Tuning hook: fix tile shape, wave groups, number of K slices and, where a shape has several kernels, workgroups per compute unit
+    of the tiled GEMM for the calls that follow (0, 0, 0 = plan automatically again)."""
+    _check(lib().zqfp_probe_force_tile_kind(bm, bn, ksplit, kg if bm else 0, occ))
+
+
+def probe_tile_plan(M, K, N, wbits=4, accum=ACCUM_EXACT, have_workspace=True):
+    """(tile rows, tile columns, wave groups, workgroups per compute unit, K slices, k-tiles per slice) that the tiled GEMM takes for a
+    problem of this size where it serves it; nothing is enqueued."""
+    plan = (ctypes.c_int * 6)()
+    _check(lib().zqfp_probe_tile_plan(M, K, N, wbits, accum, int(have_workspace), plan))
+    return tuple(plan)
 
 
 def probe_force_decode_waves(nw=8):

@@ -769,18 +769,18 @@ def test_gemm_every_tile_shape_with_and_without_a_k_split(bm, bn, kg):
         zqfp.probe_force_tile_plan(0, 0, 0)
 
 
-@pytest.mark.parametrize("bm,bn,kg", [(64, 128, 1), (64, 128, 2), (64, 192, 1), (64, 192, 2), (64, 256, 1), (64, 256, 2),
+@pytest.mark.parametrize("bm,bn,kg", [(64, 128, 1), (64, 128, 2), (64, 192, 1), (64, 192, 2), (64, 256, 1), (64, 256, 2), (64, 64, 4), (64, 96, 4), (64, 128, 4),
                                       (128, 128, 1), (128, 192, 1), (128, 256, 1), (256, 256, 1)])
 def test_gemm_every_tile_shape_on_pipelines_shorter_than_the_stages(bm, bn, kg):
-    """Four k-tiles in all, cut so that a wave group multiplies four, two or a single one: fewer than the LDS
-    stages it keeps in flight (two or three), the case in which the pipeline's first step is also its last."""
+    """Four k-tiles in all, cut so that a wave group multiplies four, two, a single one or (four groups, two slices) none but zeros:
+    fewer than the LDS stages it keeps in flight (two or three), the case in which the pipeline's first step is also its last."""
     M, K, N, G, mode, r = 300, 512, 1000, 128, 1, 0
     try:
         for ksplit in ((1, 2, 4) if kg == 1 else (1, 2)):
             zqfp.probe_force_tile_plan(bm, bn, ksplit, kg)
             for rep in range(2):  # a fragment register read before its data arrived would differ from run to run
                 Y, Y_o, Sabs = _gemm_case(M, K, N, G, mode, r)
-                check_gemm(Y, Y_o, Sabs, f"{bm}x{bn} tiles, {kg} wave group(s), {K // 128 // ksplit // kg} k-tile(s) per group")
+                check_gemm(Y, Y_o, Sabs, f"{bm}x{bn} tiles, {kg} wave group(s), {K // 128 // ksplit} k-tile(s)")
     finally:
         zqfp.probe_force_tile_plan(0, 0, 0)
 
@@ -790,9 +790,9 @@ def test_gemm_repeated_launches_give_the_same_bits_on_every_tile_shape():
     launch; so every tile shape (FP4 and FP8 weights, both accumulation modes, unsplit and with K in slices) is
     launched several times on ragged problems with long and with very short pipelines and the outputs are
     compared bit for bit.  (What the bits should be is the other tests' business.)"""
-    shapes4 = [(64, 128, 1), (64, 128, 2), (64, 192, 1), (64, 192, 2), (64, 256, 1), (64, 256, 2),
-               (128, 128, 1), (128, 192, 1), (128, 256, 1), (256, 256, 1)]
-    shapes8 = [(64, 128, 1), (64, 128, 2), (128, 128, 1)]
+    shapes4 = [(64, 128, 1, 0), (64, 128, 2, 0), (64, 192, 1, 0), (64, 192, 2, 0), (64, 256, 1, 0), (64, 256, 2, 0), (64, 64, 4, 0),
+               (64, 96, 4, 0), (64, 128, 4, 0), (128, 128, 1, 0), (128, 192, 1, 0), (128, 256, 1, 0), (256, 256, 1, 0)]
+    shapes8 = [(64, 128, 1, 2), (64, 128, 1, 3), (64, 128, 2, 0), (128, 128, 1, 0)]
     try:
         for M, K, N in ((300, 1536, 1000), (531, 256, 520), (77, 128, 200), (260, 2304, 264)):
             cfg = inputs.Config("d", K, N, (M,), 128, 1, 0.01, 0, 20.0, 0, 5)
@@ -800,16 +800,16 @@ def test_gemm_repeated_launches_give_the_same_bits_on_every_tile_shape():
             Xq, sx = zqfp.quantize_act_fp8(bf16_tensor(inputs.make_x(cfg, M)))
             p4, p8 = zqfp.pack_weight_fp4(W, 128, 1), zqfp.pack_weight_fp8(W, 128, 1)
             for wb, shapes in ((4, shapes4), (8, shapes8)):
-                for bm, bn, kg in shapes:
+                for bm, bn, kg, occ in shapes:
                     for ksplit in ((1, 2, 3) if wb == 4 else (1,)):
-                        if K // 128 < ksplit * kg:
+                        if K // 128 < ksplit:
                             continue
                         for accum in (zqfp.ACCUM_EXACT, zqfp.ACCUM_FAST):
-                            zqfp.probe_force_tile_plan(bm, bn, ksplit, kg)
+                            zqfp.probe_force_tile_plan(bm, bn, ksplit, kg, occ)
                             outs = [zqfp.w4a8_gemm(Xq, sx, p4, N, 128, accum=accum) if wb == 4
                                     else zqfp.w8a8_gemm(Xq, sx, p8, N, 128, accum=accum) for _ in range(5)]
                             torch.cuda.synchronize()
                             assert all(torch.equal(outs[0], o) for o in outs[1:]), \
-                                f"wb {wb} M {M} K {K} N {N}: {bm}x{bn} tiles, {kg} group(s), K in {ksplit}, accum {accum}"
+                                f"wb {wb} M {M} K {K} N {N}: {bm}x{bn} tiles, {kg} group(s), occ {occ}, K in {ksplit}, accum {accum}"
     finally:
         zqfp.probe_force_tile_plan(0, 0, 0)

@@ -40,6 +40,7 @@ def test_slices_that_do_not_come_out_even(shape, ksplit, G):
 
 def test_planner_takes_them():
     """Where they win, and the estimate says so: a few tiles on a short and on a long K."""
-    for M, K, N in ((150, 4096, 4096), (257, 11008, 4096), (100, 4096, 12288)):
+    for M, K, N, kg in ((150, 4096, 4096, 4), (257, 11008, 4096, 4), (100, 4096, 12288, 4)):
         assert zqfp.probe_gemm_form(M, K, N) == zqfp.FORM_TILE
+        assert zqfp.probe_tile_plan(M, K, N)[2] == kg
         _check(M, K, N, 128, 1, 0, 4)

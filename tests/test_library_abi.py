@@ -305,3 +305,23 @@ def test_left_form_with_a_row_that_cannot_be_formed_twice(lib):
     for args in ((0, 4096, 8), (1, 4100, 8), (1, 4096, 0), (1, 4096, 65), (1, 4096, 8, 5), (1, 32896, 8, 1)):
         with pytest.raises(zqfp.ZqfpError):
             zqfp.probe_left_form(*args)
+
+
+def test_tile_plan_query_and_hook(lib):
+    """The plan of a problem, what the hook puts in its place (the E4M3 form's two kernels of one shape included), and what both refuse."""
+    try:
+        for occ in (2, 3):
+            zqfp.probe_force_tile_plan(64, 128, 1, 1, occ)
+            assert zqfp.probe_tile_plan(1000, 4096, 11008, wbits=8) == (64, 128, 1, occ, 1, 32)
+        zqfp.probe_force_tile_plan(64, 96, 3, 4)
+        assert zqfp.probe_tile_plan(90, 2688, 210)[:3] == (64, 96, 4) and zqfp.probe_tile_plan(90, 2688, 210)[4:] == (3, 7)
+        assert zqfp.probe_tile_plan(90, 2688, 210, have_workspace=False)[4:] == (1, 21)
+        for args in ((64, 64, 1, 1), (64, 128, 1, 3), (128, 128, 1, 2), (64, 128, 65, 1), (64, 128, 1, 1, 4), (64, 128, 1, 2, 2), (128, 128, 1, 1, 2)):
+            with pytest.raises(zqfp.ZqfpError):
+                zqfp.probe_force_tile_plan(*args)
+    finally:
+        zqfp.probe_force_tile_plan()
+    assert zqfp.probe_tile_plan(257, 11008, 4096)[2] == 4
+    for args in ((0, 4096, 64), (64, 4100, 64), (64, 4096, 0), (64, 4096, 64, 5), (64, 4096, 64, 4, 2)):
+        with pytest.raises(zqfp.ZqfpError):
+            zqfp.probe_tile_plan(*args)
