@@ -33,8 +33,9 @@ def sources():
 # Kernels that issue LDS reads by hand (inline asm) and wait for them by count: a register spill
 # between such a read and its wait would save a value that has not arrived yet, so these must
 # compile without scratch memory.  The compiler's resource remarks are checked after every build.
-# The register-fed GEMM has no hand-issued reads, but a spill inside its loop costs a quarter of its time.
-NO_SCRATCH_KERNELS = ("k_gemm_tile", "k_gemm_mid")
+# The register-fed GEMM has no hand-issued reads, but a spill inside its loop costs a quarter of its time.  GPTQ's sums of a panel
+# are meant to stay in registers between two panels, where nothing hides a trip through memory.
+NO_SCRATCH_KERNELS = ("k_gemm_tile", "k_gemm_mid", "k_gptq")
 # Waves per SIMD that a kernel's registers must leave room for, by its mangled name: one less is a round of workgroups more.
 MIN_WAVES = {"k_quantize_actILi16ELi256ELi0E": 5, "k_quantize_actILi16ELi256ELi1E": 5, "k_quantize_actILi16ELi256ELi3E": 5,
              "k_quantize_actILi16ELi256ELi4E": 7, "k_quantize_actILi8ELi256ELi0E": 5}

@@ -27,8 +27,10 @@
 // K^2 N / 2 multiply-adds are the bound: 1.34 ms at the 154 TFLOP/s that a large float32 product reaches, for
 // 4096 x 12288; K^2 / 2 floats of U per workgroup come from L2.  Measured, G = 128, M1, one after the other -> side by side:
 // 4096 x 12288 3670 -> 2272 us, 4096 x 4096 2019 -> 1077, 4096 x 16384 4305 -> 2913, 6144 x 12288 7903 -> 4683, 1024 x 12288
-// 381 -> 288; G = 256, 4096 x 12288 3953 -> 2576 (there by the eight waves alone).  The matrix cores are then 59 % busy over the
-// whole run; U's reads hit L2 at 226 cycles and hold nothing up.  C is the least that lets every workgroup have a
+// 381 -> 288; G = 256, 4096 x 12288 3953 -> 2576 (there by the eight waves alone).  With the sums in registers for every width, where
+// 48 and 64 channels had 80 and 144 bytes a lane of them in scratch memory: 4096 x 12288 2272 -> 2165, 4096 x 16384 2920 -> 2623, 4096 x
+// 4096 (16 channels) unchanged, G = 256, 4096 x 12288 2573 -> 2430, 2048 x 16384 1023 -> 915.  The matrix cores were 59 % busy over
+// the 2272 us; U's reads hit L2 at 226 cycles and hold nothing up.  C is the least that lets every workgroup have a
 // compute unit of its own, so that N = 4096 runs on all of them as N = 12288 does.
 #include "zqfp_internal.h"
 
@@ -211,6 +213,7 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 #pragma unroll
                             for (int t = 0; t < NT; ++t) w[t] -= sum.acc[q][t][i];
                         }
+                        asm volatile("" ::"n"(q));  // keeps the four apart: folded into one with a run-time q they would put the sums in scratch memory
                     }
             }
             __syncthreads();
@@ -267,9 +270,15 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     auto taken_off = [&]() __attribute__((always_inline)) {
         for (int round = 0; round < 5; ++round) __syncthreads();
     };
+    // tid, but not as a value known before: the addresses of a copy of a whole panel, the same for every panel, would be formed ahead of
+    // all panels, and kept in scratch memory
+    auto here = [](int i) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(i));
+        return i;
+    };
     // the panel's weights, or what has been held of it, into s_w, from which the sums are taken off then
     auto fill = [&](int64_t i0, bool from_held) __attribute__((always_inline)) {
-        for (int idx = tid; idx < kPanel * C; idx += 256) {
+        for (int idx = here(tid); idx < kPanel * C; idx += 256) {
             const int r = idx / C, c = idx % C;
             s_w[r][c] = from_held ? held[idx] : n0 + c < L.N ? bf16_bits_to_f32(W[(i0 + r) * ldw + n0 + c]) : 0.0f;
         }
@@ -343,7 +352,7 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             fill(i0 + kPanel, false);
             taken_off();
             const float m = partial_max(0, kPanel, 0.0f);
-            for (int idx = tid; idx < kPanel * C; idx += 256) held[idx] = s_w[idx / C][idx % C];
+            for (int idx = here(tid); idx < kPanel * C; idx += 256) held[idx] = s_w[idx / C][idx % C];
             __syncthreads();
             fill(i0, false);
             taken_off();
@@ -463,7 +472,7 @@ __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             }
         }
         if (more) {
-            for (int idx = tid; idx < kPanel * C; idx += 256) s_w[idx / C][idx % C] = bf16_bits_to_f32(s_next[idx]);
+            for (int idx = here(tid); idx < kPanel * C; idx += 256) s_w[idx / C][idx % C] = bf16_bits_to_f32(s_next[idx]);
             first_rows(i0 + kPanel);
             taken_off();
         } else if (!ahead) {

@@ -162,6 +162,18 @@ def test_build_rejects_spills_in_the_register_fed_gemm():
         build._check_no_scratch(spilled)
 
 
+def test_build_rejects_scratch_memory_in_gptq():
+    """The remarks of the 48-channel instance with its sums in registers, and with a part of them behind a run-time index."""
+    from paper_2307_09782_amd import build
+    ok = ("x.hip:1:1: remark: Function Name: _ZN4zqfp12_GLOBAL__N_16k_gptqILi3ELi1EEEvPKtlPKf [-Rpass-analysis=kernel-resource-usage]\n"
+          "x.hip:1:1: remark:     ScratchSize [bytes/lane]: 0 [-Rpass-analysis=kernel-resource-usage]\n"
+          "x.hip:1:1: remark:     VGPRs Spill: 0 [-Rpass-analysis=kernel-resource-usage]\n")
+    build._check_no_scratch(ok)
+    for bad in (ok.replace("lane]: 0", "lane]: 80"), ok.replace("Spill: 0", "Spill: 4")):
+        with pytest.raises(RuntimeError):
+            build._check_no_scratch(bad)
+
+
 def test_build_rejects_quantizers_that_leave_room_for_fewer_waves():
     """The remarks of the sums-of-sixteen quantizer as they are, and with what a few registers more would make of them."""
     from paper_2307_09782_amd import build
