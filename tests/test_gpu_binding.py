@@ -15,14 +15,31 @@ class Nothing:
     quantize = gemm = linear = staticmethod(lambda *a: None)
 
 
-def _both(call, monkeypatch):
+class Recorder:
+    """In the module's place: the module, and whether it took each call."""
+
+    def __init__(self, native):
+        self.native, self.took = native, []
+
+    def __getattr__(self, name):
+        def call(*a):
+            done = getattr(self.native, name)(*a)
+            self.took.append(done is not None)
+            return done
+        return call
+
+
+def _both(call, monkeypatch, taken=True):
+    """The public call with the module, which has to do it itself (or, not `taken`, to leave it), and with the Python code alone."""
     zqfp.lib()
-    native = zqfp._native
-    got = call()
+    native = Recorder(zqfp._native)
+    with monkeypatch.context() as m:
+        m.setattr(zqfp, "_native", native)
+        got = call()
+    assert native.took == [taken]
     with monkeypatch.context() as m:
         m.setattr(zqfp, "_native", Nothing)
         want = call()
-    assert zqfp._native is native
     got, want = (x if isinstance(x, tuple) else (x,) for x in (got, want))
     assert len(got) == len(want)
     for a, b in zip(got, want):
@@ -42,11 +59,12 @@ def _state(M=20, K=512, N=272, r=8):
 def test_same_results(M, rank, monkeypatch):
     s = _state(M)
     X, R, g, b, U = s["X"], s["R"], s["g"], s["b"], s["U"] if rank else None
-    for call in (lambda: zqfp.quantize_act_fp8(X, U), lambda: zqfp.rmsnorm_quantize_act_fp8(X, g, 1e-5, U), lambda: zqfp.rmsnorm_quantize_act_fp8(X, g, 1, U),
+    for call in (lambda: zqfp.quantize_act_fp8(X, U), lambda: zqfp.rmsnorm_quantize_act_fp8(X, g, 1e-5, U),
                  lambda: zqfp.layernorm_quantize_act_fp8(X, g, b, 1e-5, U), lambda: zqfp.relu_quantize_act_fp8(X, U), lambda: zqfp.swiglu_quantize_act_fp8(X, R, U),
                  lambda: zqfp.add_norm_quantize_act_fp8(X, R, g, 1e-5, None, U), lambda: zqfp.add_norm_quantize_act_fp8(X, R, g, 1e-5, b, U),
                  lambda: zqfp.relu_quantize_act_fp8(torch.cat([X, R], 1)[:, :X.shape[1]], U)):
         _both(call, monkeypatch)
+    _both(lambda: zqfp.rmsnorm_quantize_act_fp8(X, g, 1, U), monkeypatch, taken=False)  # eps is no float
     T = zqfp.quantize_act_fp8(X, s["U"])[2] if rank else None
     V = s["V"] if rank else None
     Xq, sx = zqfp.quantize_act_fp8(X)
@@ -78,18 +96,52 @@ def test_what_was_refused_is_refused():
             call()
 
 
-def test_on_a_side_stream_and_under_a_function_mode():
+@pytest.mark.parametrize("M, K, rank", [(16, 4096, 0), (17, 4096, 0), (16, 4224, 0), (16, 4096, 8), (1, 4096, 0)])
+def test_linear_with_and_without_codes(M, K, rank, monkeypatch):
+    """At the edges of the form that needs no room for codes: the library refuses the module's call if the module made none where it should."""
+    s = _state(M, K, 272, rank or 8)
+    p4 = zqfp.pack_weight_fp4(s["W"], 128, 1)
+    _both(lambda: zqfp.w4a8_linear(s["X"], p4, s["N"], 128, *((s["U"], s["V"]) if rank else ())), monkeypatch)
+
+
+def _captured_calls(s):
+    """Each call that the module does itself, once: what it reads is s["X"], or the codes behind it."""
+    native, X, N, f32 = zqfp._native, s["X"], s["N"], torch.float32
+    return [native.quantize(0, X, None, None, None, None, s["U"]), native.quantize(1, X, s["R"], s["g"], None, 1e-5, None),
+            (native.gemm(4, s["Xq"], s["sx"], s["p4"], N, 128, None, None, f32, 0),), (native.gemm(8, s["Xq"], s["sx"], s["p8"], N, 128, None, None, f32, 0),),
+            (native.linear(X, s["p4"], N, 128, s["U"], s["V"], f32, 0),)]
+
+
+def test_on_a_side_stream():
+    """Captured on a side stream and replayed with other inputs: a launch on any other stream would be refused there, or would be missing from
+    the replay."""
     s = _state(200)
-    want = zqfp.quantize_act_fp8(s["X"], s["U"])
-    stream = torch.cuda.Stream()
-    stream.wait_stream(torch.cuda.current_stream())
-    with torch.cuda.stream(stream):
-        got = zqfp.quantize_act_fp8(s["X"], s["U"])
-    stream.synchronize()
-    with torch.device("cuda"):  # a torch function mode: the Python code, whose allocations it may see
-        also = zqfp.quantize_act_fp8(s["X"], s["U"])
-    for a, b, c in zip(want, got, also):
-        assert torch.equal(a, b) and torch.equal(a, c)
+    s["p4"], s["p8"] = zqfp.pack_weight_fp4(s["W"], 128, 1), zqfp.pack_weight_fp8(s["W"], 128, 1)
+    s["Xq"], s["sx"] = zqfp.quantize_act_fp8(s["X"])
+    assert all(x is not None for done in _captured_calls(s) for x in done)  # kernels loaded
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        got = _captured_calls(s)
+    assert all(done is not None and done[0] is not None for done in got)
+    for scale in (0.5, 3.0):
+        other = (s["X"].flip(0) * scale).contiguous()
+        codes, sx = zqfp.quantize_act_fp8(other)
+        s["X"].copy_(other), s["Xq"].copy_(codes), s["sx"].copy_(sx)
+        graph.replay()
+        torch.cuda.synchronize()
+        for done, want in zip(got, _captured_calls(s)):
+            assert len(done) == len(want) and all(torch.equal(a, b) for a, b in zip(done, want))
+
+
+def test_under_a_function_mode(monkeypatch):
+    """A torch function mode: the Python code, whose allocations it may see."""
+    s = _state(200)
+
+    def call():
+        with torch.device("cuda"):
+            return zqfp.quantize_act_fp8(s["X"], s["U"])
+    _both(call, monkeypatch, taken=False)
 
 
 # in the order in which the module takes them; the others are host arithmetic
