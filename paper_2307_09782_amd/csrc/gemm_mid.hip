@@ -313,7 +313,8 @@ bool gemm_mid_wins(int64_t M, const BlobLayout& L, int r, int accum, bool worksp
             if (fast && r < 8 && L.nkt <= 40 && L.nstrips >= 192 && (L.nkt * L.nstrips >= 5120 || L.nstrips > 224)) return false;
         }
         if (L.N < 64) return true;  // the tiled kernel has no such tile
-        // 64 x 128 tiles, one per compute unit, no K-split: fitted (4096 x 12288, 64 tokens: 24.4 -> 18.8; 28672 x 8192:
+        // 64 x 128 tiles in two wave groups, one per compute unit, no K-split: fitted when these took k-tiles in pairs only (6.9 + 0.434 a k-tile by the
+        // tiled kernel's present fit) (4096 x 12288, 64 tokens: 24.4 -> 18.8; 28672 x 8192:
         // 111 -> 64.7; 14336 x 2048, 300 tokens: 57.0 -> 32.5).  Near 256 tiles the tiled kernel is 6 to 13 % above its estimate and
         // this one, bound by HBM or in a second round, 10 to 25 % (12288 x 16384, 96 tokens: 57.9 against 65.8 us; 28672 x 8192, 256 tokens:
         // 119 against 140; 8192 x 28672, 32 tokens: 49.3 against 53.3).

@@ -464,8 +464,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) __attribute__((amdgpu_
     // ---- main loop.  Step kt computes stage kt % NSTAGE; the k-tiles behind it (kt + 1 .. kt + NSTAGE - 1)
     // are in the other stages or on their way, k-tile kt + NSTAGE is requested into
     // stage kt % NSTAGE behind the step's barrier: NSTAGE - 1 steps of slack for the memory latency
-    // (most of one with two stages, where two workgroups share a compute unit and fill each other's
-    // gaps; five with the six stages of the small tile, whose lone workgroup is a weight stream).  The loop is rotated so that no LDS read is in flight across its back edge: an iteration is
+    // (most of one with two stages, where the workgroups or wave groups that share a compute unit fill each other's
+    // gaps; two with three stages).  The loop is rotated so that no LDS read is in flight across its back edge: an iteration is
     // the last row block of step kt followed by the first blocks of step kt + 1 and that step's barrier,
     // at which the loads of k-tile kt + 2 must have landed and only younger ones (those of k-tiles
     // kt + 3 .. kt + NSTAGE) may be outstanding.  The last steps request nothing and are peeled.

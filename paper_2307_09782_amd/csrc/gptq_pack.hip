@@ -29,8 +29,8 @@
 // 4096 x 12288 3670 -> 2272 us, 4096 x 4096 2019 -> 1077, 4096 x 16384 4305 -> 2913, 6144 x 12288 7903 -> 4683, 1024 x 12288
 // 381 -> 288; G = 256, 4096 x 12288 3953 -> 2576 (there by the eight waves alone).  With the sums in registers for every width, where
 // 48 and 64 channels had 80 and 144 bytes a lane of them in scratch memory: 4096 x 12288 2272 -> 2165, 4096 x 16384 2920 -> 2623, 4096 x
-// 4096 (16 channels) unchanged, G = 256, 4096 x 12288 2573 -> 2430, 2048 x 16384 1023 -> 915.  The matrix cores were 59 % busy over
-// the 2272 us; U's reads hit L2 at 226 cycles and hold nothing up.  C is the least that lets every workgroup have a
+// 4096 (16 channels) unchanged, G = 256, 4096 x 12288 2573 -> 2430, 2048 x 16384 1023 -> 915.  The matrix cores are then 62 % busy over
+// the whole run; U's reads hit L2 at 226 cycles and hold nothing up.  C is the least that lets every workgroup have a
 // compute unit of its own, so that N = 4096 runs on all of them as N = 12288 does.
 #include "zqfp_internal.h"
 

@@ -243,7 +243,9 @@ D, M_, T, S = zqfp.FORM_DECODE, zqfp.FORM_MID, zqfp.FORM_TILE, zqfp.FORM_STREAM
     (8, 16, 4096, 4096, 0, 0, D), (4, 16, 28672, 4096, 0, 0, D), (4, 16, 4096, 12288, 0, 0, D)])
 def test_which_kernel_serves_a_gemm(lib, wbits, M, K, N, r, accum, form):
     """The choice is host logic; each of these is where one kernel measured faster than the other by 3 % or more
-    (the figures stand at the rule), or a plain member of a form's range."""
+    (the figures stand at the rule), or a plain member of a form's range.  With 17 to 64 tokens, and where very many tokens meet few
+    channels, "the other" is the tiled kernel with two by two waves a tile, against which the line was drawn: with four wave groups it is
+    ahead of the form for a few dozen tokens at some of these points, by less than 10 %."""
     assert zqfp.probe_gemm_form(M, K, N, 128, wbits, r, accum) == form
 
 
